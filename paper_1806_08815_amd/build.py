@@ -23,6 +23,8 @@ LIB = os.path.join(HERE, "libdapt.so")
 SOURCES = ["da_kernels.hip", "da_probe.hip", "da_tables.cpp", "da_api.cpp", "da_server.cpp",
            "da_noalloc.hip"]
 HEADERS = ["da_internal.h", "da_runtime.h"]
+# compiled in parts (-DDAPT_PART=n), side by side: the step kernel's variants
+PARTS = {"da_kernels.hip": 5}
 
 
 def source_hash() -> str:
@@ -55,9 +57,13 @@ def build_library(verbose: bool = False) -> str:
               "-Wall", "-Wno-unused-function", "-I", INCLUDE, "-I", CSRC]
     build_id = source_hash()
 
-    def compile_one(src):
-        obj = os.path.join(bdir, os.path.splitext(src)[0] + ".o")
+    def compile_one(unit):
+        src, part = unit
+        stem = os.path.splitext(src)[0] + ("" if part is None else str(part))
+        obj = os.path.join(bdir, stem + ".o")
         cmd = [hipcc(), *common, "-c", os.path.join(CSRC, src), "-o", obj]
+        if part is not None:
+            cmd.insert(1, f"-DDAPT_PART={part}")
         if src == "da_api.cpp":
             cmd.insert(1, f'-DDAPT_BUILD_ID="{build_id}"')
         if verbose:
@@ -73,8 +79,10 @@ def build_library(verbose: bool = False) -> str:
 
     # the sources compile independently: all at once
     from concurrent.futures import ThreadPoolExecutor
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    units = [(s, p) for s in SOURCES for p in (range(PARTS[s]) if s in PARTS else [None])]
+    units.sort(key=lambda u: u[1] is None)   # the long ones first
+    with ThreadPoolExecutor(max_workers=min(len(units), os.cpu_count() or 1)) as ex:
+        objs = list(ex.map(compile_one, units))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp, "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True)

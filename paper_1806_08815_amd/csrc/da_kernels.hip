@@ -33,6 +33,13 @@
 
 #include "da_internal.h"
 
+// The step kernel's variants take minutes to compile, so this file is compiled
+// in five parts side by side: 0 everything but them, 1-3 the variants of one
+// coupling type each (int8, int16, int32), 4 the batched kernel.
+#ifndef DAPT_PART
+#error "compile with -DDAPT_PART=0 .. 4"
+#endif
+
 namespace dapt {
 
 namespace {
@@ -278,6 +285,7 @@ __device__ __forceinline__ int row16_incl_scan(int v) {
 
 }  // namespace
 
+#if DAPT_PART == 0
 size_t run_lds_bytes(int NW, int RPW, int F, int w_lds_bytes, int stage_brk, int NH,
                      bool sparse, bool direct, bool gen) {
     const SlotLayout SL = slot_layout(NW, NH, sparse ? F : 0, gen);
@@ -285,6 +293,7 @@ size_t run_lds_bytes(int NW, int RPW, int F, int w_lds_bytes, int stage_brk, int
     size_t b = stage_brk ? (size_t)kMaxBuckets * 4 + (direct ? 65536 : 0) : 0;
     return w + b + (size_t)SL.bytes * RPW;
 }
+#endif
 
 // Runs steps [s0, s1) for the replicas of one workgroup.  `blk` selects which
 // replicas of the job (rows blk*RPW ..).  All waves of the workgroup execute
@@ -1257,6 +1266,7 @@ __global__ __launch_bounds__(1024) void k_batch(const JobDesc *__restrict__ jobs
     }
 }
 
+#if DAPT_PART == 0
 // --------------------------------------------------------------------------
 // Initial states.
 // --------------------------------------------------------------------------
@@ -1627,6 +1637,8 @@ __global__ __launch_bounds__(256) void k_gen_calibrate(LevelHdr *hdr, const int3
     }
 }
 
+#endif  // DAPT_PART == 0
+
 // --------------------------------------------------------------------------
 // Host launch wrappers.
 // --------------------------------------------------------------------------
@@ -1786,6 +1798,9 @@ int launch_run_f(const JobDesc &J, int F, const TraceDesc &T, int blocks, int th
     }
 }
 
+}  // namespace
+
+// (defined here, compiled for one coupling type per part of this file)
 template <typename WT>
 int launch_run_w(const JobDesc &J, int F, bool help, const TraceDesc *trace, int blocks,
                  int threads, size_t lds, void *stream) {
@@ -1797,7 +1812,25 @@ int launch_run_w(const JobDesc &J, int F, bool help, const TraceDesc *trace, int
     return help ? launch_run_f<WT, false, true>(J, F, none, blocks, threads, lds, stream)
                 : launch_run_f<WT, false, false>(J, F, none, blocks, threads, lds, stream);
 }
-}  // namespace
+
+#if DAPT_PART == 1
+template int launch_run_w<int8_t>(const JobDesc &, int, bool, const TraceDesc *, int, int, size_t,
+                                  void *);
+#elif DAPT_PART == 2
+template int launch_run_w<int16_t>(const JobDesc &, int, bool, const TraceDesc *, int, int, size_t,
+                                   void *);
+#elif DAPT_PART == 3
+template int launch_run_w<int32_t>(const JobDesc &, int, bool, const TraceDesc *, int, int, size_t,
+                                   void *);
+#endif
+
+#if DAPT_PART == 0
+extern template int launch_run_w<int8_t>(const JobDesc &, int, bool, const TraceDesc *, int, int,
+                                         size_t, void *);
+extern template int launch_run_w<int16_t>(const JobDesc &, int, bool, const TraceDesc *, int, int,
+                                          size_t, void *);
+extern template int launch_run_w<int32_t>(const JobDesc &, int, bool, const TraceDesc *, int, int,
+                                          size_t, void *);
 
 int launch_run(const JobDesc &J, int F, bool help, const TraceDesc *trace, int blocks,
                int threads, size_t lds_bytes, void *stream) {
@@ -1822,6 +1855,9 @@ int launch_run(const JobDesc &J, int F, bool help, const TraceDesc *trace, int b
     }
 }
 
+#endif  // DAPT_PART == 0
+
+#if DAPT_PART == 4
 int launch_batch(const JobDesc *jobs_dev, const BatchItem *items_dev, const int32_t *n_items_dev,
                  int32_t *counter_dev, int blocks, int threads, size_t lds_bytes, void *stream,
                  bool dynamic) {
@@ -1833,7 +1869,9 @@ int launch_batch(const JobDesc *jobs_dev, const BatchItem *items_dev, const int3
                            lds_bytes, S(stream), jobs_dev, items_dev, n_items_dev, counter_dev);
     return (int)hipGetLastError();
 }
+#endif  // DAPT_PART == 4
 
+#if DAPT_PART == 0
 int launch_state_zero(const JobDesc &J, void *stream) {
     hipLaunchKernelGGL(k_state_zero, dim3(grid_for((int64_t)J.R * J.ld, 256)), dim3(256), 0,
                        S(stream), J);
@@ -1915,5 +1953,6 @@ int launch_gen_calibrate(LevelHdr *hdr, const int32_t *thr, int32_t L, void *str
     hipLaunchKernelGGL(k_gen_calibrate, dim3(L), dim3(256), 0, S(stream), hdr, thr, L);
     return (int)hipGetLastError();
 }
+#endif  // DAPT_PART == 0
 
 }  // namespace dapt
