@@ -362,9 +362,9 @@ int da_energy(da_ctx *ctx, const uint8_t *x, int32_t count, int64_t *E);
  * on device buffers, with no allocation.  x_dev [count][N] uint8 (nonzero =
  * 1) and E_dev [count] int64 are device buffers owned by the caller; the work
  * is enqueued on `stream` (a hipStream_t; NULL = the null stream) and the
- * call returns without waiting.  The intermediates (padded states, local
- * fields) live in a fixed 32 MiB scratch array the library holds on each
- * device until the process ends, so count is limited by
+ * call returns without waiting.  The intermediates live in a fixed 32 MiB
+ * scratch array the library holds on each device until the process ends, and
+ * count is limited by
  *   ceil(count * ld / 256) * 256 + 4 * count * ld <= 2^25,  ld = N rounded up to 64
  * (6553 states at N = 1024, 819 at N = 8192); a larger count is rejected
  * with DA_EINVAL before any work.  Every call on a device shares that

@@ -241,14 +241,26 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables &lt, int32_t R, uint32_t r
     return J;
 }
 
+JobDesc matrix_job(const da_ctx *ctx) {
+    JobDesc J{};
+    J.W = ctx->d_W;
+    J.b = ctx->d_b;
+    J.N = ctx->N;
+    J.ld = ctx->ld;
+    J.dtype = ctx->dtype;
+    J.wscale = ctx->wscale;
+    return J;
+}
+
 int init_state(da_ctx *ctx, const JobDesc &J, int init, hipStream_t stream) {
     int e;
     if (init == DA_INIT_ZEROS) {
         e = launch_state_zero(J, stream);
     } else {
         e = launch_rand_bits(J.x, J.R, J.N, J.ld, J.rid_base, J.seed, stream);
-        if (!e) e = launch_fields(J, J.x, J.R, J.h, stream);
-        if (!e) e = launch_energy_from_fields(J, J.x, J.h, J.R, J.E, true, stream);
+        const int planes = coupling_planes(ctx->dtype, ctx->hbound, ctx->wscale);
+        if (!e) e = launch_fields(J, planes, J.x, J.R, J.h, stream);
+        if (!e) e = launch_finish_start(J, stream);
     }
     return check_hip(ctx, (hipError_t)e, "state initialisation launch");
 }
@@ -1433,32 +1445,23 @@ int da_pt_adapt(da_ctx *ctx, double *temps, int32_t M, int32_t chains, int32_t i
 
 int da_energy(da_ctx *ctx, const uint8_t *x, int32_t count, int64_t *E) {
     if (!ctx || !x || !E || count < 1) return fail(ctx, DA_EINVAL, "bad energy arguments");
-    const size_t ld = (size_t)ctx->ld, N = (size_t)ctx->N;
-    std::vector<uint8_t> xp((size_t)count * ld, 0);
-    for (size_t r = 0; r < (size_t)count; ++r)
-        for (size_t i = 0; i < N; ++i) xp[r * ld + i] = x[r * N + i] ? 1 : 0;
+    const size_t bytes = (size_t)count * (size_t)ctx->N;
+    const JobDesc J = matrix_job(ctx);
+    const int planes = coupling_planes(ctx->dtype, ctx->hbound, ctx->wscale);
+    const size_t scratch = (size_t)energy_scratch_elems(J, planes, count);
     uint8_t *dX = nullptr;
-    int32_t *dH = nullptr;
-    int64_t *dE = nullptr;
+    int64_t *dE = nullptr, *dS = nullptr;
     hipStream_t s = ctx->own_stream;
-    int rc = check_hip(ctx, hipMalloc(&dX, xp.size()), "energy allocation");
-    if (!rc) rc = check_hip(ctx, hipMalloc(&dH, (size_t)count * ld * 4), "energy allocation");
+    int rc = check_hip(ctx, hipMalloc(&dX, bytes), "energy allocation");
     if (!rc) rc = check_hip(ctx, hipMalloc(&dE, (size_t)count * 8), "energy allocation");
-    if (!rc) rc = check_hip(ctx, hipMemcpyAsync(dX, xp.data(), xp.size(), hipMemcpyHostToDevice, s), "energy upload");
-    JobDesc J{};
-    J.W = ctx->d_W;
-    J.b = ctx->d_b;
-    J.N = ctx->N;
-    J.ld = ctx->ld;
-    J.dtype = ctx->dtype;
-    J.wscale = ctx->wscale;
-    if (!rc) rc = check_hip(ctx, (hipError_t)launch_fields(J, dX, count, dH, s), "field launch");
-    if (!rc) rc = check_hip(ctx, (hipError_t)launch_energy_from_fields(J, dX, dH, count, dE, false, s), "energy launch");
+    if (!rc && scratch) rc = check_hip(ctx, hipMalloc(&dS, scratch * 8), "energy allocation");
+    if (!rc) rc = check_hip(ctx, hipMemcpyAsync(dX, x, bytes, hipMemcpyHostToDevice, s), "energy upload");
+    if (!rc) rc = check_hip(ctx, (hipError_t)launch_energy(J, planes, dX, count, dE, dS, s), "energy launch");
     if (!rc) rc = check_hip(ctx, hipMemcpyAsync(E, dE, (size_t)count * 8, hipMemcpyDeviceToHost, s), "energy copy");
     if (!rc) rc = check_hip(ctx, hipStreamSynchronize(s), "stream synchronise");
     if (dX) (void)hipFree(dX);
-    if (dH) (void)hipFree(dH);
     if (dE) (void)hipFree(dE);
+    if (dS) (void)hipFree(dS);
     return rc;
 }
 

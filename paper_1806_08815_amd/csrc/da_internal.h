@@ -170,9 +170,19 @@ struct BatchItem {
 int launch_state_zero(const JobDesc &J, void *stream);
 int launch_rand_bits(uint8_t *X, int32_t R, int32_t N, int32_t ld, uint32_t rid_base,
                      uint64_t seed, void *stream);
-int launch_fields(const JobDesc &J, const uint8_t *X, int32_t R, int32_t *H, void *stream);
-int launch_energy_from_fields(const JobDesc &J, const uint8_t *X, const int32_t *H, int32_t R,
-                              int64_t *E_out, bool finish_state, void *stream);
+// Byte planes of the couplings for the matrix-core products below: their bytes,
+// but three for int32 couplings whose fields bound them below 2^23.
+int coupling_planes(int dtype, int64_t hbound, int32_t wscale);
+// Fields H = X W^T + b [R][ld] of states X [R][ld] (bytes 0/1, zero past N).
+int launch_fields(const JobDesc &J, int planes, const uint8_t *X, int32_t R, int32_t *H,
+                  void *stream);
+// Energies E [count] of states x [count][N] (nonzero = 1, any alignment), with
+// energy_scratch_elems int64 of scratch for the partial sums.
+int64_t energy_scratch_elems(const JobDesc &J, int planes, int32_t count);
+int launch_energy(const JobDesc &J, int planes, const uint8_t *x, int32_t count, int64_t *E,
+                  int64_t *scratch, void *stream);
+// Energies and best states of random starts, from their fields.
+int launch_finish_start(const JobDesc &J, void *stream);
 int launch_run(const JobDesc &J, int F, bool help, const TraceDesc *trace, int blocks,
                int threads, size_t lds_bytes, void *stream);
 // Persistent batched step kernel; the item count is read from device memory so

@@ -2,12 +2,11 @@
 // cannot allocate device memory (code under HIP graph capture, tight serving
 // loops, harnesses that forbid hipMalloc).
 //
-// da_energy stages the states in padded rows and computes the local fields
-// H = X W^T + b (int8 matrix cores or the row kernel) before the energies
-// E = (1/2) sum_i x_i (h_i + b_i); both intermediates live in device scratch.
-// Here that scratch is one file-scope device array per GPU, of a fixed
-// maximum size.  Its address on each device is taken once, with that device
-// current, and only that address is handed to kernels and copies.
+// The energy kernels take the caller's states as they are and leave one partial
+// sum per state and column tile, which a second kernel adds up.  Here these sums
+// live in one file-scope device array per GPU, of a fixed maximum size.  Its
+// address on each device is taken once, with that device current, and only that
+// address is handed to kernels.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -47,25 +46,13 @@ int scratch_on_device(int dev, uint8_t **out, std::string &err) {
     return DA_OK;
 }
 
-// [count][N] states (nonzero = 1) into [count][ld] rows, zero padded.
-__global__ void k_pad_states(const uint8_t *__restrict__ x, uint8_t *__restrict__ X,
-                             int32_t count, int32_t N, int32_t ld) {
-    const int64_t n = (int64_t)count * ld;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = q / ld;
-        const int i = (int)(q - r * ld);
-        X[q] = i < N ? (uint8_t)(x[r * N + i] != 0) : (uint8_t)0;
-    }
-}
-
 }  // namespace
 }  // namespace dapt
 
 using namespace dapt;
 
 namespace {
-// Largest count whose padded states and fields fit the scratch at this N:
+// Largest count the entry point takes at this N (its documented limit):
 // ceil(count ld / 256) 256 + 4 count ld <= kScratchBytes.
 int64_t max_states(int32_t N) {
     const int64_t ld = ((int64_t)N + 63) / 64 * 64;
@@ -98,28 +85,15 @@ extern "C" int da_energy_noalloc(da_ctx *ctx, const uint8_t *x_dev, int32_t coun
     std::string err;
     rc = scratch_on_device(dev, &base, err);
     if (rc) return fail(ctx, rc, err);
-    // both intermediates are written in full before they are read: nothing in
+    // the partial sums are written in full before they are read: nothing in
     // the scratch has to start at zero
-    const size_t ld = (size_t)ctx->ld;
-    uint8_t *X = base;
-    int32_t *H = reinterpret_cast<int32_t *>(base + ((size_t)count * ld + 255) / 256 * 256);
-    hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : nullptr;
-    JobDesc J{};
-    J.W = ctx->d_W;
-    J.b = ctx->d_b;
-    J.N = ctx->N;
-    J.ld = ctx->ld;
-    J.dtype = ctx->dtype;
-    J.wscale = ctx->wscale;
-    const int64_t n = (int64_t)count * ctx->ld;
-    int64_t grid = (n + 255) / 256;
-    if (grid > 65535) grid = 65535;
-    hipLaunchKernelGGL(k_pad_states, dim3((unsigned)grid), dim3(256), 0, s, x_dev, X, count,
-                       ctx->N, ctx->ld);
-    rc = check_hip(ctx, hipGetLastError(), "state padding launch");
-    if (!rc) rc = check_hip(ctx, (hipError_t)launch_fields(J, X, count, H, s), "field launch");
-    if (!rc)
-        rc = check_hip(ctx, (hipError_t)launch_energy_from_fields(J, X, H, count, E_dev, false, s),
-                       "energy launch");
-    return rc;
+    const JobDesc J = matrix_job(ctx);
+    const int planes = coupling_planes(ctx->dtype, ctx->hbound, ctx->wscale);
+    if (energy_scratch_elems(J, planes, count) * 8 > (int64_t)kScratchBytes)
+        return fail(ctx, DA_EINVAL, "partial sums exceed the scratch");
+    return check_hip(ctx,
+                     (hipError_t)launch_energy(J, planes, x_dev, count, E_dev,
+                                               reinterpret_cast<int64_t *>(base),
+                                               stream),
+                     "energy launch");
 }

@@ -157,10 +157,10 @@ extern "C" int da_probe_fields_mfma(int32_t N, int32_t R, int32_t iters, double 
         J.dtype = 1;
         J.wscale = 1;
         if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) rc = DA_EDEVICE;
-        if (!rc && dapt::launch_fields(J, dX, R, dH, nullptr) != 0) rc = DA_EDEVICE;
+        if (!rc && dapt::launch_fields(J, 1, dX, R, dH, nullptr) != 0) rc = DA_EDEVICE;
         if (!rc && hipEventRecord(a, 0) != hipSuccess) rc = DA_EDEVICE;
         for (int32_t q = 0; q < iters && !rc; ++q)
-            if (dapt::launch_fields(J, dX, R, dH, nullptr) != 0) rc = DA_EDEVICE;
+            if (dapt::launch_fields(J, 1, dX, R, dH, nullptr) != 0) rc = DA_EDEVICE;
         float ms = 0.f;
         if (!rc && (hipEventRecord(b, 0) != hipSuccess || hipEventSynchronize(b) != hipSuccess ||
                     hipEventElapsedTime(&ms, a, b) != hipSuccess))

@@ -221,6 +221,8 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
                 const da_schedule &sched, hipStream_t s, bool may_time, LaunchShape &out);
 JobDesc make_job(const da_ctx *ctx, const LevelTables &lt, int32_t R, uint32_t rid_base,
                  uint64_t seed, int64_t steps, const da_schedule &s, const LaunchShape &sh);
+// The instance alone (W, b, sizes), for the energy kernels.
+JobDesc matrix_job(const da_ctx *ctx);
 int init_state(da_ctx *ctx, const JobDesc &J, int init, hipStream_t stream);
 // Event pair for the next timed call (from the context's pool).
 int next_events(da_ctx *ctx, hipEvent_t &e0, hipEvent_t &e1);
