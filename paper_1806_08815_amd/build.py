@@ -20,11 +20,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libdapt.so")
-SOURCES = ["da_kernels.hip", "da_fields.hip", "da_probe.hip", "da_tables.cpp", "da_api.cpp", "da_server.cpp",
+SOURCES = ["da_kernels.hip", "da_wave.hip", "da_fields.hip", "da_probe.hip", "da_tables.cpp", "da_api.cpp", "da_server.cpp",
            "da_noalloc.hip"]
-HEADERS = ["da_internal.h", "da_runtime.h"]
-# compiled in parts (-DDAPT_PART=n), side by side: the step kernel's variants
-PARTS = {"da_kernels.hip": 5}
+HEADERS = ["da_device.h", "da_internal.h", "da_runtime.h"]
+# compiled in parts (-DDAPT_PART=n), side by side: the step kernels' variants
+PARTS = {"da_kernels.hip": 5, "da_wave.hip": 4}
 
 
 def source_hash() -> str:

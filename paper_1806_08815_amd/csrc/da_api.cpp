@@ -198,7 +198,7 @@ LaunchShape choose_shape(const da_ctx *ctx, int32_t R, const da_launch *launch,
     return sh;
 }
 
-JobDesc make_job(const da_ctx *ctx, const LevelTables &lt, int32_t R, uint32_t rid_base,
+JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t rid_base,
                  uint64_t seed, int64_t steps, const da_schedule &s, const LaunchShape &sh) {
     JobDesc J{};
     J.W = ctx->d_W;
@@ -220,7 +220,7 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables &lt, int32_t R, uint32_t r
     J.s0 = 0;
     J.s1 = steps;
     J.S = steps;
-    J.L = lt.L;
+    J.L = 1;
     // increments above 2^30 act as 2^30: the offset saturates there at once
     J.eoff_inc = std::min<int32_t>(s.eoff_inc, kEoffMax);
     J.single = s.trial == DA_TRIAL_SINGLE ? 1 : 0;
@@ -233,12 +233,56 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables &lt, int32_t R, uint32_t r
     J.NH = sh.NH;
     J.RPW = sh.RPW;
     J.w_lds = sh.w_lds;
-    J.hdr = lt.d_hdr;
-    J.brk = lt.d_brk;
-    J.thr = lt.d_thr;
-    J.q8 = sh.direct ? lt.d_q8 : nullptr;
-    J.gth = (sh.gen && lt.any_gth && s.trial != DA_TRIAL_SINGLE) ? 1 : 0;
+    J.qcap = sh.qcap;
+    J.ecap = sh.ecap;
+    J.w24 = sh.w24;
+    J.wclamp = sh.wclamp;
+    if (lt) {
+        J.L = lt->L;
+        J.hdr = lt->d_hdr;
+        J.brk = lt->d_brk;
+        J.thr = lt->d_thr;
+        J.q8 = sh.direct ? lt->d_q8 : nullptr;
+        J.gth = (sh.gen && lt->any_gth && s.trial != DA_TRIAL_SINGLE) ? 1 : 0;
+    }
     return J;
+}
+
+bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh) {
+    if (ctx->N > 1024 || ctx->ell_D > 0) return false;
+    const int64_t ws = std::abs((int64_t)ctx->wscale), hb = ctx->hbound + 1;
+    // the field update's factor: 16 bits for 16-bit couplings, else 24
+    sh.w24 = ctx->dtype < 4 || (ctx->hbound / ws < (1 << 23) && ws < (1 << 23)) ? 1 : 0;
+    const int64_t wlim = ctx->dtype == 2 ? (1 << 15) : (sh.w24 ? (1 << 23) : INT64_MAX);
+    if (ws >= wlim) return false;
+    // the test's sum |h| + E_off + L(u) stays below 2^31: E_off is cut off at
+    // max |h| + 1, L(u) <= 11.79 T, and T 2^q < 2^17 wherever q > 0
+    const double room = 2147483648.0 - 65536.0;
+    if (2.0 * (double)hb + 11.8 * T_max * (1.0 + 1e-4) > room) return false;
+    int q = 0;
+    while (q < 17 && 2.0 * (double)(hb << (q + 1)) + 2097152.0 <= room && (ws << (q + 1)) < wlim) ++q;
+    sh.qcap = q;
+    // the form without a conversion needs T 2^q < 2^18; from T 2^q = 2^14 down
+    // costs of zero would fall in its bracket often enough to matter (one in
+    // T 2^q / 4 of them)
+    sh.wclamp = T_max >= 262144.0 || T_min * (double)(1 << q) < 16384.0 ? 1 : 0;
+    sh.ecap = (int)hb;
+    sh.wave = true;
+    sh.F = ctx->N <= 64 ? 1 : ctx->N <= 128 ? 2 : ctx->N <= 256 ? 4 : ctx->N <= 512 ? 8 : 16;
+    sh.NW = 1;
+    sh.NH = 0;
+    sh.direct = sh.gen = 0;
+    // a wave per SIMD before two on one; W in LDS where a workgroup's share of
+    // the replicas leaves it room (shared by all of them), read there at a
+    // quarter of the latency
+    const int64_t w_bytes = (int64_t)ctx->N * ctx->ld * ctx->dtype;
+    const int per_cu = (R + ctx->cus - 1) / ctx->cus;
+    sh.w_lds = sh.F < 16 && w_bytes + 16384 <= (int64_t)device_lds_limit() ? 1 : 0;
+    sh.RPW = sh.w_lds ? std::min(per_cu, 16) : std::min(per_cu, 4);
+    sh.threads = 64 * sh.RPW;
+    sh.blocks = (R + sh.RPW - 1) / sh.RPW;
+    sh.lds = wave_lds_bytes(sh.F, sh.RPW, sh.w_lds ? w_bytes : 0);
+    return true;
 }
 
 JobDesc matrix_job(const da_ctx *ctx) {
@@ -586,6 +630,70 @@ int create_ctx(const HostMatrix &hm, hipStream_t s, da_ctx **out, std::string &e
     return DA_OK;
 }
 
+TempList::~TempList() {
+    if (d_temps) (void)hipFree(d_temps);
+}
+
+namespace {
+std::mutex g_temps_mu;
+std::map<std::string, std::weak_ptr<TempList>> g_temps;
+std::mutex g_gerr_mu;
+std::map<int, float> g_gerr;
+}  // namespace
+
+std::shared_ptr<TempList> get_temp_list(const std::vector<double> &temps, std::string &err) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        err = "hipGetDevice failed";
+        return nullptr;
+    }
+    std::string key(reinterpret_cast<const char *>(&dev), sizeof dev);
+    key.append(reinterpret_cast<const char *>(temps.data()), temps.size() * sizeof(double));
+    std::lock_guard<std::mutex> lock(g_temps_mu);
+    auto it = g_temps.find(key);
+    if (it != g_temps.end()) {
+        if (auto sp = it->second.lock()) return sp;
+    }
+    auto tl = std::make_shared<TempList>();
+    const size_t bytes = temps.size() * sizeof(double);
+    if (hipMalloc(&tl->d_temps, bytes) != hipSuccess ||
+        hipMemcpy(tl->d_temps, temps.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+        err = "temperature list allocation or upload failed";
+        return nullptr;
+    }
+    g_temps[key] = tl;
+    return tl;
+}
+
+// The error of tt(u) of the one-wave kernel per unit of T 2^q (da_wave.hip):
+// the fp32 roundings of its three terms, (16 + 16 + 17) ln 2 2^-24 = 2.03e-6,
+// and ln 2 times the device's log2 error, which is measured.
+bool device_bound_error(float &gerr, std::string &err) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        err = "hipGetDevice failed";
+        return false;
+    }
+    const double *G = device_neg_log_u(err);
+    if (!G) return false;
+    std::lock_guard<std::mutex> lock(g_gerr_mu);
+    auto it = g_gerr.find(dev);
+    if (it == g_gerr.end()) {
+        float *d = nullptr, e = 0.0f;
+        const bool ok = hipMalloc(&d, sizeof *d) == hipSuccess &&
+                        launch_log_error(G, d, nullptr) == hipSuccess &&
+                        hipMemcpy(&e, d, sizeof e, hipMemcpyDeviceToHost) == hipSuccess;
+        if (d) (void)hipFree(d);
+        if (!ok) {
+            err = "log2 error pass failed";
+            return false;
+        }
+        it = g_gerr.emplace(dev, 0.6932f * e + 2.2e-6f).first;
+    }
+    gerr = it->second;
+    return true;
+}
+
 // ---------------------------------------------------------------------------
 // Autotuner.  Launch shapes never change results, only speed, so the first
 // anneal of each (device, N, coupling type, replica-count bucket) times every
@@ -595,11 +703,13 @@ int create_ctx(const HostMatrix &hm, hipStream_t s, da_ctx **out, std::string &e
 namespace {
 struct TuneKey {
     int dev, N, dtype, rbucket;
+    int long_levels;   // long enough for direct tables: other shapes win there
     bool operator<(const TuneKey &o) const {
         if (dev != o.dev) return dev < o.dev;
         if (N != o.N) return N < o.N;
         if (dtype != o.dtype) return dtype < o.dtype;
-        return rbucket < o.rbucket;
+        if (rbucket != o.rbucket) return rbucket < o.rbucket;
+        return long_levels < o.long_levels;
     }
 };
 std::mutex g_tune_mu;
@@ -613,24 +723,42 @@ bool tune_enabled() {
 
 // Direct tables pay for their staging (64 KiB per level and workgroup) only
 // when levels last a few hundred steps.
+static bool long_levels(const da_schedule &sched, int64_t steps) {
+    return sched.n_levels > 0 && steps >= 256 * (int64_t)sched.n_levels;
+}
 static bool want_direct(const LevelTables &lt, const da_schedule &sched, int64_t steps) {
-    return lt.d_q8 != nullptr && sched.n_levels > 0 && steps >= 256 * (int64_t)sched.n_levels;
+    return lt.d_q8 != nullptr && long_levels(sched, steps);
+}
+
+// flips_per_lane of the one-wave kernel in the tuner's cache
+static constexpr int kTuneWave = 16;
+
+static TuneKey tune_key(const da_ctx *ctx, int32_t R, const da_schedule &sched, int64_t steps) {
+    int rb = 1;
+    while (rb < R) rb <<= 1;
+    return TuneKey{ctx->device, ctx->N, ctx->dtype, rb, long_levels(sched, steps) ? 1 : 0};
+}
+
+// Whether the tuner has chosen the one-wave kernel for this size.
+static bool tuned_to_wave(const da_ctx *ctx, int32_t R, const da_schedule &sched, int64_t steps) {
+    std::lock_guard<std::mutex> lock(g_tune_mu);
+    auto it = g_tune.find(tune_key(ctx, R, sched, steps));
+    return it != g_tune.end() && it->second.flips_per_lane == kTuneWave;
 }
 
 int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
-                const da_schedule &sched, hipStream_t s, bool may_time, LaunchShape &out) {
+                const da_schedule &sched, hipStream_t s, bool may_time, const LaunchShape *wave,
+                const JobDesc *wave_job, LaunchShape &out) {
     const bool direct = want_direct(lt, sched, steps);
-    int dev = 0;
-    int rc = check_hip(ctx, hipGetDevice(&dev), "autotuner: device query");
-    if (rc) return rc;
-    int rb = 1;
-    while (rb < R) rb <<= 1;
-    const TuneKey key{dev, ctx->N, ctx->dtype, rb};
+    int rc = DA_OK;
+    const TuneKey key = tune_key(ctx, R, sched, steps);
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         auto it = g_tune.find(key);
         if (it != g_tune.end()) {
-            out = choose_shape(ctx, R, &it->second, true, direct);
+            // (a size tuned to the one-wave kernel whose instance it does not take)
+            out = choose_shape(ctx, R, it->second.flips_per_lane == kTuneWave ? nullptr : &it->second,
+                               true, direct);
             return DA_OK;
         }
     }
@@ -646,6 +774,31 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
     if (!rc) rc = check_hip(ctx, hipEventCreate(&b), "autotuner: event create");
     da_launch best{0, 0, 0, 0, 0};
     float best_ms = 1e30f;
+    auto time_candidate = [&](JobDesc J, const LaunchShape &sh, const da_launch &cand,
+                              const char *what) {
+        tune_window(steps, J.s0, J.s1);
+        if (const char *why = job_range_error(J)) {
+            rc = fail(ctx, DA_EINVAL, std::string("autotuner: ") + why);
+            return;
+        }
+        rc = check_hip(ctx, (hipError_t)launch_state_zero(J, s), what);
+        if (!rc) rc = check_hip(ctx, hipEventRecord(a, s), what);
+        if (!rc)
+            rc = check_hip(ctx,
+                           (hipError_t)(sh.wave
+                                            ? launch_wave(J, sh.F, sh.blocks, sh.threads, sh.lds, s)
+                                            : launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks,
+                                                         sh.threads, sh.lds, s)),
+                           what);
+        if (!rc) rc = check_hip(ctx, hipEventRecord(b, s), what);
+        if (!rc) rc = check_hip(ctx, hipEventSynchronize(b), what);
+        float ms = 0.f;
+        if (!rc) rc = check_hip(ctx, hipEventElapsedTime(&ms, a, b), what);
+        if (!rc && ms < best_ms) {
+            best_ms = ms;
+            best = cand;
+        }
+    };
     // W staged in LDS is a candidate whenever it fits there
     const bool w_fits = ctx->ell_D == 0 &&
                         (int64_t)ctx->N * ctx->ld * ctx->dtype <= (int64_t)device_lds_limit();
@@ -664,12 +817,7 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
                     continue;
                 // the estimate candidate only where the shape can take it
                 if (ge > 0 && (!sh.gen || !lt.any_gth)) continue;
-                JobDesc J = make_job(ctx, lt, R, 0u, 1u, steps, sched, sh);
-                tune_window(steps, J.s0, J.s1);
-                if (const char *why = job_range_error(J)) {
-                    rc = fail(ctx, DA_EINVAL, std::string("autotuner: ") + why);
-                    break;
-                }
+                JobDesc J = make_job(ctx, &lt, R, 0u, 1u, steps, sched, sh);
                 // any failure here is a device fault or a launch the device
                 // refused: report it with the candidate instead of moving on
                 char what[160];
@@ -677,24 +825,13 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
                               "autotuner candidate (flips/lane %d, replicas/workgroup %d, "
                               "rng waves %d, W in LDS %d, draw estimates %d)", F, rpw, rng, wl,
                               ge);
-                rc = check_hip(ctx, (hipError_t)launch_state_zero(J, s), what);
-                if (!rc) rc = check_hip(ctx, hipEventRecord(a, s), what);
-                if (!rc)
-                    rc = check_hip(ctx,
-                                   (hipError_t)launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks,
-                                                          sh.threads, sh.lds, s),
-                                   what);
-                if (!rc) rc = check_hip(ctx, hipEventRecord(b, s), what);
-                if (!rc) rc = check_hip(ctx, hipEventSynchronize(b), what);
-                float ms = 0.f;
-                if (!rc) rc = check_hip(ctx, hipEventElapsedTime(&ms, a, b), what);
-                if (!rc && ms < best_ms) {
-                    best_ms = ms;
-                    best = cand;
-                }
+                time_candidate(J, sh, cand, what);
             }
         }
     }
+    if (wave && !rc)
+        time_candidate(*wave_job, *wave, da_launch{kTuneWave, 0, 0, 0, 0},
+                       "autotuner candidate (one wave per replica)");
     if (a) (void)hipEventDestroy(a);
     if (b) (void)hipEventDestroy(b);
     if (rc) return rc;
@@ -703,7 +840,7 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
         std::lock_guard<std::mutex> lock(g_tune_mu);
         g_tune[key] = best;
     }
-    out = choose_shape(ctx, R, &best, true, direct);
+    out = best.flips_per_lane == kTuneWave ? *wave : choose_shape(ctx, R, &best, true, direct);
     return DA_OK;
 }
 
@@ -816,8 +953,33 @@ void record_stats(da_ctx *ctx, const LaunchShape &sh, int64_t launches, int gth 
 struct JobTables {
     std::shared_ptr<LevelTables> levels;
     std::shared_ptr<StepTables> steps;
+    std::shared_ptr<TempList> temps;   // one-wave kernel
     const double *G = nullptr;
+    float gerr = 0.0f;
 };
+
+// What the one-wave kernel takes of a schedule: its temperatures, -ln U_u and
+// the bound error.
+int wave_tables(const da_schedule &sch, int64_t steps, JobTables &jt, std::string &err) {
+    if (sch.n_levels == 0) {
+        if (steps > kMaxPerStepSteps) {
+            err = "per-step schedules take at most 2^24 steps";
+            return DA_EINVAL;
+        }
+        if (steps > 0) {
+            jt.steps = get_step_tables(sch, steps, err);
+            if (!jt.steps) return DA_ENOMEM;
+        } else {
+            jt.temps = get_temp_list(std::vector<double>{0.0}, err);
+            if (!jt.temps) return DA_ENOMEM;
+        }
+    } else {
+        jt.temps = get_temp_list(schedule_temps(sch), err);
+        if (!jt.temps) return DA_ENOMEM;
+    }
+    jt.G = device_neg_log_u(err);
+    return jt.G && device_bound_error(jt.gerr, err) ? DA_OK : DA_ENOMEM;
+}
 
 int job_tables(const da_schedule &sch, int64_t steps, JobTables &jt, std::string &err) {
     if (sch.n_levels == 0) {
@@ -841,6 +1003,8 @@ int job_tables(const da_schedule &sch, int64_t steps, JobTables &jt, std::string
 void attach_step_tables(JobDesc &J, const JobTables &jt) {
     J.stepT = jt.steps ? jt.steps->d_steps : nullptr;
     J.G = jt.G;
+    J.temps = jt.temps ? jt.temps->d_temps : nullptr;
+    J.gerr = jt.gerr;
 }
 
 // Steps [step_begin, step_end) of a `steps`-step anneal; step_begin > 0
@@ -863,28 +1027,58 @@ int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_bas
     if (step_begin > 0 && (ctx->st_step != step_begin || ctx->st_base != replica_base ||
                            ctx->st_R < replicas))
         return fail(ctx, DA_EINVAL, "the context holds no state of these replicas at step_begin");
+    // One wave per replica: always up to 512 variables (measured faster there at
+    // every replica count: 204 ns a step at N = 64 against 668, 436 at N = 512
+    // against about 600) and for a new temperature every step (no gather of ln U
+    // per flip), else where the tuner finds it faster
     JobTables jt;
-    rc = job_tables(*schedule, steps, jt, err);
+    LaunchShape sh;
+    const bool own = launch == nullptr && trace_dev == nullptr;
+    const bool tune = own && tune_enabled() && schedule->n_levels > 0;
+    LaunchShape wsh;
+    const bool wave_ok = own && wave_shape(ctx, replicas, std::min(schedule->T_hi, schedule->T_lo),
+                                           std::max(schedule->T_hi, schedule->T_lo), wsh);
+    bool wave = wave_ok && (ctx->N <= 512 || schedule->n_levels == 0 ||
+                            (tune && tuned_to_wave(ctx, replicas, *schedule, steps)));
+    if (!wave) rc = job_tables(*schedule, steps, jt, err);
+    if (!rc && (wave || (wave_ok && tune))) rc = wave_tables(*schedule, steps, jt, err);
     if (rc) return fail(ctx, rc, err);
     ctx->keep_tables = jt.levels;
     ctx->keep_steps = jt.steps;
+    ctx->keep_temps = jt.temps;
     if (!ctx->st.ensure(replicas, ctx->ld, err)) return fail(ctx, DA_ENOMEM, err);
-    const LevelTables &lt0 = *jt.levels;
     // from here on the state changes: it is resumable again only on success
     ctx->st_step = -1;
-    LaunchShape sh;
     // the tuner times its candidates on the replica state, so only when the
     // run starts from the initial state (which is written after it); a resumed
     // piece takes the cached choice or the default
-    if (launch == nullptr && trace_dev == nullptr && tune_enabled() && !jt.steps) {
-        rc = tuned_shape(ctx, lt0, replicas, steps, *schedule, s, step_begin == 0, sh);
+    auto wave_job = [&]() {
+        JobDesc W = make_job(ctx, nullptr, replicas, (uint32_t)replica_base, seed, steps, *schedule,
+                             wsh);
+        attach_step_tables(W, jt);
+        if (jt.temps) W.L = std::max(schedule->n_levels, 1);
+        return W;
+    };
+    if (wave) {
+        sh = wsh;
+    } else if (tune) {
+        JobDesc W;
+        if (wave_ok) W = wave_job();
+        rc = tuned_shape(ctx, *jt.levels, replicas, steps, *schedule, s, step_begin == 0,
+                         wave_ok ? &wsh : nullptr, &W, sh);
         if (rc) return rc;
+        wave = sh.wave;
     } else {
         sh = choose_shape(ctx, replicas, launch, true,
-                          !jt.steps && want_direct(lt0, *schedule, steps));
+                          !jt.steps && want_direct(*jt.levels, *schedule, steps));
     }
-    J = make_job(ctx, lt0, replicas, (uint32_t)replica_base, seed, steps, *schedule, sh);
-    attach_step_tables(J, jt);
+    if (wave) {
+        J = wave_job();
+    } else {
+        J = make_job(ctx, jt.levels.get(), replicas, (uint32_t)replica_base, seed, steps, *schedule,
+                     sh);
+        attach_step_tables(J, jt);
+    }
     J.s0 = step_begin;
     J.s1 = step_end;
     if (const char *why = job_range_error(J)) return fail(ctx, DA_EINVAL, why);
@@ -904,14 +1098,15 @@ int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_bas
             T.E = trace_dev->E;
             T.eoff = trace_dev->eoff;
         }
-        const int e = launch_run(J, sh.F, sh.NH > 0, trace_dev ? &T : nullptr, sh.blocks,
-                                 sh.threads, sh.lds, s);
+        const int e = wave ? launch_wave(J, sh.F, sh.blocks, sh.threads, sh.lds, s)
+                           : launch_run(J, sh.F, sh.NH > 0, trace_dev ? &T : nullptr, sh.blocks,
+                                        sh.threads, sh.lds, s);
         rc = check_hip(ctx, (hipError_t)e, "step kernel launch");
         if (rc) return rc;
     }
     rc = check_hip(ctx, hipEventRecord(e1, s), "event record");
     if (rc) return rc;
-    record_stats(ctx, sh, 1, J.gth);
+    record_stats(ctx, sh, 1, wave ? 1 : J.gth);
     ctx->st_step = step_end;
     ctx->st_base = replica_base;
     ctx->st_R = replicas;
@@ -1179,7 +1374,7 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
         ctx->keep_tables = lt;
         if (!ctx->st.ensure(it.replicas, ctx->ld, err)) return fail(ctx, DA_ENOMEM, err);
         const LaunchShape sh = batch_shape(ctx);
-        jobs[(size_t)a] = make_job(ctx, *lt, it.replicas, (uint32_t)it.replica_base, it.seed,
+        jobs[(size_t)a] = make_job(ctx, lt.get(), it.replicas, (uint32_t)it.replica_base, it.seed,
                                    it.steps, it.schedule, sh);
         attach_step_tables(jobs[(size_t)a], jt);
         if (const char *why = job_range_error(jobs[(size_t)a])) return fail(ctx, DA_EINVAL, why);
@@ -1248,9 +1443,25 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     const int32_t npair = chains * std::max(M - 1, 1);
     std::string err;
     std::vector<double> tv(temps, temps + M);
-    auto lt = get_level_tables(tv, err);
-    if (!lt) return fail(ctx, DA_ENOMEM, err);
-    ctx->keep_tables = lt;
+    // One wave per replica up to 512 variables; beyond, where the chip is full
+    // or the costs too few units apart for the wider replicas' estimates
+    LaunchShape sh;
+    const bool wave =
+        wave_shape(ctx, R, temps[0], temps[M - 1], sh) &&
+        (ctx->N <= 512 || R > 2 * ctx->cus ||
+         ctx->hbound < 4096 * (int64_t)std::abs(ctx->wscale));
+    JobTables jt;
+    if (wave) {
+        jt.temps = get_temp_list(tv, err);
+        jt.G = device_neg_log_u(err);
+        if (!jt.temps || !jt.G || !device_bound_error(jt.gerr, err)) return fail(ctx, DA_ENOMEM, err);
+    } else {
+        jt.levels = get_level_tables(tv, err);
+        if (!jt.levels) return fail(ctx, DA_ENOMEM, err);
+    }
+    const LevelTables *lt = jt.levels.get();
+    ctx->keep_tables = jt.levels;
+    ctx->keep_temps = jt.temps;
     ctx->st_step = -1;   // PT state is not a resumable anneal
     if (!ctx->st.ensure(R, ctx->ld, err)) return fail(ctx, DA_ENOMEM, err);
     hipStream_t s = ctx->own_stream;
@@ -1289,15 +1500,16 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
 
     da_schedule sched{temps[0], temps[0], DA_SCHED_GEOMETRIC, 1, eoff_inc, DA_INIT_RANDOM,
                       DA_TRIAL_PARALLEL, 0};
-    LaunchShape sh = choose_shape(ctx, R, nullptr, false);
-    JobDesc J = make_job(ctx, *lt, R, 0u, seed, 0, sched, sh);
+    if (!wave) sh = choose_shape(ctx, R, nullptr, false);
+    JobDesc J = make_job(ctx, lt, R, 0u, seed, 0, sched, sh);
+    attach_step_tables(J, jt);
     // per-draw estimates (one replica per workgroup, several compute waves,
     // fields of many coupling units, as for anneals; the levels' windows are
     // measured when the tables are made): handed over by the random-number
     // waves, whose ring then needs its estimate part in LDS, or evaluated by
     // the compute lanes themselves
     const bool wide16 = ctx->dtype != 2 || (ctx->wscale < (1 << 15) && ctx->wscale > -(1 << 15));
-    J.gth = (lt->any_gth && sh.RPW == 1 && sh.NW > 1 && sh.F >= 4 && !sh.w_lds && wide16 &&
+    J.gth = (!wave && lt->any_gth && sh.RPW == 1 && sh.NW > 1 && sh.F >= 4 && !sh.w_lds && wide16 &&
              ctx->ell_D == 0 && ctx->hbound <= kGenFieldMax &&
              ctx->hbound >= 4096 * (int64_t)std::abs(ctx->wscale))
                 ? 1
@@ -1326,7 +1538,8 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     auto one_round = [&]() -> int {
         int e = 0;
         if (steps_per_round > 0)
-            e = launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks, sh.threads, sh.lds, s);
+            e = wave ? launch_wave(J, sh.F, sh.blocks, sh.threads, sh.lds, s)
+                     : launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks, sh.threads, sh.lds, s);
         if (!e)
             e = launch_pt_exchange(J.E, ctx->pt_slot2rep, ctx->pt_lvl, ctx->pt_dbeta, ctx->pt_lnU,
                                    M, chains, seed, ctx->pt_round, ctx->pt_swaps, ctx->pt_pair, s);
@@ -1353,7 +1566,7 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     for (; done < rounds && !rc; ++done) rc = check_hip(ctx, (hipError_t)one_round(), "PT round launch");
     if (!rc) rc = check_hip(ctx, hipEventRecord(pe1, s), "event record");
     if (rc) return rc;
-    record_stats(ctx, sh, 1, J.gth);
+    record_stats(ctx, sh, 1, wave ? 1 : J.gth);
 
     if (out) {
         da_result o{out->best_x, out->best_E, out->final_x, out->final_E, out->n_accept};

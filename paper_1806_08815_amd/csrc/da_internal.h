@@ -123,6 +123,13 @@ struct JobDesc {
     int32_t ell_D;               // sparse row lists: entries per row (0: dense)
     const uint32_t *ell;         // [N][ell_D] column | value << 16, or null
     int32_t gth;                 // 1: random-number waves hand over per-draw estimates
+    // one-wave kernel (da_wave.hip)
+    const double *temps;         // temperature of each level
+    float gerr;                  // error of a bound per unit of T (wave_level)
+    int32_t qcap;                // most fraction bits of a fixed-point cost
+    int32_t ecap;                // max |h| + 1: offsets past it change no decision
+    int32_t w24;                 // couplings and their factor below 2^23
+    int32_t wclamp;              // bounds by conversion (temperatures too high or too low for the other form)
 };
 
 constexpr int64_t kMaxPerStepSteps = int64_t(1) << 24;
@@ -141,7 +148,7 @@ inline const char *job_range_error(const JobDesc &J) {
     if (J.NW < 1 || J.NH < 0 || J.RPW < 1 || J.NW * J.RPW + J.NH * J.RPW > 16)
         return "launch shape exceeds one workgroup";
     if (J.eoff_inc < 0 || J.eoff_inc > kEoffMax) return "offset increment outside [0, 2^30]";
-    if (J.L < 1 || !J.hdr) return "job has no temperature levels";
+    if (J.L < 1 || (!J.hdr && !J.temps && !J.stepT)) return "job has no temperature levels";
     if (J.round_ptr) {
         if (!J.lvl_of_rep || J.K < 0) return "parallel-tempering job without levels or round";
         return nullptr;
@@ -185,6 +192,12 @@ int launch_energy(const JobDesc &J, int planes, const uint8_t *x, int32_t count,
 int launch_finish_start(const JobDesc &J, void *stream);
 int launch_run(const JobDesc &J, int F, bool help, const TraceDesc *trace, int blocks,
                int threads, size_t lds_bytes, void *stream);
+// The step kernel with one wave per replica (J.N <= 64 F), J.RPW replicas per
+// workgroup; wave_lds_bytes is what its workgroups need.
+size_t wave_lds_bytes(int F, int RPW, int64_t w_lds_bytes);
+int launch_wave(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream);
+// Largest error of the device's fp32 log2 over the arguments u + 1/2 of all draws.
+int launch_log_error(const double *G, float *out, void *stream);
 // Persistent batched step kernel; the item count is read from device memory so
 // one captured graph can serve batches of any size.
 // dynamic: the kernel variant that reads each job's optional features

@@ -54,6 +54,14 @@ inline void tune_window(int64_t S, int64_t &s0, int64_t &s1) {
     s0 = S / 3 < S - w ? S / 3 : S - w;
     s1 = s0 + w;
 }
+// A temperature list on the device, shared by every context through a cache,
+// and the error per unit of T of the one-wave kernel's bounds on this device.
+struct TempList {
+    double *d_temps = nullptr;
+    ~TempList();
+};
+std::shared_ptr<TempList> get_temp_list(const std::vector<double> &temps, std::string &err);
+bool device_bound_error(float &gerr, std::string &err);
 // Temperature of level l of a schedule.
 double schedule_temperature(const da_schedule &s, int l);
 // Host image of the tables of a temperature list.
@@ -99,6 +107,8 @@ struct LaunchShape {
     int w_lds = 0;
     int direct = 0;     // the level's direct table is staged in LDS (anneal mode)
     int gen = 0;        // random-number waves may hand over per-draw estimates
+    bool wave = false;  // the one-wave kernel
+    int qcap = 0, ecap = 0, w24 = 0, wclamp = 0;   // its fixed point (wave_shape)
     int threads = 64;
     int blocks = 1;
     size_t lds = 0;
@@ -196,6 +206,7 @@ struct da_ctx {
     int32_t pt_cap_R = 0, pt_cap_M = 0, pt_cap_chains = 0, pt_cap_pairs = 0;
     std::shared_ptr<dapt::LevelTables> keep_tables;
     std::shared_ptr<dapt::StepTables> keep_steps;
+    std::shared_ptr<dapt::TempList> keep_temps;
     // what the replica state in `st` holds: replicas st_base .. st_base+st_R-1
     // after st_step steps (st_step < 0: nothing resumable)
     int64_t st_step = -1;
@@ -213,13 +224,18 @@ int validate_schedule(const da_schedule *s, std::string &err);
 // direct: the schedule's tables include direct tables (staged when they fit)
 LaunchShape choose_shape(const da_ctx *ctx, int32_t R, const da_launch *launch,
                          bool anneal_mode, bool direct = false);
+// Shape of the one-wave kernel for replicas of this instance at temperatures
+// between T_min and T_max; false when it does not take them.
+bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh);
 // Fastest measured shape for this instance size, coupling type and replica
 // count, into `out`: timed once (when may_time) on the context's replica state,
 // which must hold R replicas and is left overwritten, then cached.  Returns
 // DA_OK, or the error of the first HIP call that failed (naming the candidate).
+// wave: the one-wave candidate and its job, or null.
 int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
-                const da_schedule &sched, hipStream_t s, bool may_time, LaunchShape &out);
-JobDesc make_job(const da_ctx *ctx, const LevelTables &lt, int32_t R, uint32_t rid_base,
+                const da_schedule &sched, hipStream_t s, bool may_time, const LaunchShape *wave,
+                const JobDesc *wave_job, LaunchShape &out);
+JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t rid_base,
                  uint64_t seed, int64_t steps, const da_schedule &s, const LaunchShape &sh);
 // The instance alone (W, b, sizes), for the energy kernels.
 JobDesc matrix_job(const da_ctx *ctx);

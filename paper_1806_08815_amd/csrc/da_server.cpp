@@ -190,7 +190,7 @@ int da_server::start_job(Job &j) {
     ctx->keep_tables = j.tables;
     if (!ctx->st.ensure(j.spec.replicas, ctx->ld, j.err)) return DA_ENOMEM;
     const LaunchShape sh = batch_shape(ctx);
-    j.J = make_job(ctx, *j.tables, j.spec.replicas, 0u, j.spec.seed, j.spec.steps,
+    j.J = make_job(ctx, j.tables.get(), j.spec.replicas, 0u, j.spec.seed, j.spec.steps,
                    j.spec.schedule, sh);
     if (const char *why = job_range_error(j.J)) {
         j.err = why;

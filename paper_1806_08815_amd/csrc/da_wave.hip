@@ -1,0 +1,706 @@
+// da_wave.hip -- the Digital Annealer step with one wavefront per replica.
+//
+// Method: Algorithm 2 (Sec. II.B) of Aramon et al., arXiv:1806.08815.
+//
+// A replica of up to 1024 variables fits one wavefront: lane g owns the F
+// variables g*F .. g*F+F-1 (F = 1, 2, 4, 8, 16).  Then nothing of a step leaves
+// the wave: no barrier, no exchange through LDS, no random-number waves.  What
+// bounds such a step is its instruction count (a wave issues one instruction
+// of any kind every four cycles), so the work is laid out to issue little and
+// to wait for nothing:
+//   * The Metropolis test is the sign of one sum per flip.  The threshold
+//     of a draw is bracketed by one fp32 log2 and multiply-add of the draw (see
+//     wave_level), and a cost inside the bracket is decided by the definition
+//     d < T (-ln U_u) in double.  No threshold table, bracket table or direct
+//     table is built, staged or read.
+//   * Costs are held as fixed point d 2^q, q chosen per level so that T 2^q is
+//     about 2^16: the bracket is then a few parts in 10^5 of T for couplings of
+//     any scale, +-1 instances included.
+//   * Step s+1's draws (Philox) and brackets are computed while row k of W is
+//     in flight.  With F < 8 a Philox block serves 8/F lanes; the wave then
+//     draws 8/F steps at once, one block per lane, and hands them out through LDS.
+//   * The first rounds of Philox are constant over the steps but for two xors;
+//     the xors of the later ones are three-input.
+//   * Energy, offset and counts are wave-uniform scalars.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "da_device.h"
+#include "da_internal.h"
+
+#ifndef DAPT_PART
+#error "compile with -DDAPT_PART=0 .. 3"
+#endif
+
+namespace dapt {
+
+namespace {
+
+constexpr double kLn2 = 0.69314718055994530942;
+
+// a ^ b ^ k, k wave-uniform
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k) {
+    uint32_t r;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "s"(k));
+    return r;
+}
+
+// The Metropolis draws of one Philox block (counter (block, step, rid, 0)) over
+// many steps.  Of the ten rounds, what does not depend on the step is kept: the
+// first product of rounds 0 and 2, the second of rounds 0 and 1.
+struct DrawBlock {
+    uint32_t b1, d2, e2, f3;   // with the round keys they are xored with folded in
+    __device__ __forceinline__ void init(uint32_t block, uint32_t rid, uint32_t k0, uint32_t k1) {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * block, p1 = (uint64_t)kPhiloxM1 * rid;
+        const uint32_t c2 = (uint32_t)(p0 >> 32) ^ kTagMetropolis ^ k1;
+        b1 = (uint32_t)p0 ^ (k1 + kPhiloxW1);
+        const uint64_t q1 = (uint64_t)kPhiloxM1 * c2;
+        const uint32_t c0 = (uint32_t)(q1 >> 32) ^ (uint32_t)p1 ^ (k0 + kPhiloxW0);
+        d2 = (uint32_t)q1 ^ (k0 + 2u * kPhiloxW0);
+        const uint64_t q0 = (uint64_t)kPhiloxM0 * c0;
+        e2 = (uint32_t)(q0 >> 32) ^ (k1 + 2u * kPhiloxW1);
+        f3 = (uint32_t)q0 ^ (k1 + 3u * kPhiloxW1);
+    }
+    // r0: hi(M1 rid) ^ k0, wave-uniform
+    __device__ __forceinline__ uint4 draw(uint32_t step, uint32_t r0, uint32_t k0,
+                                          uint32_t k1) const {
+        const uint64_t s1 = (uint64_t)kPhiloxM0 * (r0 ^ step);      // round 1
+        uint32_t c2 = (uint32_t)(s1 >> 32) ^ b1;
+        uint64_t p1 = (uint64_t)kPhiloxM1 * c2;                     // round 2
+        uint32_t c0 = (uint32_t)(p1 >> 32) ^ d2;
+        uint32_t c1 = (uint32_t)p1;
+        c2 = (uint32_t)s1 ^ e2;
+        uint64_t p0 = (uint64_t)kPhiloxM0 * c0;                     // round 3
+        p1 = (uint64_t)kPhiloxM1 * c2;
+        c0 = xor3((uint32_t)(p1 >> 32), c1, k0 + 3u * kPhiloxW0);
+        c1 = (uint32_t)p1;
+        c2 = (uint32_t)(p0 >> 32) ^ f3;
+        uint32_t c3 = (uint32_t)p0;
+#pragma unroll
+        for (int r = 4; r < 10; ++r) {
+            p0 = (uint64_t)kPhiloxM0 * c0;
+            p1 = (uint64_t)kPhiloxM1 * c2;
+            c0 = xor3((uint32_t)(p1 >> 32), c1, k0 + (uint32_t)r * kPhiloxW0);
+            c1 = (uint32_t)p1;
+            c2 = xor3((uint32_t)(p0 >> 32), c3, k1 + (uint32_t)r * kPhiloxW1);
+            c3 = (uint32_t)p0;
+        }
+        return make_uint4(c0, c1, c2, c3);
+    }
+};
+
+// One temperature of the wave kernel.  With T' = T 2^q and y = T' (-ln U_u), a
+// flip of fixed-point cost d' = d 2^q is accepted iff d' < y.  Per draw
+//   L(u) = round(log2(u + 1/2) ga + gb), ga = -T' ln 2, gb = 16 T' ln 2 - margin,
+// where the margin covers the rounding and m, a bound on the error (gerr per
+// unit of T': the fp32 roundings and ln 2 times the device's log2 error, which
+// is measured over all 65536 arguments).  Then d' <= L + c0 implies d' < y, and
+// d' >= L + c0 + wt implies d' >= y; a cost in between takes the definition.
+//   Without CLAMP the sum carries 1.5 2^23, so that its bits are that constant's
+// plus L (T' < 2^18 keeps it in [2^23, 2^24)); c0 = 0, wt = 2 m + 3.
+//   With CLAMP, L = max(0, trunc(..)) by a conversion: any T', and costs of zero
+// never fall in between, which T' of a few units (couplings too large for more
+// fraction bits) would make common: where q >= 1, c0 = 1 is allowed, as d' <= 1
+// means d' <= 0 < y.  wt = 2 m + 2.
+// T = 0 accepts d' < 0 only: ga = 0, L = 0 and c0 = -1 state it exactly.
+// The test uses z = L + c0 + E_off' - s' less one where x = 0 (s' = (1 - 2x) h',
+// its negative taken as a one's complement): z >= 0 accepts, z < -wt rejects.
+struct WaveLevel {
+    float ga, gb;
+    uint32_t zamb;   // z is undecided iff (uint32_t)z > zamb
+    int c0;          // with the constant of the sum's bits taken off
+    int q;
+    double T;        // T 2^q
+};
+
+template <bool CLAMP>
+__device__ __forceinline__ WaveLevel wave_level(double T, int qcap, float gerr) {
+    WaveLevel w;
+    const bool pos = T > 0.0;
+    // (T = f 2^e with f in [1/2, 1): T 2^q < 2^17)
+    const int e = pos ? __builtin_amdgcn_frexp_exp(T) : 16;
+    const int q = min(max(17 - e, 0), qcap);
+    const double Tq = pos ? __builtin_ldexp(T, q) : 0.0;
+    const float m = pos ? (float)Tq * gerr + 0.01f : 0.0f;
+    const int c0 = !pos ? -1 : (CLAMP && q > 0 ? 1 : 0);
+    const int wt = !pos ? (q > 0 ? 0 : 1) : (int)(2.0f * m) + (CLAMP ? 2 : 3);
+    const double mid = Tq * (16.0 * kLn2);
+    w.ga = (float)(-Tq * kLn2);
+    if constexpr (CLAMP)
+        w.gb = pos ? (float)(mid - (double)m - (double)c0) : 0.0f;
+    else
+        w.gb = pos ? (float)(12582912.0 + __builtin_floor(mid - (double)m - 0.5)) : 12582912.0f;
+    w.zamb = (uint32_t)__builtin_amdgcn_readfirstlane((int)(0xFFFFFFFFu - (uint32_t)wt));
+    w.c0 = __builtin_amdgcn_readfirstlane(CLAMP ? c0 : (int)((uint32_t)c0 - kGenMagic));
+    w.q = __builtin_amdgcn_readfirstlane(q);
+    w.T = Tq;
+    return w;
+}
+
+template <bool CLAMP>
+__device__ __forceinline__ int draw_bound(uint32_t u, float ga, float gb) {
+    const float lg = __builtin_amdgcn_logf((float)u + 0.5f);
+    const float t = __builtin_fmaf(lg, ga, gb);
+    if constexpr (!CLAMP) return __float_as_int(t);
+    int L;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(L) : "v"(t));   // negative -> 0
+    return L;
+}
+
+// Inclusive prefix sum over the wave (rows of 16 by shifts, then the rows'
+// predecessors by the broadcasts of lanes 15 and 31).
+__device__ __forceinline__ int incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// h[bit], bit wave-uniform (negative: some field).  Of 16 fields by an indexed
+// register read, which the compiler makes of a vector: 15 selects cost more
+// (1024 replicas of N = 1024: 683 -> 672 ns a step); of 8 the selects are faster (482 -> 436 ns a step), switching the index
+// mode on and off stalls the wave.
+template <int F>
+__device__ __forceinline__ int field_at(const int (&h)[F], int bit) {
+    if constexpr (F == 1) {
+        return h[0];
+    } else if constexpr (F < 16) {
+        return pick_field<F>(h, bit);
+    } else {
+        typedef int V __attribute__((ext_vector_type(F)));
+        V v;
+#pragma unroll
+        for (int f = 0; f < F; ++f) v[f] = h[f];
+        return v[bit & (F - 1)];
+    }
+}
+
+// First set bit of a wave-uniform mask; -1 when there is none.
+__device__ __forceinline__ int first_bit(uint64_t m) {
+    int r;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(r) : "s"(m));
+    return r;
+}
+__device__ __forceinline__ int first_bit(uint32_t m) {
+    int r;
+    asm("s_ff1_i32_b32 %0, %1" : "=s"(r) : "s"(m));
+    return r;
+}
+
+// Runs steps [s0, s1) of replica rr by one wave.  wl: W in LDS (WLDS); ring:
+// this wave's Philox blocks in LDS, [2][64] (F < 8).  FEAT: per-step schedules
+// and single-trial proposals; without it neither leaves code in the loop.
+template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
+__device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t *wl,
+                                         uint4 *ring) {
+    constexpr int NB = F >= 8 ? F / 8 : 1;   // Philox blocks per lane and step (F >= 8)
+    constexpr int P = F >= 8 ? 1 : 8 / F;    // steps drawn at once
+    constexpr int RW = F >= 2 ? F / 2 : 1;   // 32-bit words of a lane's draws
+    constexpr int NX = (F + 3) / 4;
+    typedef typename VecOf<WT, F>::type RowV;
+    const int lane = threadIdx.x & 63;
+    const int i0 = lane * F;
+    const int ld = J.ld;
+    const bool lane_has = i0 < ld;
+    const int col0 = lane_has ? i0 : 0;   // lanes past the row hold ghost flips only
+    const uint32_t rid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(J.rid_base + (uint32_t)rr));
+    const uint32_t k0 = (uint32_t)J.seed, k1 = (uint32_t)(J.seed >> 32);
+    const uint32_t r0 = __umulhi(kPhiloxM1, rid) ^ k0;
+    const bool perstep = FEAT && J.stepT != nullptr;
+    const bool single = FEAT && J.single != 0;
+    const uint32_t ge_mask = lane < F ? ((0xFFFFu << lane) & ((1u << F) - 1u)) : 0u;
+    // int32 couplings below 2^23 take the 24-bit multiply-add
+    const bool w24 = sizeof(WT) < 4 || J.w24 != 0;
+
+    // --- replica state -----------------------------------------------------
+    int h[F];
+    uint32_t xb = 0, bxb = 0, vmask = 0;
+#pragma unroll
+    for (int f = 0; f < F; ++f) h[f] = 0;
+    const size_t base = (size_t)rr * ld + i0;
+    typedef typename VecOf<int, F>::type IV;
+    typedef typename VecOf<uint8_t, F>::type BV;
+    if (lane_has) {
+        const IV hv = *reinterpret_cast<const IV *>(J.h + base);
+        const BV xv = *reinterpret_cast<const BV *>(J.x + base);
+        const BV bv = *reinterpret_cast<const BV *>(J.bx + base);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            h[f] = hv[f];
+            xb |= (uint32_t)(xv[f] & 1) << f;
+            bxb |= (uint32_t)(bv[f] & 1) << f;
+            if (i0 + f < J.N) vmask |= 1u << f;
+        }
+    }
+    // the complement of x as bytes 0x00 / 0xFF, four flips per word: a flip's
+    // sign mask is then one sign-extended byte operand
+    uint32_t nx[NX];
+#pragma unroll
+    for (int q = 0; q < NX; ++q) nx[q] = 0u;
+#pragma unroll
+    for (int f = 0; f < F; ++f) nx[f >> 2] |= ((xb >> f) & 1u) ? 0u : (0xFFu << (8 * (f & 3)));
+    // energies as the best one and what the current one lies above it
+    int64_t bE = uniform64(J.bE[rr]);
+    int64_t gap = uniform64(J.E[rr]) - bE;
+    int eoff = __builtin_amdgcn_readfirstlane(J.eoff[rr]);
+    uint32_t nacc = 0;
+    const int inc = J.eoff_inc, inc_cap = kEoffMax - J.eoff_inc;
+    // past max |h| the offset changes no decision: every flip is accepted
+    const int ecap = J.ecap;
+
+    // --- steps and level in force --------------------------------------------
+    int64_t a = J.s0, b = J.s1;
+    if (J.round_ptr) {
+        a = (int64_t)*J.round_ptr * J.K;
+        b = a + J.K;
+    }
+    uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
+    const uint32_t s1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+    int lvl = 0;
+    uint32_t s_next = 0xFFFFFFFFu;   // first step of the next level
+    double T0;
+    auto next_of = [&](int l) -> uint32_t {
+        const int64_t n = next_level_step(l, J.L, J.S);
+        return (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)(n > (int64_t)0x7FFFFFFF ? 0xFFFFFFFFu : (uint32_t)n));
+    };
+    auto step_T = [&](uint32_t t) -> double {   // per-step schedules; past the end: the last
+        return J.stepT[min((int64_t)t, J.S - 1)].T;
+    };
+    if (J.lvl_of_rep) {
+        lvl = __builtin_amdgcn_readfirstlane(J.lvl_of_rep[rr]);
+        T0 = J.temps[lvl];
+    } else if (perstep) {
+        T0 = step_T(s);
+    } else {
+        lvl = __builtin_amdgcn_readfirstlane(level_of(a, J.L, J.S));
+        s_next = next_of(lvl);
+        T0 = J.temps[lvl];
+    }
+    WaveLevel lv = wave_level<CLAMP>(T0, J.qcap, J.gerr);
+#pragma unroll
+    for (int f = 0; f < F; ++f) h[f] = (int)((uint32_t)h[f] << lv.q);
+    int ec = 0, dwp = 0, dwn = 0;
+    auto level_consts = [&]() {
+        ec = (int)(((uint32_t)min(eoff, ecap) << lv.q) + (uint32_t)lv.c0);
+        dwp = (int)((uint32_t)J.wscale << lv.q);
+        dwn = -dwp;
+    };
+    auto rescale = [&](int dq) {   // to dq more fraction bits
+#pragma unroll
+        for (int f = 0; f < F; ++f) h[f] = dq > 0 ? (int)((uint32_t)h[f] << dq) : h[f] >> -dq;
+    };
+    level_consts();
+    double Tn1 = 0.0;   // per-step: the temperature of step s + 1
+    if (perstep) Tn1 = step_T(s + 1);
+
+    // --- draws ---------------------------------------------------------------
+    DrawBlock db[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+        db[q].init(F >= 8 ? (uint32_t)(lane * NB + q) : (uint32_t)(lane & (8 * F - 1)), rid, k0, k1);
+    // F < 8: the blocks of the P steps from t (a multiple of P), one per lane,
+    // into the half of the ring that the group before it does not hold
+    auto produce = [&](uint32_t t) {
+        const uint32_t sub = (uint32_t)lane / (8u * F);
+        ring[(t & P) / P * 64 + lane] = db[0].draw(t + sub, r0, k0, k1);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // this lane's draws of step t: flip f is half f & 1 of word f >> 1
+    auto fetch = [&](uint32_t t, uint32_t (&r)[RW]) {
+        if constexpr (F >= 8) {
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const uint4 v = db[q].draw(t, r0, k0, k1);
+                r[4 * q] = v.x;
+                r[4 * q + 1] = v.y;
+                r[4 * q + 2] = v.z;
+                r[4 * q + 3] = v.w;
+            }
+        } else {
+            const uint8_t *p = reinterpret_cast<const uint8_t *>(ring) +
+                               (t & (2 * P - 1)) * (128 * F) + lane * (2 * F);
+            if constexpr (F == 4) {
+                const uint2 v = *reinterpret_cast<const uint2 *>(p);
+                r[0] = v.x;
+                r[RW - 1] = v.y;
+            } else if constexpr (F == 2) {
+                r[0] = *reinterpret_cast<const uint32_t *>(p);
+            } else {
+                r[0] = *reinterpret_cast<const uint16_t *>(p);
+            }
+        }
+    };
+    auto draw16 = [&](const uint32_t (&r)[RW], int f) -> uint32_t {
+        return (f & 1) ? (r[f >> 1] >> 16) : (F == 1 ? r[0] : (r[f >> 1] & 0xFFFFu));
+    };
+    int tv[F];
+    auto bounds = [&](const uint32_t (&r)[RW]) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) tv[f] = draw_bound<CLAMP>(draw16(r, f), lv.ga, lv.gb);
+    };
+    // selection draws: lane l holds that of step (s & ~63) + l
+    int vsel = 0;
+    // rn: the draws of this step (F >= 8), or of the next one, read ahead from
+    // the ring, which holds this step's and the next one's group (F < 8)
+    uint32_t rn[RW];
+    if (P > 1) produce(s & ~(uint32_t)(P - 1));
+    fetch(s, rn);
+    bounds(rn);
+    if (P > 1) {
+        if (((s + 1) & (P - 1)) == 0) produce(s + 1);
+        fetch(s + 1, rn);
+    }
+    int prop = single ? (int)(s % (uint32_t)J.N) : 0;
+
+    // segments in which neither the level nor the selection draws change
+    for (bool first = true; s != s1; first = false) {
+        if (first || (s & 63u) == 0u)
+            vsel = (int)philox(0u, (s & ~63u) + (uint32_t)lane, rid, kTagSelect, k0, k1).x;
+        if (s == s_next) {
+            // the level that opens here: its fixed point, and this step's
+            // bounds once more
+            const int q = lv.q;
+            lvl = (int64_t)J.L > J.S
+                      ? __builtin_amdgcn_readfirstlane(level_of((int64_t)s, J.L, J.S))
+                      : lvl + 1;
+            s_next = next_of(lvl);
+            lv = wave_level<CLAMP>(J.temps[lvl], J.qcap, J.gerr);
+            if (lv.q != q) rescale(lv.q - q);
+            level_consts();
+            uint32_t rc[RW];
+            if constexpr (P > 1) {
+                fetch(s, rc);
+                bounds(rc);
+            } else {
+                bounds(rn);
+            }
+        }
+        const uint32_t seg = min(min(s1, s_next), (s & ~63u) + 64u);
+        for (; s != seg; ++s) {
+            // 1. the tests.  sgn collects the sign bits of z; undecided costs
+            // are the largest z as unsigned numbers
+            uint32_t sgn = 0, zmax = 0;
+            int z[F];
+#pragma unroll
+            for (int f = F - 1; f >= 0; --f) {
+                const int mx = (int)(int8_t)(nx[f >> 2] >> (8 * (f & 3)));
+                uint32_t zs;
+                asm("v_add3_u32 %0, %1, %2, %3" : "=v"(zs) : "v"(h[f] ^ mx), "v"(tv[f]), "s"(ec));
+                z[f] = (int)zs;
+                sgn = F == 1 ? zs >> 31 : __builtin_amdgcn_alignbit(sgn, zs, 31);
+                zmax = max(zmax, zs);
+            }
+            uint32_t acc;
+            asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(acc) : "v"(sgn), "v"(vmask));   // ~sgn & vmask
+            if (__builtin_expect(ballot(zmax > lv.zamb) != 0, 0)) {
+                // rare: the definition, in double
+                uint32_t rc[RW];
+                if constexpr (P > 1) {
+                    fetch(s, rc);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < RW; ++q) rc[q] = rn[q];
+                }
+                const int eo = ec - lv.c0;
+                double g[F];
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    g[f] = J.G[(uint32_t)z[f] > lv.zamb ? draw16(rc, f) : 0u];
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const int mx = (int)(int8_t)(nx[f >> 2] >> (8 * (f & 3)));
+                    const int d = mx - (h[f] ^ mx) - eo;   // (1 - 2x) h - E_off
+                    const bool in = (uint32_t)z[f] > lv.zamb && ((vmask >> f) & 1u);
+                    acc |= (uint32_t)(in && (double)d < lv.T * g[f]) << f;
+                }
+            }
+            if (single) acc &= lane == prop / F ? 1u << (prop % F) : 0u;
+
+            // 2. the chosen flip: the j-th accepted one in index order.  A step
+            // that accepts none runs the same instructions with ts = -1 (no
+            // lane), row 0 and factor 0: the branch around them costs more
+            const uint32_t v = (uint32_t)readlane(vsel, (int)(s & 63u));
+            int m, ts, bit = 0;
+            if constexpr (F == 1) {
+                const uint64_t mk = ballot(acc != 0);
+                m = (int)__popcll(mk);
+                const int j = (int)__umulhi(v, (uint32_t)m);
+                ts = first_bit(ballot(mbcnt64(mk) == j) & mk);
+            } else if constexpr (F == 2) {
+                const uint64_t m0 = ballot((acc & 1u) != 0), m1 = ballot((acc & 2u) != 0);
+                m = (int)(__popcll(m0) + __popcll(m1));
+                const int j = (int)__umulhi(v, (uint32_t)m);
+                const int excl = mbcnt64(m0) + mbcnt64(m1);
+                // of the j-th flip's lane either flip 0 has rank j, or flip 1 has
+                const uint64_t e0 = ballot(excl == j) & m0;
+                const uint64_t e1 = ballot(excl + (int)(acc & 1u) == j) & m1;
+                const int t0 = first_bit(e0), t1 = first_bit(e1);   // one of them is -1
+                ts = max(t0, t1);
+                asm("s_not_b32 %0, %1\n\ts_lshr_b32 %0, %0, 31" : "=s"(bit) : "s"(t1) : "scc");
+            } else {
+                const int incl = incl_scan(__popc(acc));
+                m = readlane(incl, 63);
+                const int j = (int)__umulhi(v, (uint32_t)m);
+                ts = first_bit(ballot(incl > j));
+                const uint32_t rs = (uint32_t)readlane((int)acc, ts);
+                // the set bit with incl - j set bits at or above it
+                const uint32_t need = (uint32_t)(readlane(incl, ts) - j);
+                bit = first_bit((uint32_t)ballot((uint32_t)__popc(rs & ge_mask) == need) & rs);
+            }
+            const int k = max(ts * F + bit, 0);
+            // 3. row k of W, the step's only bulk traffic
+            typedef __attribute__((address_space(3))) const RowV LdsRowV;
+            typedef __attribute__((address_space(1))) const RowV GlobalRowV;
+            RowV raw;
+            if constexpr (WLDS)
+                raw = *(LdsRowV *)(reinterpret_cast<const WT *>(wl) + k * ld + col0);
+            else
+                raw = *(GlobalRowV *)(reinterpret_cast<const WT *>(J.W) +
+                                      (size_t)(uint32_t)(k * ld) + col0);
+            const uint32_t xk = (uint32_t)readlane((int)xb, ts);
+            const int hk = readlane(field_at<F>(h, bit), ts) >> lv.q;
+            // (1 - 2 x_k) h_k, the rows' factor and the count, none of them when
+            // m = 0 (written out: the compiler carries conditions of scalars
+            // through 64-bit masks)
+            int dE, dw;
+#define DAPT_FLIP(BIT, ...)                                                            \
+    asm("s_sub_i32 %0, 0, %3\n\t"                                                      \
+        "s_bitcmp1_b32 %4, " BIT "\n\t"                                                \
+        "s_cselect_b32 %0, %0, %3\n\t"                                                 \
+        "s_cselect_b32 %1, %6, %5\n\t"                                                 \
+        "s_cmp_gt_i32 %7, 0\n\t"                                                       \
+        "s_cselect_b32 %0, %0, 0\n\t"                                                  \
+        "s_cselect_b32 %1, %1, 0\n\t"                                                  \
+        "s_addc_u32 %2, %2, 0"                                                         \
+        : "=&s"(dE), "=&s"(dw), "+s"(nacc)                                             \
+        : "s"(hk), "s"(xk), "s"(dwp), "s"(dwn), "s"(m) __VA_ARGS__                     \
+        : "scc")
+            if constexpr (F == 1) {
+                DAPT_FLIP("0", );
+            } else {
+                DAPT_FLIP("%8", , "s"(bit));
+            }
+#undef DAPT_FLIP
+            if (lane == ts) {
+                xb ^= 1u << bit;
+                const uint64_t mb = 0xFFull << (8 * (bit & 7));
+                if constexpr (NX <= 2) {
+                    nx[0] ^= (uint32_t)mb;
+                    if (NX > 1) nx[NX - 1] ^= (uint32_t)(mb >> 32);
+                } else {
+                    const uint64_t lo = bit < 8 ? mb : 0ull, hi = bit < 8 ? 0ull : mb;
+                    nx[0] ^= (uint32_t)lo;
+                    nx[1] ^= (uint32_t)(lo >> 32);
+                    nx[NX - 2] ^= (uint32_t)hi;
+                    nx[NX - 1] ^= (uint32_t)(hi >> 32);
+                }
+            }
+            gap += (int64_t)dE;
+            int gap_hi = (int)(gap >> 32);
+            asm("" : "+s"(gap_hi));   // (tested as a scalar)
+            if (__builtin_expect(gap_hi < 0, 0)) {
+                bE += gap;
+                gap = 0;
+                bxb = xb;
+            }
+            const int eo = eoff;
+            eoff = 0;
+            ec = lv.c0;
+            if (__builtin_expect(m == 0, 0)) {
+                asm volatile("");   // (a branch: the selects cost more)
+                // min(E_off + inc, 2^30) without leaving int32 (both in [0, 2^30])
+                eoff = min(eo, inc_cap) + inc;
+                ec = (int)(((uint32_t)min(eoff, ecap) << lv.q) + (uint32_t)lv.c0);
+            }
+
+            // 4. while the row is in flight: the draws and bounds of step s + 1
+            int dq = 0;
+            if constexpr (FEAT) {
+                if (perstep) {
+                    // its temperature; the fields follow after this step's update
+                    const int q = lv.q;
+                    lv = wave_level<CLAMP>(Tn1, J.qcap, J.gerr);
+                    dq = lv.q - q;
+                    Tn1 = step_T(s + 2);
+                }
+                if (single) prop = prop + 1 == J.N ? 0 : prop + 1;
+            }
+            if constexpr (P == 1) {
+                fetch(s + 1, rn);
+                bounds(rn);
+            } else {
+                bounds(rn);
+                if (((s + 2) & (P - 1)) == 0) produce(s + 2);
+                fetch(s + 2, rn);
+            }
+
+            // 5. every field moves by +-W row k
+            if constexpr (sizeof(WT) == 2 && F >= 2) {
+                update_i16<WT, F>(raw, dw, h);
+            } else if constexpr (sizeof(WT) == 2) {
+                asm("v_mad_i32_i16 %0, %1, %2, %0" : "+v"(h[0]) : "v"((int)raw[0]), "s"(dw));
+            } else if (w24) {
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    asm("v_mad_i32_i24 %0, %1, %2, %0" : "+v"(h[f]) : "v"((int)raw[f]), "s"(dw));
+            } else {
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    h[f] = (int)((uint32_t)h[f] + (uint32_t)raw[f] * (uint32_t)dw);
+            }
+            if constexpr (FEAT) {
+                if (perstep) {
+                    if (dq) rescale(dq);
+                    level_consts();
+                }
+            }
+        }
+    }
+
+    // --- state back to HBM -----------------------------------------------------
+    if (lane_has) {
+        IV hv;
+        BV xv, bv;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            hv[f] = h[f] >> lv.q;
+            xv[f] = (uint8_t)((xb >> f) & 1u);
+            bv[f] = (uint8_t)((bxb >> f) & 1u);
+        }
+        *reinterpret_cast<IV *>(J.h + base) = hv;
+        *reinterpret_cast<BV *>(J.x + base) = xv;
+        *reinterpret_cast<BV *>(J.bx + base) = bv;
+    }
+    if (lane == 0) {
+        J.E[rr] = bE + gap;
+        J.bE[rr] = bE;
+        J.eoff[rr] = eoff;
+        J.nacc[rr] += nacc;
+    }
+}
+
+// One wave per replica, J.RPW of them per workgroup (they share W in LDS and
+// nothing else).  LDS: [W][2][64] Philox blocks per wave (F < 8).
+template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
+__global__ __launch_bounds__(1024) void k_wave(JobDesc J) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    int w_bytes = 0;
+    if constexpr (WLDS) {
+        const int n16 = J.N * J.ld * (int)sizeof(WT) / 16;
+        const uint4 *src = reinterpret_cast<const uint4 *>(J.W);
+        uint4 *dst = reinterpret_cast<uint4 *>(smem);
+        for (int q = threadIdx.x; q < n16; q += blockDim.x) dst[q] = src[q];
+        __syncthreads();
+        w_bytes = n16 * 16;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int rr = blockIdx.x * J.RPW + wave;
+    if (rr >= J.R) return;
+    wave_run<WT, F, WLDS, CLAMP, FEAT>(
+        J, rr, smem, reinterpret_cast<uint4 *>(smem + w_bytes) + (F < 8 ? wave * 128 : 0));
+}
+
+template <typename WT, int F, bool WLDS>
+int launch_wave_l(const JobDesc &J, int blocks, int threads, size_t lds, void *stream) {
+    const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    if (J.stepT || J.single)
+        hipLaunchKernelGGL((k_wave<WT, F, WLDS, true, true>), dim3(blocks), dim3(threads), lds, st, J);
+    else if (J.wclamp)
+        hipLaunchKernelGGL((k_wave<WT, F, WLDS, true, false>), dim3(blocks), dim3(threads), lds, st, J);
+    else
+        hipLaunchKernelGGL((k_wave<WT, F, WLDS, false, false>), dim3(blocks), dim3(threads), lds, st, J);
+    return (int)hipGetLastError();
+}
+
+template <typename WT, int F>
+int launch_wave_f(const JobDesc &J, int blocks, int threads, size_t lds, void *stream) {
+    // (a row of 16 flips per lane is past what fits LDS)
+    if constexpr (F < 16) {
+        if (J.w_lds) return launch_wave_l<WT, F, true>(J, blocks, threads, lds, stream);
+    }
+    return launch_wave_l<WT, F, false>(J, blocks, threads, lds, stream);
+}
+
+}  // namespace
+
+// (defined here, compiled for one coupling type per part of this file)
+template <typename WT>
+int launch_wave_w(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
+    switch (F) {
+        case 1: return launch_wave_f<WT, 1>(J, blocks, threads, lds, stream);
+        case 2: return launch_wave_f<WT, 2>(J, blocks, threads, lds, stream);
+        case 4: return launch_wave_f<WT, 4>(J, blocks, threads, lds, stream);
+        case 8: return launch_wave_f<WT, 8>(J, blocks, threads, lds, stream);
+        case 16: return launch_wave_f<WT, 16>(J, blocks, threads, lds, stream);
+        default: return (int)hipErrorInvalidValue;
+    }
+}
+
+#if DAPT_PART == 1
+template int launch_wave_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
+#elif DAPT_PART == 2
+template int launch_wave_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
+#elif DAPT_PART == 3
+template int launch_wave_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
+#endif
+
+#if DAPT_PART == 0
+extern template int launch_wave_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
+extern template int launch_wave_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
+extern template int launch_wave_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
+
+size_t wave_lds_bytes(int F, int RPW, int64_t w_lds_bytes) {
+    return (size_t)w_lds_bytes + (F < 8 ? (size_t)RPW * 2048 : 0);
+}
+
+int launch_wave(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
+    // a wave per replica holds 64 F variables; everything the kernel indexes is
+    // sized by these
+    if (job_range_error(J) != nullptr || J.NW != 1 || J.NH != 0 || J.N > 64 * F || !J.G ||
+        (!J.temps && !J.stepT) || threads != 64 * J.RPW ||
+        (int64_t)blocks * J.RPW < J.R ||
+        lds < wave_lds_bytes(F, J.RPW, J.w_lds ? (int64_t)J.N * J.ld * J.dtype : 0))
+        return (int)hipErrorInvalidValue;
+    switch (J.dtype) {
+        case 1: return launch_wave_w<int8_t>(J, F, blocks, threads, lds, stream);
+        case 2: return launch_wave_w<int16_t>(J, F, blocks, threads, lds, stream);
+        case 4: return launch_wave_w<int32_t>(J, F, blocks, threads, lds, stream);
+        default: return (int)hipErrorInvalidValue;
+    }
+}
+
+// Largest |log2 as the device evaluates it - log2| over the arguments u + 1/2
+// of all draws: G[u] = -ln U_u gives the latter as 16 - G[u] / ln 2.
+__global__ __launch_bounds__(256) void k_log_error(const double *__restrict__ G, float *out) {
+    __shared__ float part[256];
+    float e = 0.0f;
+    for (int u = threadIdx.x; u < 65536; u += 256) {
+        const float lg = __builtin_amdgcn_logf((float)u + 0.5f);
+        e = fmaxf(e, (float)fabs((double)lg - (16.0 - G[u] / kLn2)));
+    }
+    part[threadIdx.x] = e;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) part[threadIdx.x] = fmaxf(part[threadIdx.x], part[threadIdx.x + o]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *out = part[0];
+}
+
+int launch_log_error(const double *G, float *out, void *stream) {
+    hipLaunchKernelGGL(k_log_error, dim3(1), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), G,
+                       out);
+    return (int)hipGetLastError();
+}
+#endif  // DAPT_PART == 0
+
+}  // namespace dapt

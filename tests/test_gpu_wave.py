@@ -1,0 +1,118 @@
+"""The one-wave step kernel (N <= 1024, chosen by da_anneal) against the CPU
+oracle: every number of flips per lane at its smallest and largest N and at
+ragged ones, every coupling type with W in LDS and in global memory, couplings
+from +-1 to 10^7 (fixed point with and without fraction bits, brackets from two
+units to hundreds), levels that change the fixed point, schedules with more
+levels than steps, per-step schedules, single trials, T = 0, large offsets, and
+replica counts that share workgroups.  Whole numbers: bit-exact."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1806_08815_amd import instances
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("best_x", "best_E", "final_x", "final_E", "n_accept")
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    from paper_1806_08815_amd import api as a
+    a.lib()
+    return a
+
+
+def _instance(kind, N, seed=5):
+    """Q, hottest and coldest temperature, offset increment."""
+    if kind == "sk":
+        u = max(1.0, N ** 0.5)
+        return instances.ising_to_qubo(instances.sk_bimodal(N, seed))[0], 3.0 * u, 0.05 * u, 1
+    if kind == "cold":   # degenerate flips at temperatures far below a coupling
+        return instances.ising_to_qubo(instances.sk_bimodal(N, seed))[0], 1.0, 0.01, 1
+    if kind == "gauss":
+        q = instances.ising_to_qubo(instances.sk_gaussian(N, seed, scale=2**16))[0]
+        return q, 3.0 * 2**16, 0.05 * 2**16, 2**16
+    lim = int(kind[1:])  # qLIM: dense, coefficients up to LIM
+    q = instances.random_qubo(N, seed, lo=-lim, hi=lim)
+    u = 0.5 * lim * N ** 0.5
+    return q, 3.0 * u, 0.05 * u, lim
+
+
+def _check(api, Q, dtype, R, S, L, T_hi, T_lo, inc, kind="geometric", init="zeros",
+           trial="parallel", seed=11):
+    ctx = api.da_create(Q, dtype)
+    sch = api.schedule(T_hi, T_lo, kind, L, eoff_inc=inc, init=init, trial=trial)
+    gpu = api.da_anneal(ctx, sch, R, S, seed)
+    rows = sorted({0, R // 2, R - 1})
+    for r in rows:
+        ref = oracle.anneal(Q, T_hi=T_hi, T_lo=T_lo, kind=int(kind != "geometric"), n_levels=L,
+                            eoff_inc=inc, init=int(init != "zeros"), trial=int(trial != "parallel"),
+                            replica_base=r, replicas=1, steps=S, seed=seed)
+        for k in KEYS:
+            assert np.array_equal(gpu[k][r], ref[k][0]), (k, r)
+    return ctx
+
+
+@pytest.mark.parametrize("kind", ["sk", "cold", "gauss", "q100", "q100000"])
+@pytest.mark.parametrize("N", [1, 2, 33, 64, 65, 127, 128, 129, 200, 256, 257, 449, 500, 512])
+def test_sizes(api, kind, N):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    ctx = _check(api, Q, 0, 3, 1500, 12, T_hi, T_lo, inc, init="random" if N % 2 else "zeros")
+    assert api.da_last_kernel_stats(ctx)["rng_waves"] == 0
+
+
+@pytest.mark.parametrize("dtype", [1, 2, 4])
+@pytest.mark.parametrize("kind,N,R", [("sk", 64, 600), ("sk", 100, 700), ("sk", 180, 520),
+                                      ("sk", 250, 300), ("sk", 390, 260), ("sk", 460, 1100)])
+def test_types_and_shared_workgroups(api, kind, N, R, dtype):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    _check(api, Q, dtype, R, 400, 6, T_hi, T_lo, inc)
+
+
+@pytest.mark.parametrize("N", [20, 90, 210, 400])
+@pytest.mark.parametrize("kind,L,S,extra", [
+    ("sk", 700, 300, {}),                              # levels skipped
+    ("gauss", 1, 300, {}),
+    ("sk", 0, 700, dict(kind="linear_beta")),          # a new temperature every step
+    ("gauss", 0, 300, dict(init="random")),
+    ("sk", 5, 900, dict(trial="single")),
+    ("q100", 0, 900, dict(trial="single")),
+    ("q100", 3, 0, {}), ("sk", 0, 1, {}),
+])
+def test_schedules(api, N, kind, L, S, extra):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    _check(api, Q, 0, 3, S, L, T_hi, T_lo, inc, **extra)
+
+
+@pytest.mark.parametrize("N", [40, 130, 300])
+@pytest.mark.parametrize("inc", [0, 7, 2**30, 2**31 - 1])
+def test_zero_temperature_and_offsets(api, N, inc):
+    Q = instances.random_qubo(N, 3, lo=-300, hi=300)
+    _check(api, Q, 0, 3, 400, 4, 0.0, 0.0, inc)
+    _check(api, Q, 0, 3, 400, 4, 200.0, 1e-3, inc)
+
+
+@pytest.mark.parametrize("scale", [2**10, 2**16, 2**20])
+@pytest.mark.parametrize("dtype", [1, 2, 4])
+def test_common_factors(api, scale, dtype):
+    """Large common factors: few or no fraction bits, or another kernel."""
+    Q = instances.ising_to_qubo(instances.sk_bimodal(100, 5))[0] * scale
+    _check(api, Q, dtype, 3, 600, 8, 30.0 * scale, 0.1 * scale, scale)
+    _check(api, Q, dtype, 3, 300, 8, 30.0, 0.1, 1)    # T far below a coupling
+
+
+def test_resume(api):
+    """Pieces that cut levels and groups of steps equal the whole run."""
+    for N in (50, 100, 220, 480):
+        Q, T_hi, T_lo, inc = _instance("sk", N)
+        ctx = api.da_create(Q)
+        sch = api.schedule(T_hi, T_lo, "geometric", 9, eoff_inc=inc)
+        whole = api.da_anneal(ctx, sch, 5, 1000, 3)
+        c2 = api.da_create(Q)
+        for a, b in [(0, 1), (1, 67), (67, 555), (555, 998), (998, 1000)]:
+            part = api.da_anneal_steps(c2, sch, 0, 5, 1000, a, b, 3)
+        for k in KEYS:
+            assert np.array_equal(part[k], whole[k]), (N, k)
