@@ -50,9 +50,7 @@ int check_hip(da_ctx *ctx, hipError_t e, const char *what) {
 }
 
 void StateBuf::release() {
-    for (void *p : {(void *)h, (void *)x, (void *)bx, (void *)E, (void *)bE, (void *)eoff,
-                    (void *)nacc})
-        if (p) (void)hipFree(p);
+    if (h) (void)hipFree(h);   // the start of the one allocation
     h = nullptr; x = bx = nullptr; E = bE = nacc = nullptr; eoff = nullptr;
     cap = 0;
 }
@@ -68,15 +66,19 @@ bool StateBuf::ensure(int32_t R, int32_t ld_, std::string &err) {
     release();
     ld = ld_;
     const int32_t n = std::max(R, 1);
-    const size_t rows = (size_t)n * ld;
-    if (hipMalloc(&h, rows * 4) != hipSuccess || hipMalloc(&x, rows) != hipSuccess ||
-        hipMalloc(&bx, rows) != hipSuccess || hipMalloc(&E, (size_t)n * 8) != hipSuccess ||
-        hipMalloc(&bE, (size_t)n * 8) != hipSuccess || hipMalloc(&eoff, (size_t)n * 4) != hipSuccess ||
-        hipMalloc(&nacc, (size_t)n * 8) != hipSuccess) {
-        release();
+    const size_t rows = (size_t)n * ld;   // (ld: a multiple of 64, so all parts are aligned)
+    char *p = nullptr;
+    if (hipMalloc(&p, (size_t)bytes_for(n, ld)) != hipSuccess) {
         err = "out of device memory for replica state";
         return false;
     }
+    h = reinterpret_cast<int32_t *>(p);
+    x = reinterpret_cast<uint8_t *>(h + rows);
+    bx = x + rows;
+    E = reinterpret_cast<int64_t *>(bx + rows);
+    bE = E + n;
+    nacc = bE + n;
+    eoff = reinterpret_cast<int32_t *>(nacc + n);
     cap = n;
     return true;
 }
@@ -873,6 +875,95 @@ int next_events(da_ctx *ctx, hipEvent_t &e0, hipEvent_t &e1) {
     return DA_OK;
 }
 
+namespace {
+// Pinned blocks that small outputs pass through: at most kBlocks per process,
+// allocated when first needed, each with one call at a time, kept until the
+// process ends.  A call that finds none free copies to the caller's memory.
+class PinnedBlocks {
+  public:
+    static constexpr size_t kBytes = size_t(1) << 20;
+    static constexpr int kBlocks = 8;
+    void *take() {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!free_.empty()) {
+            void *p = free_.back();
+            free_.pop_back();
+            return p;
+        }
+        void *p = nullptr;
+        if (made_ == kBlocks || hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess)
+            return nullptr;
+        ++made_;
+        return p;
+    }
+    void give(void *p) {
+        std::lock_guard<std::mutex> lock(mu_);
+        free_.push_back(p);
+    }
+
+  private:
+    std::mutex mu_;
+    std::vector<void *> free_;
+    int made_ = 0;
+};
+PinnedBlocks &pinned_blocks() {
+    static PinnedBlocks *p = new PinnedBlocks();   // (no frees at exit)
+    return *p;
+}
+
+// Outputs to the caller's memory.  A kernel writes them densely, up to 1 MiB
+// into a pinned block itself (one launch and one wait), more into a device
+// buffer of the context that contiguous copies leave from: strided copies to
+// pageable memory go row by row (2048 rows of 1024 bytes took 26 ms).
+}  // namespace
+
+// Outputs to the caller's memory.  A kernel writes them densely, up to 1 MiB
+// into a pinned block itself (one launch and one wait), more into a device
+// buffer of the context that contiguous copies leave from: strided copies to
+// pageable memory go row by row (2048 rows of 1024 bytes took 26 ms).
+int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o,
+                         hipStream_t s) {
+    const size_t nE = (size_t)R * 8, nx = (size_t)R * (size_t)J.N;
+    const size_t bytes = 3 * nE + 2 * nx;
+    JobDesc K = J;
+    K.R = R;
+    auto parts = [&](void *at) {   // [3][R] energies and counts, then [2][R][N] states
+        char *p = static_cast<char *>(at);
+        da_result d{};
+        d.best_E = o->best_E ? reinterpret_cast<int64_t *>(p) : nullptr;
+        d.final_E = o->final_E ? reinterpret_cast<int64_t *>(p + nE) : nullptr;
+        d.n_accept = o->n_accept ? reinterpret_cast<int64_t *>(p + 2 * nE) : nullptr;
+        d.best_x = o->best_x ? reinterpret_cast<uint8_t *>(p + 3 * nE) : nullptr;
+        d.final_x = o->final_x ? reinterpret_cast<uint8_t *>(p + 3 * nE + nx) : nullptr;
+        return d;
+    };
+    void *pin = bytes <= PinnedBlocks::kBytes ? pinned_blocks().take() : nullptr;
+    if (!pin && bytes > ctx->out_cap) {
+        if (ctx->d_out) (void)hipFree(ctx->d_out);
+        ctx->d_out = nullptr;
+        ctx->out_cap = 0;
+        const int rc = check_hip(ctx, hipMalloc(&ctx->d_out, bytes), "output buffer allocation");
+        if (rc) return rc;
+        ctx->out_cap = bytes;
+    }
+    const da_result d = parts(pin ? pin : ctx->d_out);
+    hipError_t e = (hipError_t)launch_outputs(K, d, s);
+    if (pin && e == hipSuccess) e = hipStreamSynchronize(s);
+    auto copy = [&](void *dst, const void *src, size_t n) {
+        if (!dst || e != hipSuccess) return;
+        if (pin) std::memcpy(dst, src, n);
+        else e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
+    };
+    copy(o->best_E, d.best_E, nE);
+    copy(o->final_E, d.final_E, nE);
+    copy(o->n_accept, d.n_accept, nE);
+    copy(o->best_x, d.best_x, nx);
+    copy(o->final_x, d.final_x, nx);
+    if (pin) pinned_blocks().give(pin);
+    else if (e == hipSuccess) e = hipStreamSynchronize(s);
+    return check_hip(ctx, e, "copy of outputs to host");
+}
+
 }  // namespace dapt
 
 namespace {
@@ -905,31 +996,9 @@ hipStream_t ctx_stream(da_ctx *ctx, void *stream) {
 
 // Copy-out of one anneal's outputs from the context state into device buffers.
 int extract_outputs(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o, hipStream_t s) {
-    int e = 0;
-    if (o->best_x && !e) e = launch_extract(J, J.bx, o->best_x, R, s);
-    if (o->final_x && !e) e = launch_extract(J, J.x, o->final_x, R, s);
-    if (o->best_E && !e) e = launch_copy_i64(J.bE, o->best_E, R, s);
-    if (o->final_E && !e) e = launch_copy_i64(J.E, o->final_E, R, s);
-    if (o->n_accept && !e) e = launch_copy_i64(J.nacc, o->n_accept, R, s);
-    return check_hip(ctx, (hipError_t)e, "output extraction launch");
-}
-
-int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o,
-                         hipStream_t s) {
-    hipError_t e = hipSuccess;
-    const size_t N = (size_t)J.N, ld = (size_t)J.ld;
-    if (o->best_x && e == hipSuccess)
-        e = hipMemcpy2DAsync(o->best_x, N, J.bx, ld, N, (size_t)R, hipMemcpyDeviceToHost, s);
-    if (o->final_x && e == hipSuccess)
-        e = hipMemcpy2DAsync(o->final_x, N, J.x, ld, N, (size_t)R, hipMemcpyDeviceToHost, s);
-    if (o->best_E && e == hipSuccess)
-        e = hipMemcpyAsync(o->best_E, J.bE, (size_t)R * 8, hipMemcpyDeviceToHost, s);
-    if (o->final_E && e == hipSuccess)
-        e = hipMemcpyAsync(o->final_E, J.E, (size_t)R * 8, hipMemcpyDeviceToHost, s);
-    if (o->n_accept && e == hipSuccess)
-        e = hipMemcpyAsync(o->n_accept, J.nacc, (size_t)R * 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    return check_hip(ctx, e, "copy of outputs to host");
+    JobDesc K = J;
+    K.R = R;
+    return check_hip(ctx, (hipError_t)launch_outputs(K, *o, s), "output extraction launch");
 }
 
 void record_stats(da_ctx *ctx, const LaunchShape &sh, int64_t launches, int gth = 0) {
@@ -1152,9 +1221,9 @@ void da_destroy(da_ctx *ctx) {
     if (ctx->d_W) (void)hipFree(ctx->d_W);
     if (ctx->d_b) (void)hipFree(ctx->d_b);
     if (ctx->d_ell) (void)hipFree(ctx->d_ell);
+    if (ctx->d_out) (void)hipFree(ctx->d_out);
     for (void *p : {(void *)ctx->pt_slot2rep, (void *)ctx->pt_lvl, (void *)ctx->pt_swaps,
-                    (void *)ctx->pt_pair, (void *)ctx->pt_round, (void *)ctx->pt_dbeta,
-                    (void *)ctx->pt_lnU})
+                    (void *)ctx->pt_pair, (void *)ctx->pt_round, (void *)ctx->pt_dbeta})
         if (p) (void)hipFree(p);
     for (auto &pr : ctx->ev_pool) {
         (void)hipEventDestroy(pr.first);
@@ -1453,12 +1522,13 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     JobTables jt;
     if (wave) {
         jt.temps = get_temp_list(tv, err);
-        jt.G = device_neg_log_u(err);
-        if (!jt.temps || !jt.G || !device_bound_error(jt.gerr, err)) return fail(ctx, DA_ENOMEM, err);
+        if (!jt.temps || !device_bound_error(jt.gerr, err)) return fail(ctx, DA_ENOMEM, err);
     } else {
         jt.levels = get_level_tables(tv, err);
         if (!jt.levels) return fail(ctx, DA_ENOMEM, err);
     }
+    jt.G = device_neg_log_u(err);
+    if (!jt.G) return fail(ctx, DA_ENOMEM, err);
     const LevelTables *lt = jt.levels.get();
     ctx->keep_tables = jt.levels;
     ctx->keep_temps = jt.temps;
@@ -1469,13 +1539,12 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     if (R > ctx->pt_cap_R || M > ctx->pt_cap_M || chains > ctx->pt_cap_chains ||
         npair > ctx->pt_cap_pairs) {
         for (void *p : {(void *)ctx->pt_slot2rep, (void *)ctx->pt_lvl, (void *)ctx->pt_swaps,
-                        (void *)ctx->pt_pair, (void *)ctx->pt_round, (void *)ctx->pt_dbeta,
-                        (void *)ctx->pt_lnU})
+                        (void *)ctx->pt_pair, (void *)ctx->pt_round, (void *)ctx->pt_dbeta})
             if (p) (void)hipFree(p);
         ctx->pt_slot2rep = ctx->pt_lvl = nullptr;
         ctx->pt_swaps = ctx->pt_pair = nullptr;
         ctx->pt_round = nullptr;
-        ctx->pt_dbeta = ctx->pt_lnU = nullptr;
+        ctx->pt_dbeta = nullptr;
         ctx->pt_cap_R = ctx->pt_cap_M = ctx->pt_cap_chains = ctx->pt_cap_pairs = 0;
         rc = check_hip(ctx, hipMalloc(&ctx->pt_slot2rep, (size_t)R * 4), "PT allocation");
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_lvl, (size_t)R * 4), "PT allocation");
@@ -1483,19 +1552,16 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_pair, (size_t)npair * 8), "PT allocation");
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_round, 8), "PT allocation");
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_dbeta, (size_t)M * 8), "PT allocation");
-        if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_lnU, 65536 * 8), "PT allocation");
         if (rc) return rc;
         ctx->pt_cap_R = R;
         ctx->pt_cap_M = M;
         ctx->pt_cap_chains = chains;
         ctx->pt_cap_pairs = npair;
     }
-    // exchange tables: 1/T_p - 1/T_{p+1} and ln U_u, U_u = (u + 1/2)/65536
-    std::vector<double> dbeta((size_t)M, 0.0), lnU(65536);
+    // exchange tables: 1/T_p - 1/T_{p+1}, and -ln U_u
+    std::vector<double> dbeta((size_t)M, 0.0);
     for (int p = 0; p + 1 < M; ++p) dbeta[(size_t)p] = 1.0 / temps[p] - 1.0 / temps[p + 1];
-    for (int u = 0; u < 65536; ++u) lnU[(size_t)u] = std::log(((double)u + 0.5) / 65536.0);
     rc = check_hip(ctx, hipMemcpyAsync(ctx->pt_dbeta, dbeta.data(), (size_t)M * 8, hipMemcpyHostToDevice, s), "PT upload");
-    if (!rc) rc = check_hip(ctx, hipMemcpyAsync(ctx->pt_lnU, lnU.data(), 65536 * 8, hipMemcpyHostToDevice, s), "PT upload");
     if (rc) return rc;
 
     da_schedule sched{temps[0], temps[0], DA_SCHED_GEOMETRIC, 1, eoff_inc, DA_INIT_RANDOM,
@@ -1541,7 +1607,7 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
             e = wave ? launch_wave(J, sh.F, sh.blocks, sh.threads, sh.lds, s)
                      : launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks, sh.threads, sh.lds, s);
         if (!e)
-            e = launch_pt_exchange(J.E, ctx->pt_slot2rep, ctx->pt_lvl, ctx->pt_dbeta, ctx->pt_lnU,
+            e = launch_pt_exchange(J.E, ctx->pt_slot2rep, ctx->pt_lvl, ctx->pt_dbeta, jt.G,
                                    M, chains, seed, ctx->pt_round, ctx->pt_swaps, ctx->pt_pair, s);
         return e;
     };

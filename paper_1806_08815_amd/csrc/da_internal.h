@@ -16,6 +16,8 @@
 
 #include <cstdint>
 
+#include "da.h"
+
 namespace dapt {
 
 // The band of a level: with thr non-increasing in u, every d <= tmin = thr[65535]
@@ -209,15 +211,14 @@ int launch_batch(const JobDesc *jobs_dev, const BatchItem *items_dev, const int3
 // points to two words: the round index and a count of the workgroups that
 // have read it.  pair_swaps [chains][M-1] counts accepted exchanges per pair.
 int launch_pt_exchange(int64_t *E, int32_t *slot2rep, int32_t *lvl_of_rep, const double *dbeta,
-                       const double *lnU, int32_t M, int32_t chains, uint64_t seed,
+                       const double *G, int32_t M, int32_t chains, uint64_t seed,
                        uint32_t *round_ptr, int64_t *n_swaps, int64_t *pair_swaps,
                        void *stream);
 int launch_pt_setup(int32_t *slot2rep, int32_t *lvl_of_rep, int64_t *n_swaps,
                     int64_t *pair_swaps, uint32_t *round_ptr, int32_t M, int32_t chains,
                     void *stream);
-int launch_extract(const JobDesc &J, const uint8_t *src_x, uint8_t *dst_x, int32_t R,
-                   void *stream);
-int launch_copy_i64(const int64_t *src, int64_t *dst, int32_t n, void *stream);
+// Outputs of a run into device (or pinned host) buffers, dense; null: not wanted.
+int launch_outputs(const JobDesc &J, const da_result &o, void *stream);
 int launch_fill_i32(int32_t *dst, int32_t value, int64_t n, void *stream);
 
 // Dynamic LDS a workgroup may use on the current device (bytes).

@@ -1211,7 +1211,7 @@ constexpr int kPtMaxM = 4096;
 __global__ __launch_bounds__(64) void k_pt_exchange(const int64_t *__restrict__ E,
                                                     int32_t *slot2rep, int32_t *lvl_of_rep,
                                                     const double *__restrict__ dbeta,
-                                                    const double *__restrict__ lnU, int32_t M,
+                                                    const double *__restrict__ G, int32_t M,
                                                     int32_t chains, uint64_t seed,
                                                     uint32_t *round, int64_t *n_swaps,
                                                     int64_t *pair_swaps) {
@@ -1240,7 +1240,7 @@ __global__ __launch_bounds__(64) void k_pt_exchange(const int64_t *__restrict__ 
         if (p + 1 < M) {
             const uint32_t u =
                 philox((uint32_t)p, t, (uint32_t)c, kTagExchange, k0, k1).x & 0xFFFFu;
-            lnu[p] = lnU[u];
+            lnu[p] = -G[u];
         }
     }
     __syncthreads();
@@ -1286,20 +1286,23 @@ __global__ void k_pt_setup(int32_t *slot2rep, int32_t *lvl_of_rep, int64_t *n_sw
     }
 }
 
-// Copy [R][ld] state rows to dense [R][N] output rows.
-__global__ void k_extract(const uint8_t *__restrict__ src, uint8_t *__restrict__ dst, int32_t R,
-                          int32_t N, int32_t ld) {
-    const int64_t n = (int64_t)R * N;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = q / N, i = q - r * N;
-        dst[q] = src[r * ld + i];
+// All outputs of a run in one launch: state rows [R][ld] to dense rows [R][N],
+// energies and counts, as far as asked for (null: not).
+__global__ void k_outputs(JobDesc J, da_result o) {
+    const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r = tid; r < J.R; r += step) {
+        if (o.best_E) o.best_E[r] = J.bE[r];
+        if (o.final_E) o.final_E[r] = J.E[r];
+        if (o.n_accept) o.n_accept[r] = J.nacc[r];
     }
-}
-
-__global__ void k_copy_i64(const int64_t *__restrict__ src, int64_t *__restrict__ dst, int32_t n) {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x)
-        dst[q] = src[q];
+    if (!o.best_x && !o.final_x) return;
+    const int64_t n = (int64_t)J.R * J.N;
+    for (int64_t q = tid; q < n; q += step) {
+        const int64_t r = q / J.N, i = q - r * J.N;
+        if (o.best_x) o.best_x[q] = J.bx[r * J.ld + i];
+        if (o.final_x) o.final_x[q] = J.x[r * J.ld + i];
+    }
 }
 
 __global__ void k_fill_i32(int32_t *dst, int32_t value, int64_t n) {
@@ -1601,12 +1604,12 @@ int launch_finish_start(const JobDesc &J, void *stream) {
 }
 
 int launch_pt_exchange(int64_t *E, int32_t *slot2rep, int32_t *lvl_of_rep, const double *dbeta,
-                       const double *lnU, int32_t M, int32_t chains, uint64_t seed,
+                       const double *G, int32_t M, int32_t chains, uint64_t seed,
                        uint32_t *round_ptr, int64_t *n_swaps, int64_t *pair_swaps,
                        void *stream) {
     if (M < 1 || M > kPtMaxM || chains < 1) return (int)hipErrorInvalidValue;
     hipLaunchKernelGGL(k_pt_exchange, dim3(chains), dim3(64), 0, S(stream), E, slot2rep,
-                       lvl_of_rep, dbeta, lnU, M, chains, seed, round_ptr, n_swaps, pair_swaps);
+                       lvl_of_rep, dbeta, G, M, chains, seed, round_ptr, n_swaps, pair_swaps);
     return (int)hipGetLastError();
 }
 
@@ -1619,15 +1622,9 @@ int launch_pt_setup(int32_t *slot2rep, int32_t *lvl_of_rep, int64_t *n_swaps,
     return (int)hipGetLastError();
 }
 
-int launch_extract(const JobDesc &J, const uint8_t *src_x, uint8_t *dst_x, int32_t R,
-                   void *stream) {
-    hipLaunchKernelGGL(k_extract, dim3(grid_for((int64_t)R * J.N, 256)), dim3(256), 0, S(stream),
-                       src_x, dst_x, R, J.N, J.ld);
-    return (int)hipGetLastError();
-}
-
-int launch_copy_i64(const int64_t *src, int64_t *dst, int32_t n, void *stream) {
-    hipLaunchKernelGGL(k_copy_i64, dim3(grid_for(n, 256)), dim3(256), 0, S(stream), src, dst, n);
+int launch_outputs(const JobDesc &J, const da_result &o, void *stream) {
+    hipLaunchKernelGGL(k_outputs, dim3(grid_for((int64_t)J.R * J.N, 256)), dim3(256), 0, S(stream),
+                       J, o);
     return (int)hipGetLastError();
 }
 

@@ -202,11 +202,13 @@ struct da_ctx {
     int64_t *pt_swaps = nullptr;
     int64_t *pt_pair = nullptr;      // accepted exchanges [chains][M-1]
     uint32_t *pt_round = nullptr;    // [2]: round index, workgroups that read it
-    double *pt_dbeta = nullptr, *pt_lnU = nullptr;
+    double *pt_dbeta = nullptr;
     int32_t pt_cap_R = 0, pt_cap_M = 0, pt_cap_chains = 0, pt_cap_pairs = 0;
     std::shared_ptr<dapt::LevelTables> keep_tables;
     std::shared_ptr<dapt::StepTables> keep_steps;
     std::shared_ptr<dapt::TempList> keep_temps;
+    int64_t *d_out = nullptr;    // outputs on their way to the host, dense
+    size_t out_cap = 0;          // its bytes
     // what the replica state in `st` holds: replicas st_base .. st_base+st_R-1
     // after st_step steps (st_step < 0: nothing resumable)
     int64_t st_step = -1;
@@ -240,6 +242,9 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t r
 // The instance alone (W, b, sizes), for the energy kernels.
 JobDesc matrix_job(const da_ctx *ctx);
 int init_state(da_ctx *ctx, const JobDesc &J, int init, hipStream_t stream);
+// Outputs of a run (dense, null: not wanted) into the caller's memory; waits.
+int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o,
+                         hipStream_t s);
 // Event pair for the next timed call (from the context's pool).
 int next_events(da_ctx *ctx, hipEvent_t &e0, hipEvent_t &e1);
 std::vector<double> schedule_temps(const da_schedule &s);

@@ -333,27 +333,18 @@ bool da_server::admit_locked(std::vector<Job *> &admitted) {
 void da_server::retire(std::unique_ptr<Job> &jp) {
     Job &j = *jp;
     if (j.status == DA_OK && j.ctx) {
-        const size_t R = (size_t)j.spec.replicas, N = (size_t)j.spec.N, ld = (size_t)j.J.ld;
+        const size_t R = (size_t)j.spec.replicas, N = (size_t)j.spec.N;
         j.best_x.resize(R * N);
         j.final_x.resize(R * N);
         j.best_E.resize(R);
         j.final_E.resize(R);
         j.n_accept.resize(R);
-        hipError_t e = hipMemcpy2DAsync(j.best_x.data(), N, j.J.bx, ld, N, R,
-                                        hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess)
-            e = hipMemcpy2DAsync(j.final_x.data(), N, j.J.x, ld, N, R, hipMemcpyDeviceToHost,
-                                 stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(j.best_E.data(), j.J.bE, R * 8, hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(j.final_E.data(), j.J.E, R * 8, hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(j.n_accept.data(), j.J.nacc, R * 8, hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) {
-            j.status = DA_EDEVICE;
-            j.err = hipGetErrorString(e);
+        const da_result o{j.best_x.data(), j.best_E.data(), j.final_x.data(), j.final_E.data(),
+                          j.n_accept.data()};
+        const int rc = copy_outputs_to_host(j.ctx, j.J, (int32_t)R, &o, stream);
+        if (rc) {
+            j.status = rc;
+            j.err = j.ctx->err;
         }
     }
     if (j.ctx) da_destroy(j.ctx);
