@@ -251,7 +251,7 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t r
 }
 
 bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh) {
-    if (ctx->N > 1024 || ctx->ell_D > 0) return false;
+    if (ctx->ell_D > 0) return false;
     const int64_t ws = std::abs((int64_t)ctx->wscale), hb = ctx->hbound + 1;
     // the field update's factor: 16 bits for 16-bit couplings, else 24
     sh.w24 = ctx->dtype < 4 || (ctx->hbound / ws < (1 << 23) && ws < (1 << 23)) ? 1 : 0;
@@ -270,20 +270,43 @@ bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, Launch
     sh.wclamp = T_max >= 262144.0 || T_min * (double)(1 << q) < 16384.0 ? 1 : 0;
     sh.ecap = (int)hb;
     sh.wave = true;
-    sh.F = ctx->N <= 64 ? 1 : ctx->N <= 128 ? 2 : ctx->N <= 256 ? 4 : ctx->N <= 512 ? 8 : 16;
-    sh.NW = 1;
-    sh.NH = 0;
-    sh.direct = sh.gen = 0;
-    // a wave per SIMD before two on one; W in LDS where a workgroup's share of
-    // the replicas leaves it room (shared by all of them), read there at a
-    // quarter of the latency
-    const int64_t w_bytes = (int64_t)ctx->N * ctx->ld * ctx->dtype;
+    // Up to 512 variables one wave.  Beyond, with few replicas on a compute unit,
+    // a team of 8 flips per lane whose random-number waves keep the draws off the
+    // step's chain; they draw two blocks a lane while that leaves them off it, one
+    // where replicas share the unit, and are left out where it is full; 16 flips
+    // per lane, the fewest instructions per step, where it is, or past 16 waves.
+    // ns per step measured at N = 1024 and 1, 2, 3, 4 replicas per unit: two
+    // blocks 500, 575, 701, 780, one block 517, 582, 595, 663, one wave of 16
+    // flips 637, 661, -, 646; N = 2048: two blocks 649, 956, 1281, 1630, one block
+    // 668, 772, 1016, 1451, none 721, 937, 1182, 1433; N = 4096: 8 flips and two
+    // blocks 830, 1367, 2042, 16 flips and two blocks 870, 1295, 1968, none 1050,
+    // 1466, 1939; N = 8192: 16 flips and two blocks 1226, 2311, none 1447, 2302.
+    const int N = ctx->N;
     const int per_cu = (R + ctx->cus - 1) / ctx->cus;
-    sh.w_lds = sh.F < 16 && w_bytes + 16384 <= (int64_t)device_lds_limit() ? 1 : 0;
-    sh.RPW = sh.w_lds ? std::min(per_cu, 16) : std::min(per_cu, 4);
-    sh.threads = 64 * sh.RPW;
+    int HB = 0;   // Philox blocks per lane of a random-number wave
+    if (N <= 512) {
+        sh.F = N <= 64 ? 1 : N <= 128 ? 2 : N <= 256 ? 4 : 8;
+    } else if (N <= 1024) {
+        sh.F = per_cu <= 3 ? 8 : 16;
+        HB = per_cu <= 2 ? 2 : per_cu <= 3 ? 1 : 0;
+    } else if (N <= 2048) {
+        sh.F = per_cu <= 4 ? 8 : 16;
+        HB = per_cu <= 1 ? 2 : per_cu <= 4 ? 1 : 0;
+    } else {
+        sh.F = N <= 4096 && per_cu <= 1 ? 8 : 16;
+        HB = per_cu <= (N <= 4096 ? 2 : 1) ? 2 : 0;
+    }
+    sh.NW = (N + 64 * sh.F - 1) / (64 * sh.F);
+    sh.NH = HB > 0 ? (N + 512 * HB - 1) / (512 * HB) : 0;
+    sh.direct = sh.gen = 0;
+    // One wave: W in LDS where a workgroup's share of the replicas leaves it room
+    // (shared by all of them), read there at a quarter of the latency
+    const int64_t w_bytes = (int64_t)N * ctx->ld * ctx->dtype;
+    sh.w_lds = N <= 512 && w_bytes + 32768 <= (int64_t)device_lds_limit() ? 1 : 0;
+    sh.RPW = sh.NW > 1 ? 1 : sh.w_lds ? std::min(per_cu, 16) : std::min(per_cu, 4);
+    sh.threads = 64 * sh.RPW * (sh.NW + sh.NH);
     sh.blocks = (R + sh.RPW - 1) / sh.RPW;
-    sh.lds = wave_lds_bytes(sh.F, sh.RPW, sh.w_lds ? w_bytes : 0);
+    sh.lds = wave_lds_bytes(sh.F, ctx->N, sh.NW, sh.NH, sh.RPW, sh.w_lds ? w_bytes : 0);
     return true;
 }
 
@@ -658,8 +681,11 @@ std::shared_ptr<TempList> get_temp_list(const std::vector<double> &temps, std::s
     }
     auto tl = std::make_shared<TempList>();
     const size_t bytes = temps.size() * sizeof(double);
+    // (T = 0 schedules give 0 x NaN past their first level)
+    std::vector<double> pos(temps);
+    for (double &T : pos) T = T > 0.0 ? T : 0.0;
     if (hipMalloc(&tl->d_temps, bytes) != hipSuccess ||
-        hipMemcpy(tl->d_temps, temps.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+        hipMemcpy(tl->d_temps, pos.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
         err = "temperature list allocation or upload failed";
         return nullptr;
     }
@@ -705,13 +731,13 @@ bool device_bound_error(float &gerr, std::string &err) {
 namespace {
 struct TuneKey {
     int dev, N, dtype, rbucket;
-    int long_levels;   // long enough for direct tables: other shapes win there
+    int direct;
     bool operator<(const TuneKey &o) const {
         if (dev != o.dev) return dev < o.dev;
         if (N != o.N) return N < o.N;
         if (dtype != o.dtype) return dtype < o.dtype;
         if (rbucket != o.rbucket) return rbucket < o.rbucket;
-        return long_levels < o.long_levels;
+        return direct < o.direct;
     }
 };
 std::mutex g_tune_mu;
@@ -725,42 +751,22 @@ bool tune_enabled() {
 
 // Direct tables pay for their staging (64 KiB per level and workgroup) only
 // when levels last a few hundred steps.
-static bool long_levels(const da_schedule &sched, int64_t steps) {
-    return sched.n_levels > 0 && steps >= 256 * (int64_t)sched.n_levels;
-}
 static bool want_direct(const LevelTables &lt, const da_schedule &sched, int64_t steps) {
-    return lt.d_q8 != nullptr && long_levels(sched, steps);
-}
-
-// flips_per_lane of the one-wave kernel in the tuner's cache
-static constexpr int kTuneWave = 16;
-
-static TuneKey tune_key(const da_ctx *ctx, int32_t R, const da_schedule &sched, int64_t steps) {
-    int rb = 1;
-    while (rb < R) rb <<= 1;
-    return TuneKey{ctx->device, ctx->N, ctx->dtype, rb, long_levels(sched, steps) ? 1 : 0};
-}
-
-// Whether the tuner has chosen the one-wave kernel for this size.
-static bool tuned_to_wave(const da_ctx *ctx, int32_t R, const da_schedule &sched, int64_t steps) {
-    std::lock_guard<std::mutex> lock(g_tune_mu);
-    auto it = g_tune.find(tune_key(ctx, R, sched, steps));
-    return it != g_tune.end() && it->second.flips_per_lane == kTuneWave;
+    return lt.d_q8 != nullptr && sched.n_levels > 0 && steps >= 256 * (int64_t)sched.n_levels;
 }
 
 int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
-                const da_schedule &sched, hipStream_t s, bool may_time, const LaunchShape *wave,
-                const JobDesc *wave_job, LaunchShape &out) {
+                const da_schedule &sched, hipStream_t s, bool may_time, LaunchShape &out) {
     const bool direct = want_direct(lt, sched, steps);
-    int rc = DA_OK;
-    const TuneKey key = tune_key(ctx, R, sched, steps);
+    int rc = DA_OK, rb = 1;
+    while (rb < R) rb <<= 1;
+    // (long levels have direct tables, and other shapes win there)
+    const TuneKey key{ctx->device, ctx->N, ctx->dtype, rb, direct ? 1 : 0};
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         auto it = g_tune.find(key);
         if (it != g_tune.end()) {
-            // (a size tuned to the one-wave kernel whose instance it does not take)
-            out = choose_shape(ctx, R, it->second.flips_per_lane == kTuneWave ? nullptr : &it->second,
-                               true, direct);
+            out = choose_shape(ctx, R, &it->second, true, direct);
             return DA_OK;
         }
     }
@@ -787,10 +793,8 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
         if (!rc) rc = check_hip(ctx, hipEventRecord(a, s), what);
         if (!rc)
             rc = check_hip(ctx,
-                           (hipError_t)(sh.wave
-                                            ? launch_wave(J, sh.F, sh.blocks, sh.threads, sh.lds, s)
-                                            : launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks,
-                                                         sh.threads, sh.lds, s)),
+                           (hipError_t)launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks,
+                                                  sh.threads, sh.lds, s),
                            what);
         if (!rc) rc = check_hip(ctx, hipEventRecord(b, s), what);
         if (!rc) rc = check_hip(ctx, hipEventSynchronize(b), what);
@@ -831,9 +835,6 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
             }
         }
     }
-    if (wave && !rc)
-        time_candidate(*wave_job, *wave, da_launch{kTuneWave, 0, 0, 0, 0},
-                       "autotuner candidate (one wave per replica)");
     if (a) (void)hipEventDestroy(a);
     if (b) (void)hipEventDestroy(b);
     if (rc) return rc;
@@ -842,7 +843,7 @@ int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
         std::lock_guard<std::mutex> lock(g_tune_mu);
         g_tune[key] = best;
     }
-    out = best.flips_per_lane == kTuneWave ? *wave : choose_shape(ctx, R, &best, true, direct);
+    out = choose_shape(ctx, R, &best, true, direct);
     return DA_OK;
 }
 
@@ -1096,21 +1097,12 @@ int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_bas
     if (step_begin > 0 && (ctx->st_step != step_begin || ctx->st_base != replica_base ||
                            ctx->st_R < replicas))
         return fail(ctx, DA_EINVAL, "the context holds no state of these replicas at step_begin");
-    // One wave per replica: always up to 512 variables (measured faster there at
-    // every replica count: 204 ns a step at N = 64 against 668, 436 at N = 512
-    // against about 600) and for a new temperature every step (no gather of ln U
-    // per flip), else where the tuner finds it faster
     JobTables jt;
     LaunchShape sh;
     const bool own = launch == nullptr && trace_dev == nullptr;
-    const bool tune = own && tune_enabled() && schedule->n_levels > 0;
-    LaunchShape wsh;
-    const bool wave_ok = own && wave_shape(ctx, replicas, std::min(schedule->T_hi, schedule->T_lo),
-                                           std::max(schedule->T_hi, schedule->T_lo), wsh);
-    bool wave = wave_ok && (ctx->N <= 512 || schedule->n_levels == 0 ||
-                            (tune && tuned_to_wave(ctx, replicas, *schedule, steps)));
-    if (!wave) rc = job_tables(*schedule, steps, jt, err);
-    if (!rc && (wave || (wave_ok && tune))) rc = wave_tables(*schedule, steps, jt, err);
+    const bool wave = own && wave_shape(ctx, replicas, std::min(schedule->T_hi, schedule->T_lo),
+                                        std::max(schedule->T_hi, schedule->T_lo), sh);
+    rc = wave ? wave_tables(*schedule, steps, jt, err) : job_tables(*schedule, steps, jt, err);
     if (rc) return fail(ctx, rc, err);
     ctx->keep_tables = jt.levels;
     ctx->keep_steps = jt.steps;
@@ -1121,33 +1113,18 @@ int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_bas
     // the tuner times its candidates on the replica state, so only when the
     // run starts from the initial state (which is written after it); a resumed
     // piece takes the cached choice or the default
-    auto wave_job = [&]() {
-        JobDesc W = make_job(ctx, nullptr, replicas, (uint32_t)replica_base, seed, steps, *schedule,
-                             wsh);
-        attach_step_tables(W, jt);
-        if (jt.temps) W.L = std::max(schedule->n_levels, 1);
-        return W;
-    };
-    if (wave) {
-        sh = wsh;
-    } else if (tune) {
-        JobDesc W;
-        if (wave_ok) W = wave_job();
-        rc = tuned_shape(ctx, *jt.levels, replicas, steps, *schedule, s, step_begin == 0,
-                         wave_ok ? &wsh : nullptr, &W, sh);
-        if (rc) return rc;
-        wave = sh.wave;
-    } else {
-        sh = choose_shape(ctx, replicas, launch, true,
-                          !jt.steps && want_direct(*jt.levels, *schedule, steps));
+    if (!wave) {
+        if (own && tune_enabled() && schedule->n_levels > 0) {
+            rc = tuned_shape(ctx, *jt.levels, replicas, steps, *schedule, s, step_begin == 0, sh);
+            if (rc) return rc;
+        } else {
+            sh = choose_shape(ctx, replicas, launch, true,
+                              !jt.steps && want_direct(*jt.levels, *schedule, steps));
+        }
     }
-    if (wave) {
-        J = wave_job();
-    } else {
-        J = make_job(ctx, jt.levels.get(), replicas, (uint32_t)replica_base, seed, steps, *schedule,
-                     sh);
-        attach_step_tables(J, jt);
-    }
+    J = make_job(ctx, jt.levels.get(), replicas, (uint32_t)replica_base, seed, steps, *schedule, sh);
+    attach_step_tables(J, jt);
+    if (jt.temps) J.L = std::max(schedule->n_levels, 1);
     J.s0 = step_begin;
     J.s1 = step_end;
     if (const char *why = job_range_error(J)) return fail(ctx, DA_EINVAL, why);
@@ -1512,13 +1489,8 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     const int32_t npair = chains * std::max(M - 1, 1);
     std::string err;
     std::vector<double> tv(temps, temps + M);
-    // One wave per replica up to 512 variables; beyond, where the chip is full
-    // or the costs too few units apart for the wider replicas' estimates
     LaunchShape sh;
-    const bool wave =
-        wave_shape(ctx, R, temps[0], temps[M - 1], sh) &&
-        (ctx->N <= 512 || R > 2 * ctx->cus ||
-         ctx->hbound < 4096 * (int64_t)std::abs(ctx->wscale));
+    const bool wave = wave_shape(ctx, R, temps[0], temps[M - 1], sh);
     JobTables jt;
     if (wave) {
         jt.temps = get_temp_list(tv, err);

@@ -194,9 +194,10 @@ int launch_energy(const JobDesc &J, int planes, const uint8_t *x, int32_t count,
 int launch_finish_start(const JobDesc &J, void *stream);
 int launch_run(const JobDesc &J, int F, bool help, const TraceDesc *trace, int blocks,
                int threads, size_t lds_bytes, void *stream);
-// The step kernel with one wave per replica (J.N <= 64 F), J.RPW replicas per
-// workgroup; wave_lds_bytes is what its workgroups need.
-size_t wave_lds_bytes(int F, int RPW, int64_t w_lds_bytes);
+// The step kernel with J.NW waves per replica (J.N <= 64 F J.NW): one wave, J.RPW
+// replicas per workgroup, or a team of waves per workgroup, with or without J.NH
+// random-number waves.  wave_lds_bytes is what its workgroups need.
+size_t wave_lds_bytes(int F, int N, int NW, int NH, int RPW, int64_t w_lds_bytes);
 int launch_wave(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream);
 // Largest error of the device's fp32 log2 over the arguments u + 1/2 of all draws.
 int launch_log_error(const double *G, float *out, void *stream);

@@ -226,17 +226,15 @@ int validate_schedule(const da_schedule *s, std::string &err);
 // direct: the schedule's tables include direct tables (staged when they fit)
 LaunchShape choose_shape(const da_ctx *ctx, int32_t R, const da_launch *launch,
                          bool anneal_mode, bool direct = false);
-// Shape of the one-wave kernel for replicas of this instance at temperatures
-// between T_min and T_max; false when it does not take them.
+// Shape of the wave and team kernels for replicas of this instance at temperatures
+// between T_min and T_max; false when they do not take them.
 bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh);
 // Fastest measured shape for this instance size, coupling type and replica
 // count, into `out`: timed once (when may_time) on the context's replica state,
 // which must hold R replicas and is left overwritten, then cached.  Returns
 // DA_OK, or the error of the first HIP call that failed (naming the candidate).
-// wave: the one-wave candidate and its job, or null.
 int tuned_shape(da_ctx *ctx, const LevelTables &lt, int32_t R, int64_t steps,
-                const da_schedule &sched, hipStream_t s, bool may_time, const LaunchShape *wave,
-                const JobDesc *wave_job, LaunchShape &out);
+                const da_schedule &sched, hipStream_t s, bool may_time, LaunchShape &out);
 JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t rid_base,
                  uint64_t seed, int64_t steps, const da_schedule &s, const LaunchShape &sh);
 // The instance alone (W, b, sizes), for the energy kernels.

@@ -253,7 +253,8 @@ std::shared_ptr<StepTables> get_step_tables(const da_schedule &s, int64_t S, std
     std::vector<StepT> host((size_t)S);
     for (int64_t q = 0; q < S; ++q) {
         const double T = schedule_temperature(lv, (int)q);
-        host[(size_t)q] = StepT{T, threshold_entry(T, 65535), threshold_entry(T, 0)};
+        // (T = 0 schedules give 0 x NaN past their first level)
+        host[(size_t)q] = StepT{T > 0.0 ? T : 0.0, threshold_entry(T, 65535), threshold_entry(T, 0)};
     }
     auto st = std::make_shared<StepTables>();
     st->S = S;

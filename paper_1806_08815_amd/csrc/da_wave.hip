@@ -32,7 +32,7 @@
 #include "da_internal.h"
 
 #ifndef DAPT_PART
-#error "compile with -DDAPT_PART=0 .. 3"
+#error "compile with -DDAPT_PART=0 .. 6"
 #endif
 
 namespace dapt {
@@ -105,7 +105,7 @@ struct DrawBlock {
 // never fall in between, which T' of a few units (couplings too large for more
 // fraction bits) would make common: where q >= 1, c0 = 1 is allowed, as d' <= 1
 // means d' <= 0 < y.  wt = 2 m + 2.
-// T = 0 accepts d' < 0 only: ga = 0, L = 0 and c0 = -1 state it exactly.
+// T = 0 accepts d' < 0 only: ga = 0 and L + c0 = -1 state it exactly.
 // The test uses z = L + c0 + E_off' - s' less one where x = 0 (s' = (1 - 2x) h',
 // its negative taken as a one's complement): z >= 0 accepts, z < -wt rejects.
 struct WaveLevel {
@@ -113,31 +113,39 @@ struct WaveLevel {
     uint32_t zamb;   // z is undecided iff (uint32_t)z > zamb
     int c0;          // with the constant of the sum's bits taken off
     int q;
-    double T;        // T 2^q
 };
 
 template <bool CLAMP>
 __device__ __forceinline__ WaveLevel wave_level(double T, int qcap, float gerr) {
     WaveLevel w;
-    const bool pos = T > 0.0;
-    // (T = f 2^e with f in [1/2, 1): T 2^q < 2^17)
-    const int e = pos ? __builtin_amdgcn_frexp_exp(T) : 16;
-    const int q = min(max(17 - e, 0), qcap);
-    const double Tq = pos ? __builtin_ldexp(T, q) : 0.0;
-    const float m = pos ? (float)Tq * gerr + 0.01f : 0.0f;
-    const int c0 = !pos ? -1 : (CLAMP && q > 0 ? 1 : 0);
-    const int wt = !pos ? (q > 0 ? 0 : 1) : (int)(2.0f * m) + (CLAMP ? 2 : 3);
+    const bool pos = __double_as_longlong(T) != 0;   // (T >= 0)
+    // (T = f 2^e with f in [1/2, 1), e = 0 for T = 0: T 2^q < 2^17 where q > 0)
+    const int q = min(max(17 - __builtin_amdgcn_frexp_exp(T), 0), qcap);
+    const double Tq = __builtin_ldexp(T, q);
+    const float m = (float)Tq * gerr + 0.01f;
+    const int c0 = !CLAMP ? 0 : (pos ? min(q, 1) : -1);
+    const int wt = pos ? (int)(2.0f * m) + (CLAMP ? 2 : 3) : 1 - min(q, 1);
     const double mid = Tq * (16.0 * kLn2);
     w.ga = (float)(-Tq * kLn2);
-    if constexpr (CLAMP)
-        w.gb = pos ? (float)(mid - (double)m - (double)c0) : 0.0f;
-    else
-        w.gb = pos ? (float)(12582912.0 + __builtin_floor(mid - (double)m - 0.5)) : 12582912.0f;
-    w.zamb = (uint32_t)__builtin_amdgcn_readfirstlane((int)(0xFFFFFFFFu - (uint32_t)wt));
-    w.c0 = __builtin_amdgcn_readfirstlane(CLAMP ? c0 : (int)((uint32_t)c0 - kGenMagic));
-    w.q = __builtin_amdgcn_readfirstlane(q);
-    w.T = Tq;
+    // (T = 0: L = 0 with c0 = -1, L = -1 with c0 = 0)
+    if constexpr (CLAMP) w.gb = (float)(mid - (double)m - (double)c0);
+    else w.gb = (float)(12582912.0 + __builtin_floor(mid - (double)m - 0.5));
+    w.zamb = 0xFFFFFFFFu - (uint32_t)wt;
+    w.c0 = CLAMP ? c0 : (int)((uint32_t)c0 - kGenMagic);
+    w.q = q;
     return w;
+}
+
+// The level that lane `l` holds, in scalar registers (ga, gb: for the bounds'
+// multiply-add, which takes one scalar, as they are).
+__device__ __forceinline__ WaveLevel level_at(const WaveLevel &w, int l) {
+    WaveLevel r;
+    r.ga = __int_as_float(readlane(__float_as_int(w.ga), l));
+    r.gb = __int_as_float(readlane(__float_as_int(w.gb), l));
+    r.zamb = (uint32_t)readlane((int)w.zamb, l);
+    r.c0 = readlane(w.c0, l);
+    r.q = readlane(w.q, l);
+    return r;
 }
 
 template <bool CLAMP>
@@ -193,19 +201,167 @@ __device__ __forceinline__ int first_bit(uint32_t m) {
     return r;
 }
 
-// Runs steps [s0, s1) of replica rr by one wave.  wl: W in LDS (WLDS); ring:
-// this wave's Philox blocks in LDS, [2][64] (F < 8).  FEAT: per-step schedules
-// and single-trial proposals; without it neither leaves code in the loop.
-template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
-__device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t *wl,
-                                         uint4 *ring) {
+// Lane records of a replica of several waves: accepted mask, x bits, and the
+// inclusive prefix of the accepted counts within the wave.
+template <int F>
+struct LaneRec {   // F <= 8: one word
+    typedef uint32_t type;
+    static __device__ __forceinline__ type make(uint32_t acc, uint32_t xb, int incl) {
+        return acc | (xb << 8) | ((uint32_t)incl << 16);
+    }
+    static __device__ __forceinline__ uint32_t acc(type r) { return r & 0xFFu; }
+    static __device__ __forceinline__ uint32_t x(type r) { return r >> 8; }   // (low F bits)
+    static __device__ __forceinline__ int incl(type r) { return (int)(r >> 16); }
+    static __device__ __forceinline__ type lane(type r, int l) { return (type)readlane((int)r, l); }
+};
+template <>
+struct LaneRec<16> {
+    typedef uint2 type;
+    static __device__ __forceinline__ type make(uint32_t acc, uint32_t xb, int incl) {
+        return make_uint2(acc | ((uint32_t)incl << 16), xb);
+    }
+    static __device__ __forceinline__ uint32_t acc(type r) { return r.x & 0xFFFFu; }
+    static __device__ __forceinline__ uint32_t x(type r) { return r.y; }
+    static __device__ __forceinline__ int incl(type r) { return (int)(r.x >> 16); }
+    static __device__ __forceinline__ type lane(type r, int l) {
+        return make_uint2((uint32_t)readlane((int)r.x, l), (uint32_t)readlane((int)r.y, l));
+    }
+};
+
+// LDS of a team of waves, by step parity: the lanes' records and the energy
+// change, then the bounds that the random-number waves hand over.
+template <int F>
+__host__ __device__ constexpr int team_rec_bytes(int NW) {
+    return (NW < 4 ? 4 : NW) * 64 * (F > 8 ? 8 : 4) + 16;
+}
+// Bounds of one step: of every Philox block the first four draws' and, shifted
+// by half the banks, the last four's, so that lanes of 4 and of 8 flips read
+// them without a bank conflict.
+__host__ __device__ constexpr int team_half_bytes(int N) { return (N + 1023) / 1024 * 128 * 16 + 128; }
+
+// The random-number waves of a team: during step s they write the bounds of step
+// s + 1, at its temperature, for the barrier of step s to hand over.  They fill
+// issue slots the other waves leave while they wait on each other and on W.
+// Each lane draws HB Philox blocks.
+template <int HB, bool CLAMP, bool FEAT>
+__device__ __forceinline__ void team_draws(const JobDesc &J, int rr, uint8_t *ring, int hw) {
+    const int lane = threadIdx.x & 63;
+    const int half = team_half_bytes(J.N);
+    const uint32_t rid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(J.rid_base + (uint32_t)rr));
+    const uint32_t k0 = (uint32_t)J.seed, k1 = (uint32_t)(J.seed >> 32);
+    const uint32_t r0 = __umulhi(kPhiloxM1, rid) ^ k0;
+    const bool perstep = FEAT && J.stepT != nullptr;
+    int64_t a = J.s0, b = J.s1;
+    if (J.round_ptr) {
+        a = (int64_t)*J.round_ptr * J.K;
+        b = a + J.K;
+    }
+    const uint32_t s0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
+    const uint32_t s1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+    int lvl = 0;
+    uint32_t t_next = 0xFFFFFFFFu;
+    auto next_of = [&](int l) -> uint32_t {
+        const int64_t n = next_level_step(l, J.L, J.S);
+        return (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)(n > (int64_t)0x7FFFFFFF ? 0xFFFFFFFFu : (uint32_t)n));
+    };
+    if (J.lvl_of_rep) {
+        lvl = __builtin_amdgcn_readfirstlane(J.lvl_of_rep[rr]);
+    } else if (!perstep) {
+        lvl = __builtin_amdgcn_readfirstlane(level_of(a, J.L, J.S));
+        t_next = next_of(lvl);
+    }
+    WaveLevel ls;
+    float ga, gb;
+    auto level_of_step = [&](uint32_t t) {
+        if (perstep) {
+            ls = wave_level<CLAMP>(
+                J.stepT[min((int64_t)((t & ~63u) + (uint32_t)lane), J.S - 1)].T, J.qcap, J.gerr);
+        } else {
+            ls = wave_level<CLAMP>(J.temps[lvl], J.qcap, J.gerr);
+            ga = ls.ga;
+            gb = ls.gb;
+        }
+    };
+    level_of_step(s0);
+    DrawBlock db[HB];
+#pragma unroll
+    for (int q = 0; q < HB; ++q)
+        db[q].init((uint32_t)((hw * HB + q) * 64 + lane), rid, k0, k1);
+    auto produce = [&](uint32_t t) {
+        if (perstep) {
+            ga = __int_as_float(readlane(__float_as_int(ls.ga), (int)(t & 63u)));
+            gb = __int_as_float(readlane(__float_as_int(ls.gb), (int)(t & 63u)));
+        }
+        uint8_t *slot = ring + (t & 1u) * (2 * half) + (hw * HB * 64 + lane) * 16;
+#pragma unroll
+        for (int q = 0; q < HB; ++q) {
+            const uint4 r = db[q].draw(t, r0, k0, k1);
+            int4 e0, e1;
+            e0.x = draw_bound<CLAMP>(r.x & 0xFFFFu, ga, gb);
+            e0.y = draw_bound<CLAMP>(r.x >> 16, ga, gb);
+            e0.z = draw_bound<CLAMP>(r.y & 0xFFFFu, ga, gb);
+            e0.w = draw_bound<CLAMP>(r.y >> 16, ga, gb);
+            e1.x = draw_bound<CLAMP>(r.z & 0xFFFFu, ga, gb);
+            e1.y = draw_bound<CLAMP>(r.z >> 16, ga, gb);
+            e1.z = draw_bound<CLAMP>(r.w & 0xFFFFu, ga, gb);
+            e1.w = draw_bound<CLAMP>(r.w >> 16, ga, gb);
+            *reinterpret_cast<int4 *>(slot + q * 1024) = e0;
+            *reinterpret_cast<int4 *>(slot + half + q * 1024) = e1;
+        }
+    };
+    if (s0 != s1) produce(s0);
+    __syncthreads();
+    for (uint32_t t = s0 + 1; t < s1; ++t) {
+        if (t == t_next) {
+            lvl = (int64_t)J.L > J.S
+                      ? __builtin_amdgcn_readfirstlane(level_of((int64_t)t, J.L, J.S))
+                      : lvl + 1;
+            t_next = next_of(lvl);
+            level_of_step(t);
+        } else if (perstep && (t & 63u) == 0u) {
+            level_of_step(t);
+        }
+        produce(t);
+        __syncthreads();
+    }
+    if (s0 != s1) __syncthreads();   // the last step's
+    __syncthreads();                 // after the last step
+}
+
+// Runs steps [s0, s1) of replica rr by the J.NW <= NWC waves of a team (NWC = 1:
+// this wave alone; NWC = 16: any number).  wl: W in LDS (WLDS); lds: this wave's
+// Philox blocks [2][64] (alone, F < 8), or a team's records and bounds (HELP: from
+// its random-number waves; else every wave draws its own, F >= 8).  FEAT: per-step schedules and single-trial proposals; without it
+// neither leaves code in the loop.
+//
+// A team meets at one barrier a step.  Before it every wave leaves its lanes'
+// records in LDS; after it every wave finds the chosen flip from them (up to
+// four waves: from all records of its own lane number, read at once), reads row
+// k of W for its own fields, and the wave that holds the flip leaves its energy
+// change for the others to add a step later.
+template <typename WT, int F, int NWC, bool HELP, bool WLDS, bool CLAMP, bool FEAT>
+__device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t *wl, uint8_t *lds,
+                                         int wr) {
+    constexpr bool TEAM = NWC > 1;
+    typedef LaneRec<F> Rec;
+    typedef typename Rec::type RecT;
+    const int NW = TEAM ? J.NW : 1;
+    static_assert(!HELP || TEAM, "random-number waves serve teams");
+    // this step's half of the records, and the other; its energy change at the end
+    const int RB = team_rec_bytes<F>(NW);
+    int rec_o = 0;
+    auto recs = [&](int o) { return reinterpret_cast<RecT *>(lds + o); };
+    auto denergy = [&](int o) { return reinterpret_cast<int *>(lds + o + RB - 16); };
+    uint4 *ring = reinterpret_cast<uint4 *>(lds);
     constexpr int NB = F >= 8 ? F / 8 : 1;   // Philox blocks per lane and step (F >= 8)
-    constexpr int P = F >= 8 ? 1 : 8 / F;    // steps drawn at once
+    constexpr int P = F >= 8 || HELP ? 1 : 8 / F;   // steps drawn at once
+    static_assert(!TEAM || HELP || F >= 8, "a team's lanes draw whole blocks");
     constexpr int RW = F >= 2 ? F / 2 : 1;   // 32-bit words of a lane's draws
     constexpr int NX = (F + 3) / 4;
     typedef typename VecOf<WT, F>::type RowV;
     const int lane = threadIdx.x & 63;
-    const int i0 = lane * F;
+    const int i0 = (wr * 64 + lane) * F;
     const int ld = J.ld;
     const bool lane_has = i0 < ld;
     const int col0 = lane_has ? i0 : 0;   // lanes past the row hold ghost flips only
@@ -264,7 +420,6 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     const uint32_t s1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
     int lvl = 0;
     uint32_t s_next = 0xFFFFFFFFu;   // first step of the next level
-    double T0;
     auto next_of = [&](int l) -> uint32_t {
         const int64_t n = next_level_step(l, J.L, J.S);
         return (uint32_t)__builtin_amdgcn_readfirstlane(
@@ -275,15 +430,24 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     };
     if (J.lvl_of_rep) {
         lvl = __builtin_amdgcn_readfirstlane(J.lvl_of_rep[rr]);
-        T0 = J.temps[lvl];
-    } else if (perstep) {
-        T0 = step_T(s);
-    } else {
+    } else if (!perstep) {
         lvl = __builtin_amdgcn_readfirstlane(level_of(a, J.L, J.S));
         s_next = next_of(lvl);
-        T0 = J.temps[lvl];
     }
-    WaveLevel lv = wave_level<CLAMP>(T0, J.qcap, J.gerr);
+    // the level of step t; per-step schedules: those of its 64 steps, lane by lane
+    WaveLevel ls, lv;
+    auto level_of_step = [&](uint32_t t) {
+        if (perstep) {
+            ls = wave_level<CLAMP>(step_T((t & ~63u) + (uint32_t)lane), J.qcap, J.gerr);
+            lv = level_at(ls, (int)(t & 63u));
+        } else {
+            const WaveLevel w = wave_level<CLAMP>(J.temps[lvl], J.qcap, J.gerr);
+            lv = level_at(w, 0);
+            lv.ga = w.ga;
+            lv.gb = w.gb;
+        }
+    };
+    level_of_step(s);
 #pragma unroll
     for (int f = 0; f < F; ++f) h[f] = (int)((uint32_t)h[f] << lv.q);
     int ec = 0, dwp = 0, dwn = 0;
@@ -297,14 +461,12 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
         for (int f = 0; f < F; ++f) h[f] = dq > 0 ? (int)((uint32_t)h[f] << dq) : h[f] >> -dq;
     };
     level_consts();
-    double Tn1 = 0.0;   // per-step: the temperature of step s + 1
-    if (perstep) Tn1 = step_T(s + 1);
 
     // --- draws ---------------------------------------------------------------
     DrawBlock db[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q)
-        db[q].init(F >= 8 ? (uint32_t)(lane * NB + q) : (uint32_t)(lane & (8 * F - 1)), rid, k0, k1);
+        db[q].init(P == 1 ? (uint32_t)(i0 >> 3) + q : (uint32_t)(lane & (8 * F - 1)), rid, k0, k1);
     // F < 8: the blocks of the P steps from t (a multiple of P), one per lane,
     // into the half of the ring that the group before it does not hold
     auto produce = [&](uint32_t t) {
@@ -316,7 +478,11 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     };
     // this lane's draws of step t: flip f is half f & 1 of word f >> 1
     auto fetch = [&](uint32_t t, uint32_t (&r)[RW]) {
-        if constexpr (F >= 8) {
+        if constexpr (F == 4 && P == 1) {
+            const uint4 v = db[0].draw(t, r0, k0, k1);
+            r[0] = (i0 & 4) ? v.z : v.x;
+            r[RW - 1] = (i0 & 4) ? v.w : v.y;
+        } else if constexpr (F >= 8) {
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
                 const uint4 v = db[q].draw(t, r0, k0, k1);
@@ -352,36 +518,67 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     // rn: the draws of this step (F >= 8), or of the next one, read ahead from
     // the ring, which holds this step's and the next one's group (F < 8)
     uint32_t rn[RW];
-    if (P > 1) produce(s & ~(uint32_t)(P - 1));
-    fetch(s, rn);
-    bounds(rn);
-    if (P > 1) {
-        if (((s + 1) & (P - 1)) == 0) produce(s + 1);
-        fetch(s + 1, rn);
+    if constexpr (!HELP) {
+        if (P > 1) produce(s & ~(uint32_t)(P - 1));
+        fetch(s, rn);
+        bounds(rn);
+        if (P > 1) {
+            if (((s + 1) & (P - 1)) == 0) produce(s + 1);
+            fetch(s + 1, rn);
+        }
     }
+    // HELP: this lane's bounds of step t from the ring (lanes past the last
+    // block: some block's)
+    const int half = HELP ? team_half_bytes(J.N) : 0;
+    const uint8_t *hring = lds + 2 * RB + min(i0 >> 3, (J.N - 1) >> 3) * 16 +
+                           (F == 4 && (i0 & 4) ? half : 0);
+    auto handed = [&](uint32_t t, int (&o)[F]) {
+        const uint8_t *p = hring + (t & 1u) * (2 * half);
+#pragma unroll
+        for (int q = 0; q < F / 4; ++q) {
+            const int4 e = *reinterpret_cast<const int4 *>(p + (q & 1) * half + (q >> 1) * 16);
+            o[(4 * q) % F] = e.x;
+            o[(4 * q + 1) % F] = e.y;
+            o[(4 * q + 2) % F] = e.z;
+            o[(4 * q + 3) % F] = e.w;
+        }
+    };
     int prop = single ? (int)(s % (uint32_t)J.N) : 0;
+    if constexpr (TEAM) {
+        // records of waves the team does not have: none accepted, ever
+        for (int q = NW * 64 + wr * 64 + lane; q < (NW < 4 ? 256 : 0); q += NW * 64)
+            recs(0)[q] = recs(RB)[q] = Rec::make(0u, 0u, 0);
+        if (wr == 0 && lane == 0) *denergy(0) = *denergy(RB) = 0;
+        if (HELP) __builtin_amdgcn_s_setprio(2);
+        __syncthreads();
+        if constexpr (HELP) handed(s, tv);
+    }
 
     // segments in which neither the level nor the selection draws change
     for (bool first = true; s != s1; first = false) {
         if (first || (s & 63u) == 0u)
             vsel = (int)philox(0u, (s & ~63u) + (uint32_t)lane, rid, kTagSelect, k0, k1).x;
-        if (s == s_next) {
+        if (s == s_next || (perstep && (s & 63u) == 0u)) {
             // the level that opens here: its fixed point, and this step's
             // bounds once more
             const int q = lv.q;
-            lvl = (int64_t)J.L > J.S
-                      ? __builtin_amdgcn_readfirstlane(level_of((int64_t)s, J.L, J.S))
-                      : lvl + 1;
-            s_next = next_of(lvl);
-            lv = wave_level<CLAMP>(J.temps[lvl], J.qcap, J.gerr);
+            if (!perstep) {
+                lvl = (int64_t)J.L > J.S
+                          ? __builtin_amdgcn_readfirstlane(level_of((int64_t)s, J.L, J.S))
+                          : lvl + 1;
+                s_next = next_of(lvl);
+            }
+            level_of_step(s);
             if (lv.q != q) rescale(lv.q - q);
             level_consts();
-            uint32_t rc[RW];
-            if constexpr (P > 1) {
-                fetch(s, rc);
-                bounds(rc);
-            } else {
-                bounds(rn);
+            if constexpr (!HELP) {
+                uint32_t rc[RW];
+                if constexpr (P > 1) {
+                    fetch(s, rc);
+                    bounds(rc);
+                } else {
+                    bounds(rn);
+                }
             }
         }
         const uint32_t seg = min(min(s1, s_next), (s & ~63u) + 64u);
@@ -404,13 +601,14 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
             if (__builtin_expect(ballot(zmax > lv.zamb) != 0, 0)) {
                 // rare: the definition, in double
                 uint32_t rc[RW];
-                if constexpr (P > 1) {
+                if constexpr (P > 1 || HELP) {
                     fetch(s, rc);
                 } else {
 #pragma unroll
                     for (int q = 0; q < RW; ++q) rc[q] = rn[q];
                 }
                 const int eo = ec - lv.c0;
+                const double T = __builtin_ldexp(perstep ? step_T(s) : J.temps[lvl], lv.q);
                 double g[F];
 #pragma unroll
                 for (int f = 0; f < F; ++f)
@@ -420,17 +618,66 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
                     const int mx = (int)(int8_t)(nx[f >> 2] >> (8 * (f & 3)));
                     const int d = mx - (h[f] ^ mx) - eo;   // (1 - 2x) h - E_off
                     const bool in = (uint32_t)z[f] > lv.zamb && ((vmask >> f) & 1u);
-                    acc |= (uint32_t)(in && (double)d < lv.T * g[f]) << f;
+                    acc |= (uint32_t)(in && (double)d < T * g[f]) << f;
                 }
             }
-            if (single) acc &= lane == prop / F ? 1u << (prop % F) : 0u;
+            if (single) acc &= wr * 64 + lane == prop / F ? 1u << (prop % F) : 0u;
 
             // 2. the chosen flip: the j-th accepted one in index order.  A step
             // that accepts none runs the same instructions with ts = -1 (no
             // lane), row 0 and factor 0: the branch around them costs more
             const uint32_t v = (uint32_t)readlane(vsel, (int)(s & 63u));
-            int m, ts, bit = 0;
-            if constexpr (F == 1) {
+            int m, ts, bit = 0, ws = 0;
+            uint32_t xk = 0;
+            int dEp = 0;
+            int tn[F];   // HELP: the next step's bounds
+            if constexpr (TEAM) {
+                const int incl = incl_scan(__popc(acc));
+                RecT *rec = recs(rec_o);
+                rec[wr * 64 + lane] = Rec::make(acc, xb, incl);
+                __syncthreads();
+                // everything the step reads from LDS at once
+                dEp = *denergy(RB - rec_o);
+                int j;
+                RecT r2;
+                if constexpr (NWC <= 4) {
+                    RecT r[NWC];
+                    int to[NWC];   // accepted in waves 0 .. q
+#pragma unroll
+                    for (int q = 0; q < NWC; ++q) r[q] = rec[q * 64 + lane];
+                    if constexpr (HELP) handed(s + 1, tn);
+                    m = 0;
+#pragma unroll
+                    for (int q = 0; q < NWC; ++q) to[q] = m += Rec::incl(Rec::lane(r[q], 63));
+                    j = (int)__umulhi(v, (uint32_t)m);
+                    r2 = r[0];
+                    int base = 0;
+#pragma unroll
+                    for (int q = 1; q < NWC; ++q) {
+                        // (numbers: as conditions these would go through lane masks)
+                        const int past = (to[q - 1] - 1 - j) >> 31;   // j >= to[q - 1]: -1
+                        ws -= past;
+                        base += (to[q - 1] - (q > 1 ? to[q > 1 ? q - 2 : 0] : 0)) & past;
+                        r2 = past ? r[q] : r2;
+                    }
+                    j -= base;
+                } else {
+                    const int t = Rec::incl(rec[min(lane, NW - 1) * 64 + 63]);
+                    if constexpr (HELP) handed(s + 1, tn);
+                    const int scan = incl_scan(lane < NW ? t : 0);
+                    m = readlane(scan, 63);
+                    j = (int)__umulhi(v, (uint32_t)m);
+                    ws = max(first_bit(ballot(scan > j)), 0);
+                    j -= readlane(scan, ws) - readlane(t, ws);
+                    r2 = rec[ws * 64 + lane];
+                }
+                ts = first_bit(ballot(Rec::incl(r2) > j));
+                const RecT rs = Rec::lane(r2, ts);
+                const uint32_t need = (uint32_t)(Rec::incl(rs) - j);
+                bit = first_bit((uint32_t)ballot((uint32_t)__popc(Rec::acc(rs) & ge_mask) == need) &
+                                Rec::acc(rs));
+                xk = Rec::x(rs);
+            } else if constexpr (F == 1) {
                 const uint64_t mk = ballot(acc != 0);
                 m = (int)__popcll(mk);
                 const int j = (int)__umulhi(v, (uint32_t)m);
@@ -456,7 +703,8 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
                 const uint32_t need = (uint32_t)(readlane(incl, ts) - j);
                 bit = first_bit((uint32_t)ballot((uint32_t)__popc(rs & ge_mask) == need) & rs);
             }
-            const int k = max(ts * F + bit, 0);
+            // (a team without an accepted flip has some ws)
+            const int k = TEAM ? (m > 0 ? (ws * 64 + ts) * F + bit : 0) : max(ts * F + bit, 0);
             // 3. row k of W, the step's only bulk traffic
             typedef __attribute__((address_space(3))) const RowV LdsRowV;
             typedef __attribute__((address_space(1))) const RowV GlobalRowV;
@@ -466,12 +714,14 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
             else
                 raw = *(GlobalRowV *)(reinterpret_cast<const WT *>(J.W) +
                                       (size_t)(uint32_t)(k * ld) + col0);
-            const uint32_t xk = (uint32_t)readlane((int)xb, ts);
-            const int hk = readlane(field_at<F>(h, bit), ts) >> lv.q;
+            int dE = 0, dw, hk = 0;
+            if constexpr (!TEAM) {
+                xk = (uint32_t)readlane((int)xb, ts);
+                hk = readlane(field_at<F>(h, bit), ts) >> lv.q;
+            }
             // (1 - 2 x_k) h_k, the rows' factor and the count, none of them when
             // m = 0 (written out: the compiler carries conditions of scalars
             // through 64-bit masks)
-            int dE, dw;
 #define DAPT_FLIP(BIT, ...)                                                            \
     asm("s_sub_i32 %0, 0, %3\n\t"                                                      \
         "s_bitcmp1_b32 %4, " BIT "\n\t"                                                \
@@ -484,15 +734,12 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
         : "=&s"(dE), "=&s"(dw), "+s"(nacc)                                             \
         : "s"(hk), "s"(xk), "s"(dwp), "s"(dwn), "s"(m) __VA_ARGS__                     \
         : "scc")
-            if constexpr (F == 1) {
-                DAPT_FLIP("0", );
-            } else {
-                DAPT_FLIP("%8", , "s"(bit));
-            }
+            if constexpr (F == 1) DAPT_FLIP("0", );
+            else DAPT_FLIP("%8", , "s"(bit));
 #undef DAPT_FLIP
-            if (lane == ts) {
-                xb ^= 1u << bit;
+            auto flip = [&]() __attribute__((always_inline)) {
                 const uint64_t mb = 0xFFull << (8 * (bit & 7));
+                xb ^= 1u << bit;
                 if constexpr (NX <= 2) {
                     nx[0] ^= (uint32_t)mb;
                     if (NX > 1) nx[NX - 1] ^= (uint32_t)(mb >> 32);
@@ -503,20 +750,41 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
                     nx[NX - 2] ^= (uint32_t)hi;
                     nx[NX - 1] ^= (uint32_t)(hi >> 32);
                 }
-            }
-            gap += (int64_t)dE;
-            int gap_hi = (int)(gap >> 32);
-            asm("" : "+s"(gap_hi));   // (tested as a scalar)
-            if (__builtin_expect(gap_hi < 0, 0)) {
-                bE += gap;
-                gap = 0;
-                bxb = xb;
+            };
+            auto add_energy = [&](int d) __attribute__((always_inline)) {
+                gap += (int64_t)d;
+                int gap_hi = (int)(gap >> 32);
+                asm("" : "+s"(gap_hi));   // (tested as a scalar)
+                if (__builtin_expect(gap_hi < 0, 0)) {
+                    bE += gap;
+                    gap = 0;
+                    bxb = xb;
+                }
+            };
+            if constexpr (TEAM) {
+                // the last step's energy change, its state not yet flipped
+                add_energy(__builtin_amdgcn_readfirstlane(dEp));
+                int *dEw = denergy(rec_o);
+                if (ws == wr) {
+                    hk = readlane(field_at<F>(h, bit), ts) >> lv.q;
+                    if (lane == ts) {
+                        *dEw = ((xk >> (bit & 31)) & 1u) ? -hk : hk;
+                        flip();
+                    }
+                }
+                rec_o = RB - rec_o;
+            } else {
+                if (lane == ts) flip();
+                add_energy(dE);
             }
             const int eo = eoff;
             eoff = 0;
             ec = lv.c0;
             if (__builtin_expect(m == 0, 0)) {
                 asm volatile("");   // (a branch: the selects cost more)
+                if constexpr (TEAM) {
+                    if (wr == 0 && lane == 0) *denergy(RB - rec_o) = 0;
+                }
                 // min(E_off + inc, 2^30) without leaving int32 (both in [0, 2^30])
                 eoff = min(eo, inc_cap) + inc;
                 ec = (int)(((uint32_t)min(eoff, ecap) << lv.q) + (uint32_t)lv.c0);
@@ -526,15 +794,18 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
             int dq = 0;
             if constexpr (FEAT) {
                 if (perstep) {
-                    // its temperature; the fields follow after this step's update
+                    // its temperature; the fields follow after this step's
+                    // update (past the 64 steps at hand: done again above)
                     const int q = lv.q;
-                    lv = wave_level<CLAMP>(Tn1, J.qcap, J.gerr);
+                    lv = level_at(ls, (int)((s + 1) & 63u));
                     dq = lv.q - q;
-                    Tn1 = step_T(s + 2);
                 }
                 if (single) prop = prop + 1 == J.N ? 0 : prop + 1;
             }
-            if constexpr (P == 1) {
+            if constexpr (HELP) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) tv[f] = tn[f];
+            } else if constexpr (P == 1) {
                 fetch(s + 1, rn);
                 bounds(rn);
             } else {
@@ -566,6 +837,18 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
         }
     }
 
+    if constexpr (TEAM) {
+        // the last step's energy change
+        __syncthreads();
+        const int d = __builtin_amdgcn_readfirstlane(*denergy(RB - rec_o));
+        gap += (int64_t)d;
+        if (gap < 0) {
+            bE += gap;
+            gap = 0;
+            bxb = xb;
+        }
+    }
+
     // --- state back to HBM -----------------------------------------------------
     if (lane_has) {
         IV hv;
@@ -580,7 +863,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
         *reinterpret_cast<BV *>(J.x + base) = xv;
         *reinterpret_cast<BV *>(J.bx + base) = bv;
     }
-    if (lane == 0) {
+    if (wr == 0 && lane == 0) {
         J.E[rr] = bE + gap;
         J.bE[rr] = bE;
         J.eoff[rr] = eoff;
@@ -605,45 +888,92 @@ __global__ __launch_bounds__(1024) void k_wave(JobDesc J) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int rr = blockIdx.x * J.RPW + wave;
     if (rr >= J.R) return;
-    wave_run<WT, F, WLDS, CLAMP, FEAT>(
-        J, rr, smem, reinterpret_cast<uint4 *>(smem + w_bytes) + (F < 8 ? wave * 128 : 0));
+    wave_run<WT, F, 1, false, WLDS, CLAMP, FEAT>(J, rr, smem, smem + w_bytes + (F < 8 ? wave * 2048 : 0), 0);
 }
 
-template <typename WT, int F, bool WLDS>
-int launch_wave_l(const JobDesc &J, int blocks, int threads, size_t lds, void *stream) {
-    const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (J.stepT || J.single)
-        hipLaunchKernelGGL((k_wave<WT, F, WLDS, true, true>), dim3(blocks), dim3(threads), lds, st, J);
-    else if (J.wclamp)
-        hipLaunchKernelGGL((k_wave<WT, F, WLDS, true, false>), dim3(blocks), dim3(threads), lds, st, J);
-    else
-        hipLaunchKernelGGL((k_wave<WT, F, WLDS, false, false>), dim3(blocks), dim3(threads), lds, st, J);
-    return (int)hipGetLastError();
-}
-
-template <typename WT, int F>
-int launch_wave_f(const JobDesc &J, int blocks, int threads, size_t lds, void *stream) {
-    // (a row of 16 flips per lane is past what fits LDS)
-    if constexpr (F < 16) {
-        if (J.w_lds) return launch_wave_l<WT, F, true>(J, blocks, threads, lds, stream);
+// One replica per workgroup: a team of J.NW waves and J.NH random-number waves.
+// HB: Philox blocks per lane of a random-number wave (0: no such waves).
+template <typename WT, int F, int NWC, int HB, bool CLAMP, bool FEAT>
+__global__ __launch_bounds__(NWC > 4 ? 1024 : 512) void k_team(JobDesc J) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if constexpr (HB > 0) {
+        if (wave >= J.NW) {
+            // (its lanes' blocks past N land in the padding of the ring)
+            team_draws<HB, CLAMP, FEAT>(J, blockIdx.x, smem + 2 * team_rec_bytes<F>(J.NW), wave - J.NW);
+            return;
+        }
     }
-    return launch_wave_l<WT, F, false>(J, blocks, threads, lds, stream);
+    wave_run<WT, F, NWC, (HB > 0), false, CLAMP, FEAT>(J, blockIdx.x, smem, smem, wave);
 }
+
+// Launches KERNEL<.., CLAMP, FEAT> as the job needs.
+#define DAPT_LAUNCH(KERNEL, ...)                                                                 \
+    do {                                                                                         \
+        const hipStream_t st = reinterpret_cast<hipStream_t>(stream);                            \
+        if (J.stepT || J.single)                                                                 \
+            hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true, true>), dim3(blocks), dim3(threads),   \
+                               lds, st, J);                                                      \
+        else if (J.wclamp)                                                                       \
+            hipLaunchKernelGGL((KERNEL<__VA_ARGS__, true, false>), dim3(blocks), dim3(threads),  \
+                               lds, st, J);                                                      \
+        else                                                                                     \
+            hipLaunchKernelGGL((KERNEL<__VA_ARGS__, false, false>), dim3(blocks), dim3(threads), \
+                               lds, st, J);                                                      \
+        return (int)hipGetLastError();                                                           \
+    } while (0)
 
 }  // namespace
 
-// (defined here, compiled for one coupling type per part of this file)
+// (defined here, compiled for one coupling type and team size per part of this file)
 template <typename WT>
 int launch_wave_w(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
+    if (J.w_lds) {
+        // (a row of 16 flips per lane is past what fits LDS)
+        switch (F) {
+            case 1: DAPT_LAUNCH(k_wave, WT, 1, true);
+            case 2: DAPT_LAUNCH(k_wave, WT, 2, true);
+            case 4: DAPT_LAUNCH(k_wave, WT, 4, true);
+            case 8: DAPT_LAUNCH(k_wave, WT, 8, true);
+            default: return (int)hipErrorInvalidValue;
+        }
+    }
     switch (F) {
-        case 1: return launch_wave_f<WT, 1>(J, blocks, threads, lds, stream);
-        case 2: return launch_wave_f<WT, 2>(J, blocks, threads, lds, stream);
-        case 4: return launch_wave_f<WT, 4>(J, blocks, threads, lds, stream);
-        case 8: return launch_wave_f<WT, 8>(J, blocks, threads, lds, stream);
-        case 16: return launch_wave_f<WT, 16>(J, blocks, threads, lds, stream);
+        case 1: DAPT_LAUNCH(k_wave, WT, 1, false);
+        case 2: DAPT_LAUNCH(k_wave, WT, 2, false);
+        case 4: DAPT_LAUNCH(k_wave, WT, 4, false);
+        case 8: DAPT_LAUNCH(k_wave, WT, 8, false);
+        case 16: DAPT_LAUNCH(k_wave, WT, 16, false);
         default: return (int)hipErrorInvalidValue;
     }
 }
+
+template <typename WT>
+int launch_team_w(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
+    const int key = F * 1000 + (J.NW <= 2 ? 2 : J.NW <= 4 ? 4 : 16) * 10 +
+                    (J.NH == 0 ? 0 : J.NH * 512 >= J.N ? 1 : 2);
+    switch (key) {
+        case 4041: DAPT_LAUNCH(k_team, WT, 4, 4, 1);
+        case 4042: DAPT_LAUNCH(k_team, WT, 4, 4, 2);
+        case 8020: DAPT_LAUNCH(k_team, WT, 8, 2, 0);
+        case 8021: DAPT_LAUNCH(k_team, WT, 8, 2, 1);
+        case 8022: DAPT_LAUNCH(k_team, WT, 8, 2, 2);
+        case 8040: DAPT_LAUNCH(k_team, WT, 8, 4, 0);
+        case 8041: DAPT_LAUNCH(k_team, WT, 8, 4, 1);
+        case 8042: DAPT_LAUNCH(k_team, WT, 8, 4, 2);
+        case 8160: DAPT_LAUNCH(k_team, WT, 8, 16, 0);
+        case 8161: DAPT_LAUNCH(k_team, WT, 8, 16, 1);
+        case 8162: DAPT_LAUNCH(k_team, WT, 8, 16, 2);
+        case 16040: DAPT_LAUNCH(k_team, WT, 16, 4, 0);
+        case 16041: DAPT_LAUNCH(k_team, WT, 16, 4, 1);
+        case 16042: DAPT_LAUNCH(k_team, WT, 16, 4, 2);
+        case 16160: DAPT_LAUNCH(k_team, WT, 16, 16, 0);
+        case 16162: DAPT_LAUNCH(k_team, WT, 16, 16, 2);
+        case 16020: DAPT_LAUNCH(k_team, WT, 16, 2, 0);
+        default: return (int)hipErrorInvalidValue;
+    }
+}
+#undef DAPT_LAUNCH
 
 #if DAPT_PART == 1
 template int launch_wave_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
@@ -651,29 +981,51 @@ template int launch_wave_w<int8_t>(const JobDesc &, int, int, int, size_t, void 
 template int launch_wave_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
 #elif DAPT_PART == 3
 template int launch_wave_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
+#elif DAPT_PART == 4
+template int launch_team_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
+#elif DAPT_PART == 5
+template int launch_team_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
+#elif DAPT_PART == 6
+template int launch_team_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
 #endif
 
 #if DAPT_PART == 0
 extern template int launch_wave_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
 extern template int launch_wave_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
 extern template int launch_wave_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
+extern template int launch_team_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
+extern template int launch_team_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
+extern template int launch_team_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
 
-size_t wave_lds_bytes(int F, int RPW, int64_t w_lds_bytes) {
+size_t wave_lds_bytes(int F, int N, int NW, int NH, int RPW, int64_t w_lds_bytes) {
+    if (NW > 1)
+        return 2 * (size_t)(F > 8 ? team_rec_bytes<16>(NW) : team_rec_bytes<8>(NW)) +
+               (NH > 0 ? 4 * (size_t)team_half_bytes(N) : 0);
     return (size_t)w_lds_bytes + (F < 8 ? (size_t)RPW * 2048 : 0);
 }
 
 int launch_wave(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
-    // a wave per replica holds 64 F variables; everything the kernel indexes is
-    // sized by these
-    if (job_range_error(J) != nullptr || J.NW != 1 || J.NH != 0 || J.N > 64 * F || !J.G ||
-        (!J.temps && !J.stepT) || threads != 64 * J.RPW ||
-        (int64_t)blocks * J.RPW < J.R ||
-        lds < wave_lds_bytes(F, J.RPW, J.w_lds ? (int64_t)J.N * J.ld * J.dtype : 0))
+    // a replica's waves hold 64 F variables each; everything the kernel indexes
+    // is sized by these
+    const bool team = J.NW > 1;
+    if (job_range_error(J) != nullptr || J.N > 64 * F * J.NW || !J.G || (!J.temps && !J.stepT) ||
+        threads != 64 * (J.NW + J.NH) * J.RPW || (int64_t)blocks * J.RPW < J.R ||
+        lds < wave_lds_bytes(F, J.N, J.NW, J.NH, J.RPW, J.w_lds ? (int64_t)J.N * J.ld * J.dtype : 0))
+        return (int)hipErrorInvalidValue;
+    if (team ? J.RPW != 1 || J.w_lds || blocks != J.R || threads > (J.NW > 4 ? 1024 : 512) ||
+                   (J.NH > 0 && J.N > 1024 * J.NH)
+             : J.NH != 0)
         return (int)hipErrorInvalidValue;
     switch (J.dtype) {
-        case 1: return launch_wave_w<int8_t>(J, F, blocks, threads, lds, stream);
-        case 2: return launch_wave_w<int16_t>(J, F, blocks, threads, lds, stream);
-        case 4: return launch_wave_w<int32_t>(J, F, blocks, threads, lds, stream);
+        case 1:
+            return team ? launch_team_w<int8_t>(J, F, blocks, threads, lds, stream)
+                        : launch_wave_w<int8_t>(J, F, blocks, threads, lds, stream);
+        case 2:
+            return team ? launch_team_w<int16_t>(J, F, blocks, threads, lds, stream)
+                        : launch_wave_w<int16_t>(J, F, blocks, threads, lds, stream);
+        case 4:
+            return team ? launch_team_w<int32_t>(J, F, blocks, threads, lds, stream)
+                        : launch_wave_w<int32_t>(J, F, blocks, threads, lds, stream);
         default: return (int)hipErrorInvalidValue;
     }
 }

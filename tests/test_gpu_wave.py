@@ -1,5 +1,5 @@
-"""The one-wave step kernel (N <= 1024, chosen by da_anneal) against the CPU
-oracle: every number of flips per lane at its smallest and largest N and at
+"""The step kernels of one wave and of teams of waves (chosen by da_anneal)
+against the CPU oracle: every number of flips per lane at its smallest and largest N and at
 ragged ones, every coupling type with W in LDS and in global memory, couplings
 from +-1 to 10^7 (fixed point with and without fraction bits, brackets from two
 units to hundreds), levels that change the fixed point, schedules with more
@@ -92,6 +92,7 @@ def test_schedules(api, N, kind, L, S, extra):
 def test_zero_temperature_and_offsets(api, N, inc):
     Q = instances.random_qubo(N, 3, lo=-300, hi=300)
     _check(api, Q, 0, 3, 400, 4, 0.0, 0.0, inc)
+    _check(api, Q, 0, 3, 200, 0, 0.0, 0.0, inc)
     _check(api, Q, 0, 3, 400, 4, 200.0, 1e-3, inc)
 
 
@@ -104,9 +105,35 @@ def test_common_factors(api, scale, dtype):
     _check(api, Q, dtype, 3, 300, 8, 30.0, 0.1, 1)    # T far below a coupling
 
 
+# teams of waves: 8 and 16 flips per lane, random-number waves that draw two
+# blocks, one, and none (by replicas per compute unit)
+@pytest.mark.parametrize("kind", ["sk", "gauss", "q100000"])
+@pytest.mark.parametrize("N,R", [
+    (513, 3), (600, 3), (1000, 3), (1024, 3), (999, 600), (1000, 1100),
+    (1025, 2), (1500, 2), (2048, 300), (1300, 1100), (1300, 1300),
+    (2049, 2), (3000, 2), (4096, 2), (2100, 300), (2100, 600),
+    (4097, 2), (8192, 2), (5000, 300)])
+def test_teams(api, kind, N, R):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    S = 60 if N > 2048 else 200
+    if R < 10:
+        S *= 2
+    _check(api, Q, 0, R, S, 7, T_hi, T_lo, inc, init="random")
+
+
+@pytest.mark.parametrize("N,R", [(700, 3), (1000, 600), (700, 1100), (1500, 2), (3000, 2), (4200, 2)])
+@pytest.mark.parametrize("kind,L,S,extra", [
+    ("sk", 150, 100, {}), ("cold", 4, 150, {}), ("sk", 0, 150, dict(kind="linear_beta")),
+    ("gauss", 0, 70, {}), ("q100", 3, 150, dict(trial="single")), ("sk", 3, 0, {}), ("sk", 0, 1, {}),
+])
+def test_team_schedules(api, N, R, kind, L, S, extra):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    _check(api, Q, 0, R, S, L, T_hi, T_lo, inc, **extra)
+
+
 def test_resume(api):
     """Pieces that cut levels and groups of steps equal the whole run."""
-    for N in (50, 100, 220, 480):
+    for N in (50, 100, 220, 480, 800, 1400):
         Q, T_hi, T_lo, inc = _instance("sk", N)
         ctx = api.da_create(Q)
         sch = api.schedule(T_hi, T_lo, "geometric", 9, eoff_inc=inc)
