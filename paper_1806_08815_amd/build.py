@@ -24,7 +24,7 @@ SOURCES = ["da_kernels.hip", "da_wave.hip", "da_fields.hip", "da_probe.hip", "da
            "da_noalloc.hip"]
 HEADERS = ["da_device.h", "da_internal.h", "da_runtime.h"]
 # compiled in parts (-DDAPT_PART=n), side by side: the step kernels' variants
-PARTS = {"da_kernels.hip": 5, "da_wave.hip": 7}
+PARTS = {"da_kernels.hip": 5, "da_wave.hip": 10}
 
 
 def source_hash() -> str:

@@ -238,6 +238,7 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t r
     J.qcap = sh.qcap;
     J.ecap = sh.ecap;
     J.w24 = sh.w24;
+    J.F = sh.wave ? sh.F : 0;
     J.wclamp = sh.wclamp;
     if (lt) {
         J.L = lt->L;
@@ -347,8 +348,10 @@ int device_lds_limit() {
     return limit;
 }
 
-LaunchShape batch_shape(const da_ctx *ctx) {
+LaunchShape batch_shape(const da_ctx *ctx, int32_t R, const da_schedule &s) {
     LaunchShape sh;
+    if (wave_shape(ctx, R, std::min(s.T_hi, s.T_lo), std::max(s.T_hi, s.T_lo), sh)) return sh;
+    sh = LaunchShape();
     sh.NH = 0;
     sh.F = 8;
     sh.NW = (ctx->N + 511) / 512;
@@ -363,10 +366,6 @@ LaunchShape batch_shape(const da_ctx *ctx) {
                  ? 1
                  : 0;
     return sh;
-}
-
-void append_batch_items(const JobDesc &J, int job_index, std::vector<BatchItem> &items) {
-    for (int32_t r0 = 0; r0 < J.R; r0 += J.RPW) items.push_back(BatchItem{job_index, r0});
 }
 
 int BatchRunner::prepare(std::string &err) {
@@ -393,7 +392,12 @@ int BatchRunner::prepare(std::string &err) {
         release();
         return DA_ENOMEM;
     }
-    if (hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking) != hipSuccess) {
+    bool made = hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking) == hipSuccess &&
+                hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
+    for (int b = 0; b < kSide && made; ++b)
+        made = hipStreamCreateWithFlags(&side[b], hipStreamNonBlocking) == hipSuccess &&
+               hipEventCreateWithFlags(&join[b], hipEventDisableTiming) == hipSuccess;
+    if (!made) {
         err = "stream creation failed";
         release();
         return DA_EDEVICE;
@@ -431,14 +435,138 @@ int BatchRunner::prepare(std::string &err) {
     return DA_OK;
 }
 
-int BatchRunner::run(const std::vector<JobDesc> &jobs, const std::vector<BatchItem> &items,
-                     hipStream_t s, std::string &err) {
+namespace {
+// Shape of a job among others: at most 8 waves a workgroup.  A replica's step is
+// the limit (16 jobs of N = 64 .. 2048, 10^4 steps: 10.7 ms; 13.5 with 16 flips
+// per lane throughout) unless the batch holds more waves than the chip does at
+// once (full): then the shapes with the fewest instructions.
+void mix_shape(JobDesc &J, bool full) {
+    const int N = J.N;
+    J.F = N <= 64 ? 1 : N <= 128 ? 2 : N <= 256 ? 4 : N <= 512 ? 8 : !full && N <= 2048 ? 8 : 16;
+    J.NW = (N + 64 * J.F - 1) / (64 * J.F);
+    J.NH = J.NW > 1 && !full && N <= 4096 ? (N + 1023) / 1024 : 0;
+    J.RPW = J.NW > 1 ? 1 : 4;
+    J.w_lds = J.F <= 2 && (int64_t)N * J.ld * J.dtype <= 32768 ? 1 : 0;
+}
+// A replica-step's time, roughly, in 100 ns (the order of the items only).
+int mix_weight(int N) {
+    int w = 2;
+    for (int n = 64; n < N; n <<= 1) ++w;
+    return w;
+}
+}  // namespace
+
+int BatchRunner::run(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err) {
     int rc = prepare(err);
     if (rc) return rc;
     if (jobs.size() > (size_t)kCapJobs) {
         err = "too many jobs in one batch";
         return DA_EINVAL;
     }
+    std::vector<JobDesc> mixed, rest;
+    for (const JobDesc &J : jobs)
+        if (J.s1 > J.s0) (J.F > 0 ? mixed : rest).push_back(J);
+    if (!mixed.empty()) rc = run_mixed(mixed, s, err);
+    if (!rc && !rest.empty()) {
+        // (the tables are in use until the launches before are done)
+        if (!mixed.empty()) {
+            const hipError_t e = hipStreamSynchronize(s);
+            if (e != hipSuccess) {
+                err = hipGetErrorString(e);
+                return DA_EDEVICE;
+            }
+        }
+        rc = run_persistent(rest, s, err);
+    }
+    return rc;
+}
+
+int BatchRunner::run_mixed(const std::vector<JobDesc> &given, hipStream_t s, std::string &err) {
+    int64_t waves = 0;
+    std::vector<JobDesc> jobs(given);
+    for (JobDesc &J : jobs) {
+        mix_shape(J, false);
+        waves += (int64_t)J.R * (J.NW + J.NH);
+    }
+    if (waves > 32 * (int64_t)blocks)   // more than the chip holds at once
+        for (JobDesc &J : jobs) mix_shape(J, true);
+    // classes: coupling type and mode
+    struct Item {
+        int cls;
+        int64_t cost;
+        BatchItem it;
+    };
+    std::vector<Item> order;
+    size_t class_lds[9] = {};
+    int64_t class_cost[9] = {};
+    for (size_t j = 0; j < jobs.size(); ++j) {
+        const JobDesc &J = jobs[j];
+        const size_t l = wave_lds_bytes(J.F, J.N, J.NW, J.NH, J.RPW,
+                                        J.w_lds ? (int64_t)J.N * J.ld * J.dtype : 0);
+        const char *why = job_range_error(J);
+        if (!why && (J.N > 64 * J.F * J.NW || !J.G || (!J.temps && !J.stepT) || J.NW + J.NH > 8 ||
+                     (J.NH > 0 && J.N > 1024 * J.NH) || l > (size_t)device_lds_limit()))
+            why = "batched job outside the kernel's shapes";
+        if (why) {
+            err = why;
+            return DA_EINVAL;
+        }
+        const int mode = J.stepT || J.single ? 2 : J.wclamp ? 1 : 0;
+        const int cls = (J.dtype == 1 ? 0 : J.dtype == 2 ? 1 : 2) * 3 + mode;
+        class_lds[cls] = std::max(class_lds[cls], l);
+        const int64_t cost = (J.s1 - J.s0) * mix_weight(J.N);
+        for (int32_t r0 = 0; r0 < J.R; r0 += J.RPW)
+            order.push_back(Item{cls, cost, BatchItem{(int32_t)j, r0}});
+        class_cost[cls] = std::max(class_cost[cls], cost);
+    }
+    // longest first within a class, and the class with the longest first
+    std::stable_sort(order.begin(), order.end(), [&](const Item &p, const Item &q) {
+        if (p.cls != q.cls)
+            return class_cost[p.cls] != class_cost[q.cls] ? class_cost[p.cls] > class_cost[q.cls]
+                                                          : p.cls < q.cls;
+        return p.cost > q.cost;
+    });
+    std::memcpy(h_jobs, jobs.data(), jobs.size() * sizeof(JobDesc));
+    hipError_t e = hipMemcpyAsync(d_jobs, h_jobs, jobs.size() * sizeof(JobDesc),
+                                  hipMemcpyHostToDevice, s);
+    for (size_t off = 0; off < order.size() && e == hipSuccess; off += kCapItems) {
+        const size_t n = std::min(order.size() - off, (size_t)kCapItems);
+        // the chunk before must be done with the table before it changes
+        if (off) e = hipStreamSynchronize(s);
+        for (size_t q = 0; q < n; ++q) h_items[q] = order[off + q].it;
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(d_items, h_items, n * sizeof(BatchItem), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipEventRecord(fork, s);
+        int k = 0;   // launches of this chunk: the first on s, the others beside it
+        for (size_t q = 0; q < n && e == hipSuccess; ++k) {
+            const int cls = order[off + q].cls;
+            size_t end = q;
+            while (end < n && order[off + end].cls == cls) ++end;
+            const int b = k == 0 ? -1 : (k - 1) % kSide;
+            const hipStream_t st = b < 0 ? s : side[b];
+            if (b >= 0) e = hipStreamWaitEvent(st, fork, 0);
+            if (e == hipSuccess)
+                e = (hipError_t)launch_mix(d_jobs, d_items + q, cls / 3 == 0 ? 1 : cls / 3 == 1 ? 2 : 4,
+                                           cls % 3, (int)(end - q), class_lds[cls], st);
+            q = end;
+        }
+        for (int b = 0; b < std::min(k - 1, kSide) && e == hipSuccess; ++b) {
+            e = hipEventRecord(join[b], side[b]);
+            if (e == hipSuccess) e = hipStreamWaitEvent(s, join[b], 0);
+        }
+    }
+    if (e != hipSuccess) {
+        err = std::string("batch launch failed: ") + hipGetErrorString(e);
+        return DA_EDEVICE;
+    }
+    return DA_OK;
+}
+
+int BatchRunner::run_persistent(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err) {
+    std::vector<BatchItem> items;
+    for (size_t j = 0; j < jobs.size(); ++j)
+        for (int32_t r0 = 0; r0 < jobs[j].R; r0 += jobs[j].RPW)
+            items.push_back(BatchItem{(int32_t)j, r0});
     bool dynamic = false;
     for (const JobDesc &J : jobs) dynamic = dynamic || J.single || J.stepT || J.ell;
     // longest items first so the tail of the persistent launch is short
@@ -482,6 +610,14 @@ void BatchRunner::release() {
         graph[v] = nullptr;
     }
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
+    if (fork) (void)hipEventDestroy(fork);
+    fork = nullptr;
+    for (int b = 0; b < kSide; ++b) {
+        if (side[b]) (void)hipStreamDestroy(side[b]);
+        if (join[b]) (void)hipEventDestroy(join[b]);
+        side[b] = nullptr;
+        join[b] = nullptr;
+    }
     for (void *p : {(void *)d_jobs, (void *)d_items, (void *)d_n, (void *)d_counter})
         if (p) (void)hipFree(p);
     for (void *p : {(void *)h_jobs, (void *)h_items, (void *)h_n})
@@ -876,6 +1012,43 @@ int next_events(da_ctx *ctx, hipEvent_t &e0, hipEvent_t &e1) {
     return DA_OK;
 }
 
+int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err) {
+    if (sch.n_levels == 0 && steps > kMaxPerStepSteps) {
+        err = "per-step schedules take at most 2^24 steps";
+        return DA_EINVAL;
+    }
+    const bool perstep = sch.n_levels == 0 && steps > 0;
+    if (perstep) {
+        jt.steps = get_step_tables(sch, steps, err);
+        if (!jt.steps) return DA_ENOMEM;
+    }
+    if (wave) {
+        if (!perstep) {
+            jt.temps = get_temp_list(
+                sch.n_levels > 0 ? schedule_temps(sch) : std::vector<double>{0.0}, err);
+            if (!jt.temps) return DA_ENOMEM;
+        }
+        if (!device_bound_error(jt.gerr, err)) return DA_ENOMEM;
+    } else {
+        jt.levels = get_level_tables(
+            sch.n_levels > 0 ? schedule_temps(sch) : std::vector<double>{0.0}, err);
+        if (!jt.levels) return DA_ENOMEM;
+    }
+    if (wave || perstep) {
+        jt.G = device_neg_log_u(err);
+        if (!jt.G) return DA_ENOMEM;
+    }
+    return DA_OK;
+}
+
+void attach_tables(JobDesc &J, const da_schedule &sch, const JobTables &jt) {
+    J.stepT = jt.steps ? jt.steps->d_steps : nullptr;
+    J.G = jt.G;
+    J.temps = jt.temps ? jt.temps->d_temps : nullptr;
+    J.gerr = jt.gerr;
+    if (jt.temps) J.L = std::max(sch.n_levels, 1);
+}
+
 namespace {
 // Pinned blocks that small outputs pass through: at most kBlocks per process,
 // allocated when first needed, each with one call at a time, kept until the
@@ -1017,66 +1190,6 @@ void record_stats(da_ctx *ctx, const LaunchShape &sh, int64_t launches, int gth 
 }
 
 // Enqueue a full anneal: state init, step kernel between timing events.
-// Tables a schedule needs: per-level decision tables, or, for a per-step
-// schedule (n_levels = 0), one dummy level (T = 0, empty band) plus the step
-// table and -ln U_u.
-struct JobTables {
-    std::shared_ptr<LevelTables> levels;
-    std::shared_ptr<StepTables> steps;
-    std::shared_ptr<TempList> temps;   // one-wave kernel
-    const double *G = nullptr;
-    float gerr = 0.0f;
-};
-
-// What the one-wave kernel takes of a schedule: its temperatures, -ln U_u and
-// the bound error.
-int wave_tables(const da_schedule &sch, int64_t steps, JobTables &jt, std::string &err) {
-    if (sch.n_levels == 0) {
-        if (steps > kMaxPerStepSteps) {
-            err = "per-step schedules take at most 2^24 steps";
-            return DA_EINVAL;
-        }
-        if (steps > 0) {
-            jt.steps = get_step_tables(sch, steps, err);
-            if (!jt.steps) return DA_ENOMEM;
-        } else {
-            jt.temps = get_temp_list(std::vector<double>{0.0}, err);
-            if (!jt.temps) return DA_ENOMEM;
-        }
-    } else {
-        jt.temps = get_temp_list(schedule_temps(sch), err);
-        if (!jt.temps) return DA_ENOMEM;
-    }
-    jt.G = device_neg_log_u(err);
-    return jt.G && device_bound_error(jt.gerr, err) ? DA_OK : DA_ENOMEM;
-}
-
-int job_tables(const da_schedule &sch, int64_t steps, JobTables &jt, std::string &err) {
-    if (sch.n_levels == 0) {
-        if (steps > kMaxPerStepSteps) {
-            err = "per-step schedules take at most 2^24 steps";
-            return DA_EINVAL;
-        }
-        jt.levels = get_level_tables(std::vector<double>{0.0}, err);
-        if (!jt.levels) return DA_ENOMEM;
-        if (steps > 0) {
-            jt.steps = get_step_tables(sch, steps, err);
-            jt.G = device_neg_log_u(err);
-            if (!jt.steps || !jt.G) return DA_ENOMEM;
-        }
-        return DA_OK;
-    }
-    jt.levels = get_level_tables(schedule_temps(sch), err);
-    return jt.levels ? DA_OK : DA_ENOMEM;
-}
-
-void attach_step_tables(JobDesc &J, const JobTables &jt) {
-    J.stepT = jt.steps ? jt.steps->d_steps : nullptr;
-    J.G = jt.G;
-    J.temps = jt.temps ? jt.temps->d_temps : nullptr;
-    J.gerr = jt.gerr;
-}
-
 // Steps [step_begin, step_end) of a `steps`-step anneal; step_begin > 0
 // continues from the state the context holds.
 int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_base,
@@ -1102,7 +1215,7 @@ int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_bas
     const bool own = launch == nullptr && trace_dev == nullptr;
     const bool wave = own && wave_shape(ctx, replicas, std::min(schedule->T_hi, schedule->T_lo),
                                         std::max(schedule->T_hi, schedule->T_lo), sh);
-    rc = wave ? wave_tables(*schedule, steps, jt, err) : job_tables(*schedule, steps, jt, err);
+    rc = job_tables(*schedule, steps, wave, jt, err);
     if (rc) return fail(ctx, rc, err);
     ctx->keep_tables = jt.levels;
     ctx->keep_steps = jt.steps;
@@ -1123,8 +1236,7 @@ int enqueue_anneal(da_ctx *ctx, const da_schedule *schedule, int64_t replica_bas
         }
     }
     J = make_job(ctx, jt.levels.get(), replicas, (uint32_t)replica_base, seed, steps, *schedule, sh);
-    attach_step_tables(J, jt);
-    if (jt.temps) J.L = std::max(schedule->n_levels, 1);
+    attach_tables(J, *schedule, jt);
     J.s0 = step_begin;
     J.s1 = step_end;
     if (const char *why = job_range_error(J)) return fail(ctx, DA_EINVAL, why);
@@ -1393,9 +1505,7 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
             if (items[a].ctx == items[c].ctx)
                 return fail(nullptr, DA_EINVAL, "batch items must use distinct contexts");
     std::vector<JobDesc> jobs((size_t)count);
-    std::vector<BatchItem> work;
-    std::vector<std::shared_ptr<LevelTables>> keep;
-    std::vector<std::shared_ptr<StepTables>> keep_steps;
+    std::vector<JobTables> keep((size_t)count);
     // no context claims a resumable state until the whole batch has run
     for (int32_t a = 0; a < count; ++a)
         if (items[a].ctx) items[a].ctx->st_step = -1;
@@ -1410,24 +1520,20 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
         if (it.replicas < 1 || it.steps < 0 || it.steps > kMaxSteps || it.replica_base < 0 ||
             it.replica_base + it.replicas > (int64_t(1) << 31))
             return fail(ctx, DA_EINVAL, "bad replicas / steps / replica_base in batch item");
-        JobTables jt;
-        rc = job_tables(it.schedule, it.steps, jt, err);
+        const LaunchShape sh = batch_shape(ctx, it.replicas, it.schedule);
+        JobTables &jt = keep[(size_t)a];
+        rc = job_tables(it.schedule, it.steps, sh.wave, jt, err);
         if (rc) return fail(ctx, rc, err);
-        auto lt = jt.levels;
-        if (jt.steps) keep_steps.push_back(jt.steps);
-        if (!lt) return fail(ctx, DA_ENOMEM, err);
-        keep.push_back(lt);
-        ctx->keep_tables = lt;
+        ctx->keep_tables = jt.levels;
+        ctx->keep_temps = jt.temps;
         if (!ctx->st.ensure(it.replicas, ctx->ld, err)) return fail(ctx, DA_ENOMEM, err);
-        const LaunchShape sh = batch_shape(ctx);
-        jobs[(size_t)a] = make_job(ctx, lt.get(), it.replicas, (uint32_t)it.replica_base, it.seed,
-                                   it.steps, it.schedule, sh);
-        attach_step_tables(jobs[(size_t)a], jt);
+        jobs[(size_t)a] = make_job(ctx, jt.levels.get(), it.replicas, (uint32_t)it.replica_base,
+                                   it.seed, it.steps, it.schedule, sh);
+        attach_tables(jobs[(size_t)a], it.schedule, jt);
         if (const char *why = job_range_error(jobs[(size_t)a])) return fail(ctx, DA_EINVAL, why);
         rc = init_state(ctx, jobs[(size_t)a], it.schedule.init, s);
         if (rc) return rc;
-        if (it.steps > 0) append_batch_items(jobs[(size_t)a], a, work);
-        record_stats(ctx, sh, 1);
+        record_stats(ctx, sh, 1, sh.wave ? 1 : 0);
     }
     da_ctx *c0 = items[0].ctx;
     // process-lifetime runner (never destroyed: no device frees at exit)
@@ -1439,11 +1545,9 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
     hipEvent_t be0 = nullptr, be1 = nullptr;
     int rc = next_events(c0, be0, be1);
     if (!rc) rc = check_hip(c0, hipEventRecord(be0, s), "event record");
-    if (!rc && !work.empty()) {
-        rc = runner.run(jobs, work, s, err);
+    if (!rc) {
+        rc = runner.run(jobs, s, err);
         if (rc) fail(c0, rc, err);
-        c0->last.blocks = runner.blocks;
-        c0->last.threads = 1024;
     }
     if (!rc) rc = check_hip(c0, hipEventRecord(be1, s), "event record");
     for (int32_t a = 0; a < count && !rc; ++a)
@@ -1540,7 +1644,7 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
                       DA_TRIAL_PARALLEL, 0};
     if (!wave) sh = choose_shape(ctx, R, nullptr, false);
     JobDesc J = make_job(ctx, lt, R, 0u, seed, 0, sched, sh);
-    attach_step_tables(J, jt);
+    attach_tables(J, sched, jt);
     // per-draw estimates (one replica per workgroup, several compute waves,
     // fields of many coupling units, as for anneals; the levels' windows are
     // measured when the tables are made): handed over by the random-number

@@ -125,7 +125,8 @@ struct JobDesc {
     int32_t ell_D;               // sparse row lists: entries per row (0: dense)
     const uint32_t *ell;         // [N][ell_D] column | value << 16, or null
     int32_t gth;                 // 1: random-number waves hand over per-draw estimates
-    // one-wave kernel (da_wave.hip)
+    // wave and team kernels (da_wave.hip)
+    int32_t F;                   // flips per lane, where launches mix jobs
     const double *temps;         // temperature of each level
     float gerr;                  // error of a bound per unit of T (wave_level)
     int32_t qcap;                // most fraction bits of a fixed-point cost
@@ -199,6 +200,11 @@ int launch_run(const JobDesc &J, int F, bool help, const TraceDesc *trace, int b
 // random-number waves.  wave_lds_bytes is what its workgroups need.
 size_t wave_lds_bytes(int F, int N, int NW, int NH, int RPW, int64_t w_lds_bytes);
 int launch_wave(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream);
+// The wave and team kernels over many jobs of one coupling type and mode (0 plain,
+// 1 bounds by conversion, 2 per-step or single-trial): one workgroup of 512
+// threads per item, in the shape its job states.
+int launch_mix(const JobDesc *jobs, const BatchItem *items, int dtype, int mode, int blocks,
+               size_t lds, void *stream);
 // Largest error of the device's fp32 log2 over the arguments u + 1/2 of all draws.
 int launch_log_error(const double *G, float *out, void *stream);
 // Persistent batched step kernel; the item count is read from device memory so

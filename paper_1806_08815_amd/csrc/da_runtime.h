@@ -74,10 +74,8 @@ struct HostTables {
 };
 void build_host_tables(const std::vector<double> &temps, HostTables &ht);
 // Tables for a temperature list (cached per device); nullptr on failure with
-// `err` set.  `pre`, when given, must hold the host image of these
-// temperatures' tables and is uploaded instead of building them again.
-std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err,
-                                              const HostTables *pre = nullptr);
+// `err` set.
+std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err);
 // Device bytes of the tables of L levels with `buckets` brackets in total.
 int64_t level_table_bytes(int32_t L, int64_t buckets);
 
@@ -114,10 +112,13 @@ struct LaunchShape {
     size_t lds = 0;
 };
 
-// Runs batches of jobs in one persistent launch of the batched step kernel.
-// Descriptor tables have a fixed device capacity so that the launch (counter
-// reset + kernel) is captured once as a hipGraph and replayed for every batch;
-// only the table contents are re-uploaded, from pinned host staging.
+// Runs batches of jobs.  Jobs of the wave and team kernels go in one launch per
+// class of coupling type and mode, side by side on streams of the runner; the
+// others (sparse row lists, fields too large for those kernels) in one persistent
+// launch of the batched step kernel.
+// Descriptor tables have a fixed device capacity so that the persistent launch
+// (counter reset + kernel) is captured once as a hipGraph and replayed for every
+// batch; only the table contents are re-uploaded, from pinned host staging.
 struct BatchRunner {
     static constexpr int kCapJobs = 1024;
     static constexpr int kCapItems = 65536;
@@ -131,21 +132,25 @@ struct BatchRunner {
     int blocks = 0;
     size_t lds = 0;
     hipStream_t cap_stream = nullptr;
+    static constexpr int kSide = 3;
+    hipStream_t side[kSide] = {};
+    hipEvent_t fork = nullptr, join[kSide] = {};
     // [0]: plain DA step kernel; [1]: the variant reading per-job features
     hipGraph_t graph[2] = {nullptr, nullptr};
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     int prepare(std::string &err);
     // Enqueues the batch on `s` (jobs must already have initialised state).
-    int run(const std::vector<JobDesc> &jobs, const std::vector<BatchItem> &items, hipStream_t s,
-            std::string &err);
+    int run(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
+    int run_mixed(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
+    int run_persistent(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
     void release();
     ~BatchRunner() { release(); }
 };
 
-// Launch shape of a job inside the batched kernel (16 waves per workgroup).
-LaunchShape batch_shape(const da_ctx *ctx);
-// The workgroup items of one job, appended to `items`.
-void append_batch_items(const JobDesc &J, int job_index, std::vector<BatchItem> &items);
+// Launch shape of a job of a batch: of the wave and team kernels (their shape is
+// chosen with the whole batch known), else inside the batched kernel (16 waves
+// per workgroup).
+LaunchShape batch_shape(const da_ctx *ctx, int32_t R, const da_schedule &s);
 
 // Storage choice for a Q (shared by da_create and admission): W = Q + Q^T off
 // the diagonal, b = diag(Q); returns DA_OK and fills dtype / wscale, or an
@@ -240,6 +245,19 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t r
 // The instance alone (W, b, sizes), for the energy kernels.
 JobDesc matrix_job(const da_ctx *ctx);
 int init_state(da_ctx *ctx, const JobDesc &J, int init, hipStream_t stream);
+// Tables a schedule needs: per-level decision tables, or, for a per-step
+// schedule (n_levels = 0), one dummy level (T = 0, empty band) plus the step
+// table and -ln U_u; for the wave and team kernels (wave) only its temperatures,
+// -ln U_u and the bound error.
+struct JobTables {
+    std::shared_ptr<LevelTables> levels;
+    std::shared_ptr<StepTables> steps;
+    std::shared_ptr<TempList> temps;
+    const double *G = nullptr;
+    float gerr = 0.0f;
+};
+int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err);
+void attach_tables(JobDesc &J, const da_schedule &sch, const JobTables &jt);
 // Outputs of a run (dense, null: not wanted) into the caller's memory; waits.
 int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o,
                          hipStream_t s);

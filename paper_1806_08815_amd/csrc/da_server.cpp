@@ -50,9 +50,8 @@ struct Job {
     int32_t dtype = 0, wscale = 1;
     int64_t footprint = 0;
     HostMatrix hm;                    // prepared, until uploaded
-    std::unique_ptr<HostTables> ht;   // prepared, until uploaded
     da_ctx *ctx = nullptr;
-    std::shared_ptr<LevelTables> tables;
+    JobTables tables;
     JobDesc J{};
     std::atomic<int64_t> done_steps{0};   // written by the worker, read by status queries
     int32_t priority = 0;
@@ -156,8 +155,6 @@ void da_server::prep_loop() {
         Job &j = *jp;
         prepare_matrix(j.Q.data(), j.spec.N, j.dtype, j.wscale, j.hm);
         std::vector<int32_t>().swap(j.Q);
-        j.ht.reset(new HostTables());
-        build_host_tables(schedule_temps(j.spec.schedule), *j.ht);
         {
             std::lock_guard<std::mutex> lock(mu);
             preparing.erase(j.ticket);
@@ -183,15 +180,14 @@ int da_server::start_job(Job &j) {
     HostMatrix().W.swap(j.hm.W);
     if (rc) return rc;
     j.ctx = ctx;
-    // (a re-admitted job's tables come from the cache, or are built again)
-    j.tables = get_level_tables(schedule_temps(j.spec.schedule), j.err, j.ht.get());
-    j.ht.reset();
-    if (!j.tables) return DA_ENOMEM;
-    ctx->keep_tables = j.tables;
+    const LaunchShape sh = batch_shape(ctx, j.spec.replicas, j.spec.schedule);
+    rc = job_tables(j.spec.schedule, j.spec.steps, sh.wave, j.tables, j.err);
+    if (rc) return rc;
+    ctx->keep_tables = j.tables.levels;
     if (!ctx->st.ensure(j.spec.replicas, ctx->ld, j.err)) return DA_ENOMEM;
-    const LaunchShape sh = batch_shape(ctx);
-    j.J = make_job(ctx, j.tables.get(), j.spec.replicas, 0u, j.spec.seed, j.spec.steps,
+    j.J = make_job(ctx, j.tables.levels.get(), j.spec.replicas, 0u, j.spec.seed, j.spec.steps,
                    j.spec.schedule, sh);
+    attach_tables(j.J, j.spec.schedule, j.tables);
     if (const char *why = job_range_error(j.J)) {
         j.err = why;
         return DA_EINVAL;
@@ -301,7 +297,7 @@ void da_server::preempt(Job &j) {
     }
     da_destroy(ctx);
     j.ctx = nullptr;
-    j.tables.reset();
+    j.tables = JobTables();
     j.preempted = true;
     j.stats.preemptions += 1;
 }
@@ -349,7 +345,7 @@ void da_server::retire(std::unique_ptr<Job> &jp) {
     }
     if (j.ctx) da_destroy(j.ctx);
     j.ctx = nullptr;
-    j.tables.reset();
+    j.tables = JobTables();
     for (auto *v : {&j.snap_x, &j.snap_bx}) std::vector<uint8_t>().swap(*v);
     for (auto *v : {&j.snap_h, &j.snap_eoff}) std::vector<int32_t>().swap(*v);
     for (auto *v : {&j.snap_E, &j.snap_bE, &j.snap_nacc}) std::vector<int64_t>().swap(*v);
@@ -485,7 +481,6 @@ void da_server::run() {
         // next epoch over every resident job, launched without waiting
         in_epoch.clear();
         jobs.clear();
-        std::vector<BatchItem> items;
         {
             std::lock_guard<std::mutex> lock(mu);
             for (auto &jp : resident) {
@@ -493,14 +488,13 @@ void da_server::run() {
                 JobDesc J = j.J;
                 J.s0 = j.done_steps;
                 J.s1 = std::min(j.spec.steps, j.done_steps + epoch_steps);
-                append_batch_items(J, (int)jobs.size(), items);
                 jobs.push_back(J);
                 in_epoch.push_back(&j);
             }
         }
         if (!jobs.empty()) {
             std::string err;
-            const int rc = runner.run(jobs, items, stream, err);
+            const int rc = runner.run(jobs, stream, err);
             if (rc) {
                 for (Job *j : in_epoch) {
                     j->status = rc;

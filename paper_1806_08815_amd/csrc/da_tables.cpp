@@ -163,8 +163,7 @@ void build_host_tables(const std::vector<double> &temps, HostTables &ht) {
     if (ht.brk.empty()) ht.brk.push_back(0);
 }
 
-std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err,
-                                              const HostTables *pre) {
+std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         err = "hipGetDevice failed";
@@ -177,28 +176,25 @@ std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, 
     if (it != g_cache.end()) {
         if (auto sp = it->second.lock()) return sp;
     }
-    HostTables own;
-    if (!pre || pre->temps != temps) {
-        build_host_tables(temps, own);
-        pre = &own;
-    }
+    HostTables ht;
+    build_host_tables(temps, ht);
     auto lt = std::make_shared<LevelTables>();
     lt->temps = temps;
     lt->L = (int32_t)temps.size();
-    lt->hdr = pre->hdr;
-    const size_t thr_b = pre->thr.size() * 4, hdr_b = pre->hdr.size() * sizeof(LevelHdr),
-                 brk_b = pre->brk.size() * 4;
-    const size_t q8_b = pre->q8.size();
+    lt->hdr = ht.hdr;
+    const size_t thr_b = ht.thr.size() * 4, hdr_b = ht.hdr.size() * sizeof(LevelHdr),
+                 brk_b = ht.brk.size() * 4;
+    const size_t q8_b = ht.q8.size();
     if (hipMalloc(&lt->d_thr, thr_b) != hipSuccess || hipMalloc(&lt->d_hdr, hdr_b) != hipSuccess ||
         hipMalloc(&lt->d_brk, brk_b) != hipSuccess ||
         (q8_b && hipMalloc(&lt->d_q8, q8_b) != hipSuccess)) {
         err = "out of device memory for level tables";
         return nullptr;
     }
-    if (hipMemcpy(lt->d_thr, pre->thr.data(), thr_b, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(lt->d_hdr, pre->hdr.data(), hdr_b, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(lt->d_brk, pre->brk.data(), brk_b, hipMemcpyHostToDevice) != hipSuccess ||
-        (q8_b && hipMemcpy(lt->d_q8, pre->q8.data(), q8_b, hipMemcpyHostToDevice) != hipSuccess)) {
+    if (hipMemcpy(lt->d_thr, ht.thr.data(), thr_b, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(lt->d_hdr, ht.hdr.data(), hdr_b, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(lt->d_brk, ht.brk.data(), brk_b, hipMemcpyHostToDevice) != hipSuccess ||
+        (q8_b && hipMemcpy(lt->d_q8, ht.q8.data(), q8_b, hipMemcpyHostToDevice) != hipSuccess)) {
         err = "upload of level tables failed";
         return nullptr;
     }

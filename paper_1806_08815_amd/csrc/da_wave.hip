@@ -32,7 +32,7 @@
 #include "da_internal.h"
 
 #ifndef DAPT_PART
-#error "compile with -DDAPT_PART=0 .. 6"
+#error "compile with -DDAPT_PART=0 .. 9"
 #endif
 
 namespace dapt {
@@ -871,11 +871,10 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     }
 }
 
-// One wave per replica, J.RPW of them per workgroup (they share W in LDS and
-// nothing else).  LDS: [W][2][64] Philox blocks per wave (F < 8).
+// One wave per replica, the J.RPW replicas from rr0 per workgroup (they share W in
+// LDS and nothing else).  LDS: [W][2][64] Philox blocks per wave (F < 8).
 template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
-__global__ __launch_bounds__(1024) void k_wave(JobDesc J) {
-    extern __shared__ __align__(16) uint8_t smem[];
+__device__ __forceinline__ void wave_block(const JobDesc &J, int rr0, uint8_t *smem) {
     int w_bytes = 0;
     if constexpr (WLDS) {
         const int n16 = J.N * J.ld * (int)sizeof(WT) / 16;
@@ -886,25 +885,72 @@ __global__ __launch_bounds__(1024) void k_wave(JobDesc J) {
         w_bytes = n16 * 16;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int rr = blockIdx.x * J.RPW + wave;
-    if (rr >= J.R) return;
-    wave_run<WT, F, 1, false, WLDS, CLAMP, FEAT>(J, rr, smem, smem + w_bytes + (F < 8 ? wave * 2048 : 0), 0);
+    if (wave >= J.RPW || rr0 + wave >= J.R) return;
+    wave_run<WT, F, 1, false, WLDS, CLAMP, FEAT>(J, rr0 + wave, smem,
+                                                 smem + w_bytes + (F < 8 ? wave * 2048 : 0), 0);
 }
 
-// One replica per workgroup: a team of J.NW waves and J.NH random-number waves.
-// HB: Philox blocks per lane of a random-number wave (0: no such waves).
+// A team of J.NW waves and J.NH random-number waves for replica rr; HB: Philox
+// blocks per lane of the latter (0: none of them).
+template <typename WT, int F, int NWC, int HB, bool CLAMP, bool FEAT>
+__device__ __forceinline__ void team_block(const JobDesc &J, int rr, uint8_t *smem) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (wave < J.NW) {
+        wave_run<WT, F, NWC, (HB > 0), false, CLAMP, FEAT>(J, rr, smem, smem, wave);
+    } else if constexpr (HB > 0) {
+        // (its lanes' blocks past N land in the padding of the ring)
+        if (wave < J.NW + J.NH)
+            team_draws<HB, CLAMP, FEAT>(J, rr, smem + 2 * team_rec_bytes<F>(J.NW), wave - J.NW);
+    }
+}
+
+template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
+__global__ __launch_bounds__(1024) void k_wave(JobDesc J) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    wave_block<WT, F, WLDS, CLAMP, FEAT>(J, blockIdx.x * J.RPW, smem);
+}
+
 template <typename WT, int F, int NWC, int HB, bool CLAMP, bool FEAT>
 __global__ __launch_bounds__(NWC > 4 ? 1024 : 512) void k_team(JobDesc J) {
     extern __shared__ __align__(16) uint8_t smem[];
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if constexpr (HB > 0) {
-        if (wave >= J.NW) {
-            // (its lanes' blocks past N land in the padding of the ring)
-            team_draws<HB, CLAMP, FEAT>(J, blockIdx.x, smem + 2 * team_rec_bytes<F>(J.NW), wave - J.NW);
-            return;
+    team_block<WT, F, NWC, HB, CLAMP, FEAT>(J, blockIdx.x, smem);
+}
+
+// Replicas of many jobs of one coupling type in one launch: every workgroup runs
+// the item of its index in its job's shape (mix_shape: at most 8 waves, the
+// waves past a shape's end at once).  The items come longest first, so the
+// launch's tail is short.
+template <typename WT, bool CLAMP, bool FEAT>
+__global__ __launch_bounds__(512) void k_mix(const JobDesc *__restrict__ jobs,
+                                             const BatchItem *__restrict__ items) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    const BatchItem it = items[blockIdx.x];
+    const JobDesc J = jobs[__builtin_amdgcn_readfirstlane(it.job)];
+    const int r0 = __builtin_amdgcn_readfirstlane(it.r0);
+    if (J.NW == 1) {
+        switch (J.F) {
+            case 1:
+                if (J.w_lds) wave_block<WT, 1, true, CLAMP, FEAT>(J, r0, smem);
+                else wave_block<WT, 1, false, CLAMP, FEAT>(J, r0, smem);
+                break;
+            case 2:
+                if (J.w_lds) wave_block<WT, 2, true, CLAMP, FEAT>(J, r0, smem);
+                else wave_block<WT, 2, false, CLAMP, FEAT>(J, r0, smem);
+                break;
+            case 4: wave_block<WT, 4, false, CLAMP, FEAT>(J, r0, smem); break;
+            case 8: wave_block<WT, 8, false, CLAMP, FEAT>(J, r0, smem); break;
+            default: wave_block<WT, 16, false, CLAMP, FEAT>(J, r0, smem); break;
         }
+    } else if (J.F == 8) {
+        if (J.NW <= 2) team_block<WT, 8, 2, 2, CLAMP, FEAT>(J, r0, smem);
+        else team_block<WT, 8, 4, 2, CLAMP, FEAT>(J, r0, smem);
+    } else if (J.NW <= 2) {
+        team_block<WT, 16, 2, 0, CLAMP, FEAT>(J, r0, smem);
+    } else if (J.NH > 0) {
+        team_block<WT, 16, 4, 2, CLAMP, FEAT>(J, r0, smem);
+    } else {
+        team_block<WT, 16, 16, 0, CLAMP, FEAT>(J, r0, smem);
     }
-    wave_run<WT, F, NWC, (HB > 0), false, CLAMP, FEAT>(J, blockIdx.x, smem, smem, wave);
 }
 
 // Launches KERNEL<.., CLAMP, FEAT> as the job needs.
@@ -975,6 +1021,24 @@ int launch_team_w(const JobDesc &J, int F, int blocks, int threads, size_t lds, 
 }
 #undef DAPT_LAUNCH
 
+template <typename WT>
+int launch_mix_w(const JobDesc *jobs, const BatchItem *items, int mode, int blocks, size_t lds,
+                 void *stream) {
+    const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    switch (mode) {
+        case 0:
+            hipLaunchKernelGGL((k_mix<WT, false, false>), dim3(blocks), dim3(512), lds, st, jobs, items);
+            break;
+        case 1:
+            hipLaunchKernelGGL((k_mix<WT, true, false>), dim3(blocks), dim3(512), lds, st, jobs, items);
+            break;
+        default:
+            hipLaunchKernelGGL((k_mix<WT, true, true>), dim3(blocks), dim3(512), lds, st, jobs, items);
+            break;
+    }
+    return (int)hipGetLastError();
+}
+
 #if DAPT_PART == 1
 template int launch_wave_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
 #elif DAPT_PART == 2
@@ -987,6 +1051,12 @@ template int launch_team_w<int8_t>(const JobDesc &, int, int, int, size_t, void 
 template int launch_team_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
 #elif DAPT_PART == 6
 template int launch_team_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
+#elif DAPT_PART == 7
+template int launch_mix_w<int8_t>(const JobDesc *, const BatchItem *, int, int, size_t, void *);
+#elif DAPT_PART == 8
+template int launch_mix_w<int16_t>(const JobDesc *, const BatchItem *, int, int, size_t, void *);
+#elif DAPT_PART == 9
+template int launch_mix_w<int32_t>(const JobDesc *, const BatchItem *, int, int, size_t, void *);
 #endif
 
 #if DAPT_PART == 0
@@ -996,6 +1066,20 @@ extern template int launch_wave_w<int32_t>(const JobDesc &, int, int, int, size_
 extern template int launch_team_w<int8_t>(const JobDesc &, int, int, int, size_t, void *);
 extern template int launch_team_w<int16_t>(const JobDesc &, int, int, int, size_t, void *);
 extern template int launch_team_w<int32_t>(const JobDesc &, int, int, int, size_t, void *);
+extern template int launch_mix_w<int8_t>(const JobDesc *, const BatchItem *, int, int, size_t, void *);
+extern template int launch_mix_w<int16_t>(const JobDesc *, const BatchItem *, int, int, size_t, void *);
+extern template int launch_mix_w<int32_t>(const JobDesc *, const BatchItem *, int, int, size_t, void *);
+
+int launch_mix(const JobDesc *jobs, const BatchItem *items, int dtype, int mode, int blocks,
+               size_t lds, void *stream) {
+    if (blocks < 1 || mode < 0 || mode > 2) return (int)hipErrorInvalidValue;
+    switch (dtype) {
+        case 1: return launch_mix_w<int8_t>(jobs, items, mode, blocks, lds, stream);
+        case 2: return launch_mix_w<int16_t>(jobs, items, mode, blocks, lds, stream);
+        case 4: return launch_mix_w<int32_t>(jobs, items, mode, blocks, lds, stream);
+        default: return (int)hipErrorInvalidValue;
+    }
+}
 
 size_t wave_lds_bytes(int F, int N, int NW, int NH, int RPW, int64_t w_lds_bytes) {
     if (NW > 1)

@@ -143,3 +143,32 @@ def test_resume(api):
             part = api.da_anneal_steps(c2, sch, 0, 5, 1000, a, b, 3)
         for k in KEYS:
             assert np.array_equal(part[k], whole[k]), (N, k)
+
+
+@pytest.mark.parametrize("fill", [0, 9000])
+def test_mixed_batch(api, fill):
+    """One launch per coupling type and mode, every shape among them; with `fill`
+    more replicas than the chip holds, in the shapes of a full chip."""
+    import torch
+    specs = [("sk", 40, 1, 9, "geometric", {}), ("gauss", 64, 0, 3, "geometric", {}),
+             ("sk", 100, 2, 5, "geometric", {}), ("q100000", 200, 0, 4, "geometric", {}),
+             ("gauss", 300, 0, 3, "geometric", {}), ("sk", 512, 0, 6, "linear_beta", {}),
+             ("cold", 600, 0, 2, "geometric", {}), ("gauss", 1024, 0, 2, "geometric", {}),
+             ("sk", 1500, 1, 2, "geometric", {}), ("gauss", 2049, 0, 2, "geometric", {}),
+             ("sk", 4200, 0, 1, "geometric", {}), ("q100", 150, 0, 5, "geometric", dict(trial="single")),
+             ("q100000", 1100, 0, 2, "geometric", {})]
+    items, alone = [], []
+    for i, (kind, N, dtype, R, sk, extra) in enumerate(specs):
+        Q, T_hi, T_lo, inc = _instance(kind, N, seed=i + 1)
+        R = fill if fill and i == 0 else R
+        S, L = 120 + 10 * i, 0 if sk == "linear_beta" else 5
+        sch = api.schedule(T_hi, T_lo, sk, L, eoff_inc=inc, init="random", **extra)
+        ctx = api.da_create(Q, dtype)
+        alone.append(api.da_anneal(ctx, sch, R, S, 50 + i))
+        items.append(dict(ctx=api.da_create(Q, dtype), schedule=sch, replicas=R, steps=S,
+                          seed=50 + i, out_dev=api.device_outputs(R, N)))
+    api.da_anneal_batch(items)
+    torch.cuda.synchronize()
+    for i, it in enumerate(items):
+        for k in KEYS:
+            assert np.array_equal(it["out_dev"][k].cpu().numpy(), alone[i][k]), (i, k)
