@@ -224,6 +224,13 @@ int launch_pt_exchange(int64_t *E, int32_t *slot2rep, int32_t *lvl_of_rep, const
 int launch_pt_setup(int32_t *slot2rep, int32_t *lvl_of_rep, int64_t *n_swaps,
                     int64_t *pair_swaps, uint32_t *round_ptr, int32_t M, int32_t chains,
                     void *stream);
+// An instance's device image from Q on the device (da_prepare.hip): first out[3] =
+// the largest |b_i| + sum_j |W_ij|, the largest |W_ij| and the common factor of all
+// couplings (0: none), then W / g padded to [ld][ld] and b [ld].
+size_t derive_scratch_bytes(int N);
+int launch_derive(const int32_t *Q, int N, uint64_t *scratch, uint64_t **out, void *stream);
+int launch_image(const int32_t *Q, int N, int ld, int dtype, int64_t g, void *W, int32_t *b,
+                 void *stream);
 // Outputs of a run into device (or pinned host) buffers, dense; null: not wanted.
 int launch_outputs(const JobDesc &J, const da_result &o, void *stream);
 int launch_fill_i32(int32_t *dst, int32_t value, int64_t n, void *stream);

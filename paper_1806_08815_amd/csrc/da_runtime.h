@@ -158,6 +158,11 @@ LaunchShape batch_shape(const da_ctx *ctx, int32_t R, const da_schedule &s);
 int derive_storage(const int32_t *Q, int32_t N, int32_t dtype_hint, int32_t &dtype,
                    int32_t &wscale, std::string &err);
 
+// The choice itself, from the largest |b_i| + sum_j |W_ij|, the largest |W_ij| and
+// the common factor g of all couplings (0: none).
+int choose_storage(int64_t maxrow, int64_t maxw, int64_t g, int32_t dtype_hint, int32_t &dtype,
+                   int32_t &wscale, std::string &err);
+
 // Host image of the device copy of W and b: W_ij = (Q_ij + Q_ji) / wscale off
 // the diagonal, zero diagonal, rows padded to ld = N rounded up to 64, dtype
 // bytes per coupling; b = diag(Q), zero padded.
@@ -175,8 +180,10 @@ int prepare_sparse(const int32_t *Q, int32_t N, HostMatrix &hm, std::string &err
 // Fills hm for a storage choice made by derive_storage.
 void prepare_matrix(const int32_t *Q, int32_t N, int32_t dtype, int32_t wscale, HostMatrix &hm);
 // New context holding hm on the current device (uploaded on stream s, which
-// is synchronised before returning).
-int create_ctx(const HostMatrix &hm, hipStream_t s, da_ctx **out, std::string &err);
+// is synchronised before returning).  Q given: hm holds no W and b (only the sizes
+// and the sparse lists), they are made on the device from Q.
+int create_ctx(const HostMatrix &hm, hipStream_t s, da_ctx **out, std::string &err,
+               const int32_t *d_Q = nullptr);
 
 }  // namespace dapt
 
