@@ -1673,7 +1673,7 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_lvl, (size_t)R * 4), "PT allocation");
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_swaps, (size_t)chains * 8), "PT allocation");
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_pair, (size_t)npair * 8), "PT allocation");
-        if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_round, 8), "PT allocation");
+        if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_round, 8 + (size_t)chains * 4), "PT allocation");
         if (!rc) rc = check_hip(ctx, hipMalloc(&ctx->pt_dbeta, (size_t)M * 8), "PT allocation");
         if (rc) return rc;
         ctx->pt_cap_R = R;
@@ -1712,6 +1712,11 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
     J.lvl_of_rep = ctx->pt_lvl;
     J.round_ptr = ctx->pt_round;
     J.K = steps_per_round;
+    // the wave and team kernels sweep the chains themselves
+    const bool sweeps = wave && M <= 64 && steps_per_round > 0;
+    if (sweeps)
+        J.pt = PtDesc{M, chains, ctx->pt_slot2rep, ctx->pt_lvl, ctx->pt_dbeta, ctx->pt_swaps,
+                      ctx->pt_pair, ctx->pt_round, ctx->pt_round + 2};
     if (const char *why = job_range_error(J)) return fail(ctx, DA_EINVAL, why);
     rc = init_state(ctx, J, DA_INIT_RANDOM, s);
     if (!rc)
@@ -1729,7 +1734,7 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
         if (steps_per_round > 0)
             e = wave ? launch_wave(J, sh.F, sh.blocks, sh.threads, sh.lds, s)
                      : launch_run(J, sh.F, sh.NH > 0, nullptr, sh.blocks, sh.threads, sh.lds, s);
-        if (!e)
+        if (!e && !sweeps)
             e = launch_pt_exchange(J.E, ctx->pt_slot2rep, ctx->pt_lvl, ctx->pt_dbeta, jt.G,
                                    M, chains, seed, ctx->pt_round, ctx->pt_swaps, ctx->pt_pair, s);
         return e;

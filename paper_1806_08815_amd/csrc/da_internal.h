@@ -86,6 +86,18 @@ struct StepT {
     int32_t tmin, tmax;
 };
 
+// Exchange sweeps of parallel tempering done by the step kernel itself: the last
+// replica of a chain to finish its round walks the chain's pairs, the last chain
+// advances the round.
+struct PtDesc {
+    int32_t M, chains;             // M = 0: no sweeps; at most 64
+    int32_t *slot2rep, *lvl_of_rep;
+    const double *dbeta;           // 1 / T_p - 1 / T_{p+1}
+    int64_t *n_swaps, *pair_swaps;
+    uint32_t *round;               // round index, chains done
+    uint32_t *done;                // [chains] replicas done
+};
+
 // Compile-time feature sets of the step kernel (see run_block).
 constexpr int kModePlain = 0, kModeSingle = 1, kModePerStep = 2, kModeDynamic = 4,
               kModeSparse = 8, kModeWide = 16, kModeDirect = 32, kModeGen = 64,
@@ -127,6 +139,7 @@ struct JobDesc {
     int32_t gth;                 // 1: random-number waves hand over per-draw estimates
     // wave and team kernels (da_wave.hip)
     int32_t F;                   // flips per lane, where launches mix jobs
+    PtDesc pt;
     const double *temps;         // temperature of each level
     float gerr;                  // error of a bound per unit of T (wave_level)
     int32_t qcap;                // most fraction bits of a fixed-point cost

@@ -1277,7 +1277,10 @@ __global__ void k_pt_setup(int32_t *slot2rep, int32_t *lvl_of_rep, int64_t *n_sw
             slot2rep[q] = q % M;
             lvl_of_rep[q] = q % M;
         }
-        if (q < chains) n_swaps[q] = 0;
+        if (q < chains) {
+            n_swaps[q] = 0;
+            round[2 + q] = 0u;
+        }
         if (q < npair) pair_swaps[q] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {

@@ -329,6 +329,81 @@ __device__ __forceinline__ void team_draws(const JobDesc &J, int rr, uint8_t *ri
     __syncthreads();                 // after the last step
 }
 
+// value of lane l
+__device__ __forceinline__ double lane_double(double v, int l) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((uint64_t)(uint32_t)readlane((int)(u >> 32), l) << 32) |
+                                            (uint32_t)readlane((int)(uint32_t)u, l)));
+}
+
+// End of a parallel-tempering round for replica rr (one wave of it; its energy is
+// stored): the last replica of the chain does the chain's exchange sweep
+// (Algorithm 3's move; k_pt_exchange is the same for more than 64 temperatures),
+// the last chain opens the next round.  Nothing waits: the others just count
+// themselves.  A kernel of its own took 6 us a round.  Lane p holds slot p; the
+// pairs are walked in order, each decision after the swaps before it.
+__device__ __forceinline__ void pt_sweep(const JobDesc &J, int rr, uint32_t t) {
+    const PtDesc &P = J.pt;
+    const int lane = threadIdx.x & 63;
+    const int M = P.M, c = rr / M;
+    uint32_t n = 0;
+    // (energies go to and come from the device's coherence point, so a wait for
+    // the store before the count is all the order this needs: a device-wide fence
+    // would write back a whole L2 for every replica)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0)
+        n = __hip_atomic_fetch_add(&P.done[c], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)n) != (uint32_t)M - 1u) return;
+    asm volatile("" ::: "memory");
+    const bool on = lane < M;
+    int rep = 0;
+    int64_t E = 0;
+    double lnu = 0.0, db = 0.0;
+    if (on) {
+        rep = P.slot2rep[(size_t)c * M + lane];
+        E = __hip_atomic_load(&J.E[(size_t)c * M + rep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t u = philox((uint32_t)lane, t, (uint32_t)c, kTagExchange, (uint32_t)J.seed,
+                                  (uint32_t)(J.seed >> 32)).x & 0xFFFFu;
+        lnu = -J.G[u];
+        db = P.dbeta[lane];
+    }
+    int a = readlane(rep, 0);   // the replica that stands in slot p
+    int64_t Ea = uniform64(E);
+    int slot = rep;             // this lane's slot after the sweep
+    bool swapped = false;
+    for (int p = 0; p + 1 < M; ++p) {
+        const int b = readlane(rep, p + 1);
+        const int64_t Eb = (int64_t)(((uint64_t)(uint32_t)readlane((int)(E >> 32), p + 1) << 32) |
+                                     (uint32_t)readlane((int)(uint32_t)(uint64_t)E, p + 1));
+        const double delta = __dmul_rn(lane_double(db, p), (double)(Ea - Eb));
+        const bool sw = lane_double(lnu, p) < delta;
+        if (lane == p) {
+            slot = sw ? b : a;
+            swapped = sw;
+        }
+        a = sw ? a : b;
+        Ea = sw ? Ea : Eb;
+    }
+    if (lane == M - 1) slot = a;
+    if (on) {
+        P.slot2rep[(size_t)c * M + lane] = slot;
+        P.lvl_of_rep[(size_t)c * M + slot] = lane;
+        if (swapped) P.pair_swaps[(size_t)c * (M - 1) + lane] += 1;
+    }
+    const int sw = (int)__popcll(ballot(swapped));
+    if (lane == 0) {
+        P.n_swaps[c] += sw;
+        P.done[c] = 0u;
+        // (every replica of every chain has read the round index before the
+        // last chain gets here)
+        if (__hip_atomic_fetch_add(&P.round[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+            (uint32_t)P.chains - 1u) {
+            P.round[1] = 0u;
+            P.round[0] = t + 1u;
+        }
+    }
+}
+
 // Runs steps [s0, s1) of replica rr by the J.NW <= NWC waves of a team (NWC = 1:
 // this wave alone; NWC = 16: any number).  wl: W in LDS (WLDS); lds: this wave's
 // Philox blocks [2][64] (alone, F < 8), or a team's records and bounds (HELP: from
@@ -412,8 +487,10 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
 
     // --- steps and level in force --------------------------------------------
     int64_t a = J.s0, b = J.s1;
+    uint32_t pt_round = 0;
     if (J.round_ptr) {
-        a = (int64_t)*J.round_ptr * J.K;
+        pt_round = (uint32_t)__builtin_amdgcn_readfirstlane((int)*J.round_ptr);
+        a = (int64_t)pt_round * J.K;
         b = a + J.K;
     }
     uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
@@ -864,10 +941,14 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
         *reinterpret_cast<BV *>(J.bx + base) = bv;
     }
     if (wr == 0 && lane == 0) {
-        J.E[rr] = bE + gap;
+        // (where another wave's sweep reads it: pt_sweep)
+        __hip_atomic_store(&J.E[rr], bE + gap, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         J.bE[rr] = bE;
         J.eoff[rr] = eoff;
         J.nacc[rr] += nacc;
+    }
+    if constexpr (!FEAT) {
+        if (J.pt.M > 0 && wr == 0) pt_sweep(J, rr, pt_round);
     }
 }
 

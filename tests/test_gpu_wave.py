@@ -172,3 +172,17 @@ def test_mixed_batch(api, fill):
     for i, it in enumerate(items):
         for k in KEYS:
             assert np.array_equal(it["out_dev"][k].cpu().numpy(), alone[i][k]), (i, k)
+
+
+# one replica, both ends of what the step kernel sweeps itself, more than that;
+# captured rounds (at least 64) and single launches; one wave and teams
+@pytest.mark.parametrize("N,M,chains,rounds,K", [
+    (60, 1, 3, 4, 30), (60, 2, 300, 66, 3), (100, 64, 2, 5, 40), (100, 65, 2, 5, 40),
+    (300, 17, 3, 70, 9), (700, 16, 2, 5, 40), (700, 5, 1, 0, 40), (60, 4, 2, 5, 0)])
+def test_tempering_sweeps(api, N, M, chains, rounds, K):
+    Q, T_hi, T_lo, _ = _instance("sk", N)
+    temps = T_lo * (T_hi / T_lo) ** (np.arange(M) / max(M - 1, 1))
+    gpu = api.da_pt(api.da_create(Q), temps, chains, rounds, K, 1, 5)
+    ref = oracle.pt(Q, temps, chains=chains, rounds=rounds, steps_per_round=K, eoff_inc=1, seed=5)
+    for k in KEYS + ("slot", "n_swaps", "pair_swaps"):
+        assert np.array_equal(np.asarray(gpu[k]).reshape(-1), np.asarray(ref[k]).reshape(-1)[:np.asarray(gpu[k]).size]), k
