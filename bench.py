@@ -59,7 +59,8 @@ def cpu_info():
     return model, os.cpu_count()
 
 
-KERNEL_SOURCES = ("paper_1806_08815_amd/csrc/da_kernels.hip", "paper_1806_08815_amd/csrc/da_internal.h")
+KERNEL_SOURCES = ("paper_1806_08815_amd/csrc/da_wave.hip", "paper_1806_08815_amd/csrc/da_device.h",
+                  "paper_1806_08815_amd/csrc/da_internal.h")
 
 
 def measured_traffic(workload: str, launch: dict):
@@ -67,7 +68,7 @@ def measured_traffic(workload: str, launch: dict):
     summary of this workload, or None when the kernel source or the launch
     shape differs from the one the counters were taken on."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", f"pmc_k_run_{workload}.md")
+    path = os.path.join(ROOT, "profiles", f"pmc_k_wave_{workload}.md")
     try:
         with open(path) as f:
             recs = [json.loads(l.split(":", 1)[1]) for l in f if l.startswith("machine-readable:")]
@@ -644,7 +645,7 @@ def main() -> int:
                           "is L2-resident)"),
             "hbm_peak": HBM_PEAK_GBS,
             "hbm_frac": achieved / HBM_PEAK_GBS,
-            "kernel": "k_run (step kernel)",
+            "kernel": "k_wave (step kernel)",
             "kernel_ms": kernel_s * 1e3,
             "bytes_per_launch": row_bytes,
             "accepted_step_fraction": float(n_acc.sum()) / (R * S),

@@ -124,8 +124,9 @@ typedef struct da_trace {
     int64_t *eoff;
 } da_trace;
 
-/* Launch-shape knobs; zero fields mean "choose automatically" (autotuned
- * table).  Results never depend on them.
+/* Launch-shape knobs of the table-driven step kernel, which a call that passes
+ * them runs on (without them a call takes the shape its sizes suggest); zero
+ * fields mean "choose automatically".  Results never depend on them.
  *   flips_per_lane      2, 4 or 8 variables per GPU lane (2: 8/16-bit
  *                       couplings only, else 4)
  *   replicas_per_block  replicas sharing one workgroup (1..16)
@@ -241,8 +242,8 @@ typedef struct da_batch_item {
 } da_batch_item;
 
 /* Run several anneals -- different instances, sizes, coupling types,
- * schedules and replica counts -- in ONE persistent kernel launch on
- * `stream`, each with exactly the outputs it would have alone.  Contexts must
+ * schedules and replica counts -- side by side on `stream`, in one launch per
+ * coupling type, each with exactly the outputs it would have alone.  Contexts must
  * be distinct and live on the current device.  Errors as da_anneal_async. */
 int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream);
 
@@ -457,7 +458,7 @@ typedef struct da_server_opts {
 } da_server_opts;
 
 /* Start a server that keeps job state resident on the current device and
- * runs every resident job in shared persistent-kernel epochs.  hbm_budget is
+ * runs every resident job in shared epochs.  hbm_budget is
  * the device memory (bytes) jobs may hold at once.  opts may be NULL. */
 int da_server_create(size_t hbm_budget, const da_server_opts *opts, da_server **out);
 

@@ -3,6 +3,10 @@
 // Method: Algorithm 2 (Sec. II.B) of Aramon et al., arXiv:1806.08815, and its
 // parallel-tempering variant (Sec. II.D, exchange move of Algorithm 3).
 //
+// The step kernel of this file serves what da_wave.hip does not take: sparse row
+// lists, step traces, launch shapes given by the caller, and instances whose
+// fields or factors are too large for its fixed point.
+//
 // Mapping of one DA step onto CDNA4:
 //   * A replica is NW wavefronts; lane g of the replica owns the F consecutive
 //     variables i0 = g*F .. g*F+F-1 and keeps their fields h (int32) and bits

@@ -1,13 +1,14 @@
-// da_wave.hip -- the Digital Annealer step with one wavefront per replica.
+// da_wave.hip -- the Digital Annealer step with every replica in one wavefront or
+// in a team of wavefronts that draw and bound for themselves.
 //
-// Method: Algorithm 2 (Sec. II.B) of Aramon et al., arXiv:1806.08815.
+// Method: Algorithm 2 (Sec. II.B) of Aramon et al., arXiv:1806.08815, and its
+// parallel-tempering rounds (Sec. II.D).
 //
-// A replica of up to 1024 variables fits one wavefront: lane g owns the F
-// variables g*F .. g*F+F-1 (F = 1, 2, 4, 8, 16).  Then nothing of a step leaves
-// the wave: no barrier, no exchange through LDS, no random-number waves.  What
-// bounds such a step is its instruction count (a wave issues one instruction
-// of any kind every four cycles), so the work is laid out to issue little and
-// to wait for nothing:
+// One wave holds a replica of up to 1024 variables: lane g owns the F variables
+// g*F .. g*F+F-1 (F = 1, 2, 4, 8, 16).  Then nothing of a step leaves the wave: no
+// barrier, no exchange through LDS, no random-number waves.  What bounds such a
+// step is its instruction count (a wave issues one instruction of any kind every
+// four cycles), so the work is laid out to issue little and to wait for nothing:
 //   * The Metropolis test is the sign of one sum per flip.  The threshold
 //     of a draw is bracketed by one fp32 log2 and multiply-add of the draw (see
 //     wave_level), and a cost inside the bracket is decided by the definition
@@ -22,6 +23,19 @@
 //   * The first rounds of Philox are constant over the steps but for two xors;
 //     the xors of the later ones are three-input.
 //   * Energy, offset and counts are wave-uniform scalars.
+// ns per step, before (compute and random-number waves on tables, da_kernels.hip)
+// and now: N = 64, 16 replicas 668 -> 194; N = 512 Gaussian, 64 replicas ~600 -> 428;
+// N = 1024 Gaussian, 1024 replicas 690 -> 657 alone (VALU instructions per
+// replica-step 359 -> 230; two anneals at once 690 -> 465 each), 2048 replicas
+// 1440 -> 1001, +-1 2190 -> 1109.
+//
+// Beyond 512 variables with few replicas the chain of one wave is too long, and a
+// team shares it (wave_run, team_draws): one barrier a step, the lanes' records and
+// the bounds of random-number waves through LDS.  What bounds it then is the chain
+// row fetch (231 ns from L2), test, scan, exchange, search: N = 1024, 128 replicas
+// 543 (direct tables, +-1), 533 (Gaussian), 718 (+-1, short levels) -> 485 .. 511;
+// dense int32 N = 999 890 -> 543; a new temperature every step 1030 -> 550; N = 8192,
+// 64 replicas 2700 -> 1110.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
