@@ -109,7 +109,7 @@ def test_common_factors(api, scale, dtype):
 # blocks, one, and none (by replicas per compute unit)
 @pytest.mark.parametrize("kind", ["sk", "gauss", "q100000"])
 @pytest.mark.parametrize("N,R", [
-    (513, 3), (600, 3), (1000, 3), (1024, 3), (999, 600), (1000, 1100),
+    (513, 3), (600, 3), (1000, 3), (1024, 3), (999, 600), (1000, 1100), (1000, 1200),
     (1025, 2), (1500, 2), (2048, 300), (1300, 1100), (1300, 1300),
     (2049, 2), (3000, 2), (4096, 2), (2100, 300), (2100, 600),
     (4097, 2), (8192, 2), (5000, 300)])
