@@ -55,11 +55,12 @@ namespace {
 
 constexpr double kLn2 = 0.69314718055994530942;
 
-// a ^ b ^ k, k wave-uniform
+// a ^ b ^ k, k wave-uniform.  (The builtin, not inline asm: round keys that were
+// spilled come back by v_readlane, after which a vector instruction may read the
+// scalar only two wait states later.  The compiler keeps these for its own
+// instructions and cannot for text.)
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k) {
-    uint32_t r;
-    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "s"(k));
-    return r;
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)k, 0x96);
 }
 
 // The Metropolis draws of one Philox block (counter (block, step, rid, 0)) over
