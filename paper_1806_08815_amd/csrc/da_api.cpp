@@ -480,7 +480,15 @@ int BatchRunner::run(const std::vector<JobDesc> &jobs, hipStream_t s, std::strin
         }
         rc = run_persistent(rest, s, err);
     }
+    if (rc) settle(s);
     return rc;
+}
+
+// Waits for whatever a failed batch has enqueued: the next batch rewrites the
+// descriptor tables, and the caller may free the jobs' memory.
+void BatchRunner::settle(hipStream_t s) {
+    (void)hipStreamSynchronize(s);
+    for (hipStream_t b : side) (void)hipStreamSynchronize(b);
 }
 
 int BatchRunner::run_mixed(const std::vector<JobDesc> &given, hipStream_t s, std::string &err) {
@@ -1601,8 +1609,10 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
     if (!rc) rc = check_hip(c0, hipEventRecord(be1, s), "event record");
     for (int32_t a = 0; a < count && !rc; ++a)
         rc = extract_outputs(items[a].ctx, jobs[(size_t)a], items[a].replicas, &items[a].out_dev, s);
-    // descriptor tables are reused by the next batch: finish this one first
-    if (!rc) rc = check_hip(c0, hipStreamSynchronize(s), "stream synchronise");
+    // descriptor tables are reused by the next batch: finish this one first, also
+    // where it failed on the way
+    const hipError_t done = hipStreamSynchronize(s);
+    if (!rc) rc = check_hip(c0, done, "stream synchronise");
     if (rc) return rc;
     for (int32_t a = 0; a < count; ++a) {
         da_ctx *ctx = items[a].ctx;

@@ -143,6 +143,7 @@ struct BatchRunner {
     int run(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
     int run_mixed(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
     int run_persistent(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
+    void settle(hipStream_t s);
     void release();
     ~BatchRunner() { release(); }
 };

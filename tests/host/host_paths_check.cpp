@@ -1,0 +1,102 @@
+// Checks of the library's host code on a device that is the host (fake_device.h):
+// what it enqueues, in which order and where, what it waits for, and what it does
+// when a call fails.  The argument names the check; exit status 0 when it holds.
+#include "fake_device.h"
+
+// the code under test, with its file-scope state in reach
+#include "da_api.cpp"
+
+#include <cstdio>
+
+static long g_bad = 0;
+#define CHECK(c)                                              \
+    do {                                                      \
+        if (!(c)) {                                           \
+            std::printf("%s:%d: %s\n", __FILE__, __LINE__, #c); \
+            ++g_bad;                                          \
+        }                                                     \
+    } while (0)
+
+// Q of N variables: +-1 couplings, or (wide) up to 300 in size, times scale.
+static std::vector<int32_t> instance(int N, bool wide = false, int32_t scale = 1) {
+    std::vector<int32_t> Q((size_t)N * N, 0);
+    uint32_t r = 12345u + (uint32_t)N;
+    for (int i = 0; i < N; ++i)
+        for (int j = i; j < N; ++j) {
+            r = r * 1664525u + 1013904223u;
+            const int32_t v = wide ? (int32_t)((r >> 8) % 601u) - 300 : ((r >> 8) & 1u ? 1 : -1);
+            Q[(size_t)i * N + j] = v * scale;
+        }
+    return Q;
+}
+static da_ctx *create(int N, bool wide = false, int32_t scale = 1, int32_t hint = 0) {
+    da_ctx *c = nullptr;
+    const std::vector<int32_t> Q = instance(N, wide, scale);
+    if (da_create(Q.data(), N, hint, &c) != DA_OK) std::printf("da_create(%d) failed\n", N), ++g_bad;
+    return c;
+}
+static da_schedule schedule(double T_hi = 30.0, double T_lo = 1.0, int32_t levels = 8) {
+    da_schedule s{};
+    s.T_hi = T_hi;
+    s.T_lo = T_lo;
+    s.kind = DA_SCHED_GEOMETRIC;
+    s.n_levels = levels;
+    s.eoff_inc = 1;
+    s.init = DA_INIT_ZEROS;
+    s.trial = DA_TRIAL_PARALLEL;
+    return s;
+}
+struct Batch {
+    std::vector<da_batch_item> items;
+    void add(da_ctx *c, int32_t replicas = 3, int64_t steps = 100) {
+        da_batch_item it{};
+        it.ctx = c;
+        it.schedule = schedule();
+        it.replicas = replicas;
+        it.steps = steps;
+        it.seed = items.size() + 1;
+        items.push_back(it);
+    }
+    int run() { return da_anneal_batch(items.data(), (int32_t)items.size(), nullptr); }
+    ~Batch() {
+        for (auto &it : items) da_destroy(it.ctx);
+    }
+};
+static bool is_launch(const fake::Call &c) { return c.name == "mix" || c.name == "hipGraphLaunch"; }
+
+// A launch of a batch fails: the call returns only when everything it enqueued
+// before is done (the kernels read tables that the next call rewrites).
+static void batch_error() {
+    Batch b;
+    b.add(create(40));
+    b.add(create(40, true));
+    b.add(create(40, true, 0, 4));
+    CHECK(b.run() == DA_OK);
+    for (int ok = 0; ok < 3; ++ok) {   // launches that go out before one fails
+        fake::reset();
+        fake::st().fail_from["mix"] = ok;
+        CHECK(b.run() != DA_OK);
+        const auto &log = fake::st().log;
+        for (size_t q = 0; q < log.size(); ++q) {
+            if (!is_launch(log[q])) continue;
+            bool waited = false;
+            for (size_t w = q + 1; w < log.size(); ++w)
+                waited = waited || log[w].name == "hipDeviceSynchronize" ||
+                         (log[w].name == "hipStreamSynchronize" && log[w].stream == log[q].stream);
+            CHECK(waited);
+        }
+    }
+    fake::reset();
+    CHECK(b.run() == DA_OK);
+}
+
+int main(int argc, char **argv) {
+    const std::map<std::string, void (*)()> checks = {
+        {"batch_error", batch_error},
+    };
+    auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
+    if (it == checks.end()) return 2;
+    it->second();
+    std::printf("failures %ld\n", g_bad);
+    return g_bad ? 1 : 0;
+}

@@ -1,0 +1,42 @@
+"""Host paths of the library on a device that is the host.
+
+`tests/host/host_paths_check.cpp` is compiled with the library's host sources
+against `tests/host/fake_device.h`, in which device memory is host memory, a
+launch leaves a line in a log, and any call can be made to fail.  So the order of
+launches, waits and copies, and what happens when one of them fails, are checked
+on the CPU.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIP_INCLUDE = "/opt/rocm/include"
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None or not os.path.exists(os.path.join(HIP_INCLUDE, "hip", "hip_runtime_api.h")):
+        pytest.skip("g++ or the HIP headers not found")
+    csrc = os.path.join(ROOT, "paper_1806_08815_amd", "csrc")
+    exe = str(tmp_path_factory.mktemp("host") / "host_paths_check")
+    b = subprocess.run([gxx, "-O1", "-g", "-std=c++17", "-D__HIP_PLATFORM_AMD__",
+                        '-DDAPT_BUILD_ID="host"', "-I", HIP_INCLUDE,
+                        "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                        os.path.join(ROOT, "tests", "host", "host_paths_check.cpp"),
+                        os.path.join(csrc, "da_tables.cpp"), "-lpthread", "-o", exe],
+                       capture_output=True, text=True, timeout=600)
+    assert b.returncode == 0, b.stderr[-4000:]
+    return exe
+
+
+@pytest.mark.parametrize("check", [
+    "batch_error",     # a failed launch of a batch: nothing is still running at the return
+])
+def test_host_path(program, check):
+    r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-4000:] + r.stderr[-2000:]
+    assert "failures 0" in r.stdout
