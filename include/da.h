@@ -242,9 +242,13 @@ typedef struct da_batch_item {
 } da_batch_item;
 
 /* Run several anneals -- different instances, sizes, coupling types,
- * schedules and replica counts -- side by side on `stream`, in one launch per
- * coupling type, each with exactly the outputs it would have alone.  Contexts must
- * be distinct and live on the current device.  Errors as da_anneal_async. */
+ * schedules and replica counts -- side by side, ordered on `stream`: one launch
+ * per coupling type and mode (levels, temperatures far from the couplings',
+ * per-step or single-trial) and one for the jobs of the table-driven kernel (sparse
+ * row lists, fields near the int32 range).  Each has exactly the outputs it would
+ * have alone.  Contexts must be distinct and live on the current device.  The call
+ * returns when the batch is done, also when it fails.  Errors as
+ * da_anneal_async. */
 int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream);
 
 /* ---- checkpoint / resume ------------------------------------------------

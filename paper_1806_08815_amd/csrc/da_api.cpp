@@ -386,9 +386,11 @@ int BatchRunner::prepare(std::string &err) {
         lds = std::max(lds, run_lds_bytes(nw, 16 / nw, 8, 0, 1, 0, true));
     if (hipMalloc(&d_jobs, sizeof(JobDesc) * kCapJobs) != hipSuccess ||
         hipMalloc(&d_items, sizeof(BatchItem) * kCapItems) != hipSuccess ||
+        hipMalloc(&d_rest, sizeof(BatchItem) * kCapItems) != hipSuccess ||
         hipMalloc(&d_n, 4) != hipSuccess || hipMalloc(&d_counter, 4) != hipSuccess ||
         hipHostMalloc(&h_jobs, sizeof(JobDesc) * kCapJobs) != hipSuccess ||
         hipHostMalloc(&h_items, sizeof(BatchItem) * kCapItems) != hipSuccess ||
+        hipHostMalloc(&h_rest, sizeof(BatchItem) * kCapItems) != hipSuccess ||
         hipHostMalloc(&h_n, 4) != hipSuccess) {
         err = "batch descriptor allocation failed";
         release();
@@ -415,7 +417,7 @@ int BatchRunner::prepare(std::string &err) {
             e = (hipError_t)launch_fill_i32(d_counter, 0, 1, cap_stream);
             if (e == hipSuccess) {
                 stage = "kernel node";
-                e = (hipError_t)launch_batch(d_jobs, d_items, d_n, d_counter, blocks, 1024, lds,
+                e = (hipError_t)launch_batch(d_jobs, d_rest, d_n, d_counter, blocks, 1024, lds,
                                              cap_stream, v == 1);
             }
             const hipError_t e2 = hipStreamEndCapture(cap_stream, &graph[v]);
@@ -458,6 +460,19 @@ int mix_weight(int N) {
 }
 }  // namespace
 
+struct BatchPlan {
+    struct Mixed {
+        int cls;        // coupling type and mode
+        int64_t cost;
+        BatchItem it;
+    };
+    std::vector<JobDesc> jobs;        // in their shapes
+    std::vector<Mixed> mixed;         // items of the wave and team kernels, class by class
+    size_t class_lds[9] = {};
+    std::vector<BatchItem> rest;      // items of the batched step kernel
+    bool dynamic = false;             // one of them needs its per-job features
+};
+
 int BatchRunner::run(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err) {
     int rc = prepare(err);
     if (rc) return rc;
@@ -465,23 +480,27 @@ int BatchRunner::run(const std::vector<JobDesc> &jobs, hipStream_t s, std::strin
         err = "too many jobs in one batch";
         return DA_EINVAL;
     }
-    std::vector<JobDesc> mixed, rest;
-    for (const JobDesc &J : jobs)
-        if (J.s1 > J.s0) (J.F > 0 ? mixed : rest).push_back(J);
-    if (!mixed.empty()) rc = run_mixed(mixed, s, err);
-    if (!rc && !rest.empty()) {
-        // (the tables are in use until the launches before are done)
-        if (!mixed.empty()) {
-            const hipError_t e = hipStreamSynchronize(s);
-            if (e != hipSuccess) {
-                err = hipGetErrorString(e);
-                return DA_EDEVICE;
-            }
-        }
-        rc = run_persistent(rest, s, err);
+    BatchPlan P;
+    P.jobs = jobs;
+    rc = plan_mixed(P, err);
+    if (rc) return rc;
+    plan_rest(P);
+    const size_t items = std::max(P.mixed.size(), P.rest.size());
+    if (items == 0) return DA_OK;
+    std::memcpy(h_jobs, P.jobs.data(), P.jobs.size() * sizeof(JobDesc));
+    hipError_t e = hipMemcpyAsync(d_jobs, h_jobs, P.jobs.size() * sizeof(JobDesc),
+                                  hipMemcpyHostToDevice, s);
+    for (size_t off = 0; off < items && e == hipSuccess; off += kCapItems) {
+        // the chunk before must be done with the item tables before they change
+        if (off) e = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = enqueue(P, off, s);
     }
-    if (rc) settle(s);
-    return rc;
+    if (e != hipSuccess) {
+        err = std::string("batch launch failed: ") + hipGetErrorString(e);
+        settle(s);
+        return DA_EDEVICE;
+    }
+    return DA_OK;
 }
 
 // Waits for whatever a failed batch has enqueued: the next batch rewrites the
@@ -491,26 +510,21 @@ void BatchRunner::settle(hipStream_t s) {
     for (hipStream_t b : side) (void)hipStreamSynchronize(b);
 }
 
-int BatchRunner::run_mixed(const std::vector<JobDesc> &given, hipStream_t s, std::string &err) {
+int BatchRunner::plan_mixed(BatchPlan &P, std::string &err) {
     int64_t waves = 0;
-    std::vector<JobDesc> jobs(given);
-    for (JobDesc &J : jobs) {
+    auto takes = [](const JobDesc &J) { return J.F > 0 && J.s1 > J.s0; };
+    for (JobDesc &J : P.jobs) {
+        if (!takes(J)) continue;
         mix_shape(J, false);
         waves += (int64_t)J.R * (J.NW + J.NH);
     }
     if (waves > 32 * (int64_t)blocks)   // more than the chip holds at once
-        for (JobDesc &J : jobs) mix_shape(J, true);
-    // classes: coupling type and mode
-    struct Item {
-        int cls;
-        int64_t cost;
-        BatchItem it;
-    };
-    std::vector<Item> order;
-    size_t class_lds[9] = {};
+        for (JobDesc &J : P.jobs)
+            if (takes(J)) mix_shape(J, true);
     int64_t class_cost[9] = {};
-    for (size_t j = 0; j < jobs.size(); ++j) {
-        const JobDesc &J = jobs[j];
+    for (size_t j = 0; j < P.jobs.size(); ++j) {
+        const JobDesc &J = P.jobs[j];
+        if (!takes(J)) continue;
         const size_t l = wave_lds_bytes(J.F, J.N, J.NW, J.NH, J.RPW,
                                         J.w_lds ? (int64_t)J.N * J.ld * J.dtype : 0);
         const char *why = job_range_error(J);
@@ -523,93 +537,74 @@ int BatchRunner::run_mixed(const std::vector<JobDesc> &given, hipStream_t s, std
         }
         const int mode = J.stepT || J.single ? 2 : J.wclamp ? 1 : 0;
         const int cls = (J.dtype == 1 ? 0 : J.dtype == 2 ? 1 : 2) * 3 + mode;
-        class_lds[cls] = std::max(class_lds[cls], l);
+        P.class_lds[cls] = std::max(P.class_lds[cls], l);
         const int64_t cost = (J.s1 - J.s0) * mix_weight(J.N);
         for (int32_t r0 = 0; r0 < J.R; r0 += J.RPW)
-            order.push_back(Item{cls, cost, BatchItem{(int32_t)j, r0}});
+            P.mixed.push_back(BatchPlan::Mixed{cls, cost, BatchItem{(int32_t)j, r0}});
         class_cost[cls] = std::max(class_cost[cls], cost);
     }
     // longest first within a class, and the class with the longest first
-    std::stable_sort(order.begin(), order.end(), [&](const Item &p, const Item &q) {
+    typedef BatchPlan::Mixed Item;
+    std::stable_sort(P.mixed.begin(), P.mixed.end(), [&](const Item &p, const Item &q) {
         if (p.cls != q.cls)
             return class_cost[p.cls] != class_cost[q.cls] ? class_cost[p.cls] > class_cost[q.cls]
                                                           : p.cls < q.cls;
         return p.cost > q.cost;
     });
-    std::memcpy(h_jobs, jobs.data(), jobs.size() * sizeof(JobDesc));
-    hipError_t e = hipMemcpyAsync(d_jobs, h_jobs, jobs.size() * sizeof(JobDesc),
-                                  hipMemcpyHostToDevice, s);
-    for (size_t off = 0; off < order.size() && e == hipSuccess; off += kCapItems) {
-        const size_t n = std::min(order.size() - off, (size_t)kCapItems);
-        // the chunk before must be done with the table before it changes
-        if (off) e = hipStreamSynchronize(s);
-        for (size_t q = 0; q < n; ++q) h_items[q] = order[off + q].it;
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_items, h_items, n * sizeof(BatchItem), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = hipEventRecord(fork, s);
-        int k = 0;   // launches of this chunk: the first on s, the others beside it
-        for (size_t q = 0; q < n && e == hipSuccess; ++k) {
-            const int cls = order[off + q].cls;
-            size_t end = q;
-            while (end < n && order[off + end].cls == cls) ++end;
-            const int b = k == 0 ? -1 : (k - 1) % kSide;
-            const hipStream_t st = b < 0 ? s : side[b];
-            if (b >= 0) e = hipStreamWaitEvent(st, fork, 0);
-            if (e == hipSuccess)
-                e = (hipError_t)launch_mix(d_jobs, d_items + q, cls / 3 == 0 ? 1 : cls / 3 == 1 ? 2 : 4,
-                                           cls % 3, (int)(end - q), class_lds[cls], st);
-            q = end;
-        }
-        for (int b = 0; b < std::min(k - 1, kSide) && e == hipSuccess; ++b) {
-            e = hipEventRecord(join[b], side[b]);
-            if (e == hipSuccess) e = hipStreamWaitEvent(s, join[b], 0);
-        }
-    }
-    if (e != hipSuccess) {
-        err = std::string("batch launch failed: ") + hipGetErrorString(e);
-        return DA_EDEVICE;
-    }
     return DA_OK;
 }
 
-int BatchRunner::run_persistent(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err) {
-    std::vector<BatchItem> items;
-    for (size_t j = 0; j < jobs.size(); ++j)
-        for (int32_t r0 = 0; r0 < jobs[j].R; r0 += jobs[j].RPW)
-            items.push_back(BatchItem{(int32_t)j, r0});
-    bool dynamic = false;
-    for (const JobDesc &J : jobs) dynamic = dynamic || J.single || J.stepT || J.ell;
+void BatchRunner::plan_rest(BatchPlan &P) {
+    for (size_t j = 0; j < P.jobs.size(); ++j) {
+        const JobDesc &J = P.jobs[j];
+        if (J.F > 0 || J.s1 <= J.s0) continue;
+        P.dynamic = P.dynamic || J.single || J.stepT || J.ell;
+        for (int32_t r0 = 0; r0 < J.R; r0 += J.RPW) P.rest.push_back(BatchItem{(int32_t)j, r0});
+    }
     // longest items first so the tail of the persistent launch is short
-    std::vector<BatchItem> order(items);
-    std::stable_sort(order.begin(), order.end(), [&](const BatchItem &p, const BatchItem &q) {
-        const JobDesc &a = jobs[(size_t)p.job], &b = jobs[(size_t)q.job];
+    std::stable_sort(P.rest.begin(), P.rest.end(), [&](const BatchItem &p, const BatchItem &q) {
+        const JobDesc &a = P.jobs[(size_t)p.job], &b = P.jobs[(size_t)q.job];
         return (a.s1 - a.s0) * a.NW > (b.s1 - b.s0) * b.NW;
     });
-    std::memcpy(h_jobs, jobs.data(), jobs.size() * sizeof(JobDesc));
-    for (size_t off = 0; off < order.size(); off += kCapItems) {
-        const size_t n = std::min(order.size() - off, (size_t)kCapItems);
-        // the previous chunk must be done with the tables before they change
-        if (off) {
-            hipError_t e = hipStreamSynchronize(s);
-            if (e != hipSuccess) {
-                err = hipGetErrorString(e);
-                return DA_EDEVICE;
-            }
-        }
-        std::memcpy(h_items, order.data() + off, n * sizeof(BatchItem));
-        *h_n = (int32_t)n;
-        hipError_t e = hipMemcpyAsync(d_jobs, h_jobs, jobs.size() * sizeof(JobDesc),
-                                      hipMemcpyHostToDevice, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_items, h_items, n * sizeof(BatchItem), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(d_n, h_n, 4, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = hipGraphLaunch(exec[dynamic ? 1 : 0], s);
-        if (e != hipSuccess) {
-            err = std::string("batch launch failed: ") + hipGetErrorString(e);
-            return DA_EDEVICE;
-        }
+}
+
+// Items off .. off + kCapItems of both tables: the persistent launch (its idle
+// workgroups end at once) and one launch per class, the first of them on s, the
+// others beside it, joined to s.
+hipError_t BatchRunner::enqueue(const BatchPlan &P, size_t off, hipStream_t s) {
+    auto in_chunk = [&](size_t n) { return n > off ? std::min(n - off, (size_t)kCapItems) : 0; };
+    const size_t nm = in_chunk(P.mixed.size()), nr = in_chunk(P.rest.size());
+    for (size_t q = 0; q < nm; ++q) h_items[q] = P.mixed[off + q].it;
+    for (size_t q = 0; q < nr; ++q) h_rest[q] = P.rest[off + q];
+    *h_n = (int32_t)nr;
+    hipError_t e = hipSuccess;
+    if (nm) e = hipMemcpyAsync(d_items, h_items, nm * sizeof(BatchItem), hipMemcpyHostToDevice, s);
+    if (nr && e == hipSuccess)
+        e = hipMemcpyAsync(d_rest, h_rest, nr * sizeof(BatchItem), hipMemcpyHostToDevice, s);
+    if (nr && e == hipSuccess) e = hipMemcpyAsync(d_n, h_n, 4, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipEventRecord(fork, s);
+    int k = 0;   // launches so far
+    if (nr && e == hipSuccess) {
+        e = hipGraphLaunch(exec[P.dynamic ? 1 : 0], s);
+        ++k;
     }
-    return DA_OK;
+    for (size_t q = 0; q < nm && e == hipSuccess; ++k) {
+        const int cls = P.mixed[off + q].cls;
+        size_t end = q;
+        while (end < nm && P.mixed[off + end].cls == cls) ++end;
+        const int b = k == 0 ? -1 : (k - 1) % kSide;
+        const hipStream_t st = b < 0 ? s : side[b];
+        if (b >= 0) e = hipStreamWaitEvent(st, fork, 0);
+        if (e == hipSuccess)
+            e = (hipError_t)launch_mix(d_jobs, d_items + q, cls / 3 == 0 ? 1 : cls / 3 == 1 ? 2 : 4,
+                                       cls % 3, (int)(end - q), P.class_lds[cls], st);
+        q = end;
+    }
+    for (int b = 0; b < std::min(k - 1, kSide) && e == hipSuccess; ++b) {
+        e = hipEventRecord(join[b], side[b]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, join[b], 0);
+    }
+    return e;
 }
 
 void BatchRunner::release() {
@@ -628,16 +623,16 @@ void BatchRunner::release() {
         side[b] = nullptr;
         join[b] = nullptr;
     }
-    for (void *p : {(void *)d_jobs, (void *)d_items, (void *)d_n, (void *)d_counter})
+    for (void *p : {(void *)d_jobs, (void *)d_items, (void *)d_rest, (void *)d_n, (void *)d_counter})
         if (p) (void)hipFree(p);
-    for (void *p : {(void *)h_jobs, (void *)h_items, (void *)h_n})
+    for (void *p : {(void *)h_jobs, (void *)h_items, (void *)h_rest, (void *)h_n})
         if (p) (void)hipHostFree(p);
     cap_stream = nullptr;
     d_jobs = nullptr;
-    d_items = nullptr;
+    d_items = d_rest = nullptr;
     d_n = d_counter = nullptr;
     h_jobs = nullptr;
-    h_items = nullptr;
+    h_items = h_rest = nullptr;
     h_n = nullptr;
 }
 

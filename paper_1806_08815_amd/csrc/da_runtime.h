@@ -113,21 +113,24 @@ struct LaunchShape {
 };
 
 // Runs batches of jobs.  Jobs of the wave and team kernels go in one launch per
-// class of coupling type and mode, side by side on streams of the runner; the
-// others (sparse row lists, fields too large for those kernels) in one persistent
-// launch of the batched step kernel.
+// class of coupling type and mode, the others (sparse row lists, fields too large
+// for those kernels) in one persistent launch of the batched step kernel, all of
+// them side by side: the first on the caller's stream, the rest on streams of the
+// runner.  Nothing waits on the host unless a batch has more than kCapItems items.
 // Descriptor tables have a fixed device capacity so that the persistent launch
 // (counter reset + kernel) is captured once as a hipGraph and replayed for every
 // batch; only the table contents are re-uploaded, from pinned host staging.
+struct BatchPlan;
 struct BatchRunner {
     static constexpr int kCapJobs = 1024;
     static constexpr int kCapItems = 65536;
     JobDesc *d_jobs = nullptr;
-    BatchItem *d_items = nullptr;
-    int32_t *d_n = nullptr;
+    BatchItem *d_items = nullptr;    // of the wave and team kernels
+    BatchItem *d_rest = nullptr;     // of the batched kernel
+    int32_t *d_n = nullptr;          // how many of the latter
     int32_t *d_counter = nullptr;
     JobDesc *h_jobs = nullptr;       // pinned
-    BatchItem *h_items = nullptr;    // pinned
+    BatchItem *h_items = nullptr, *h_rest = nullptr;   // pinned
     int32_t *h_n = nullptr;          // pinned
     int blocks = 0;
     size_t lds = 0;
@@ -141,8 +144,9 @@ struct BatchRunner {
     int prepare(std::string &err);
     // Enqueues the batch on `s` (jobs must already have initialised state).
     int run(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
-    int run_mixed(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
-    int run_persistent(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
+    int plan_mixed(BatchPlan &P, std::string &err);
+    void plan_rest(BatchPlan &P);
+    hipError_t enqueue(const BatchPlan &P, size_t off, hipStream_t s);
     void settle(hipStream_t s);
     void release();
     ~BatchRunner() { release(); }

@@ -35,7 +35,8 @@ struct State {
     size_t memory = SIZE_MAX, used = 0;      // device memory, and what is allocated
     std::map<void *, size_t> live;
     hipError_t last = hipSuccess;            // as hipGetLastError keeps it
-    std::vector<std::vector<dapt::JobDesc>> mix_jobs;   // what each mixed launch ran
+    std::vector<int> mix_blocks;             // workgroups of each mixed launch
+    std::vector<dapt::JobDesc> mix_jobs;     // the jobs they ran
     uintptr_t handles = 0x1000;
 };
 inline State &st() {
@@ -70,6 +71,7 @@ inline void reset() {
     std::lock_guard<std::recursive_mutex> lock(st().mu);
     st().log.clear();
     st().fail_from.clear();
+    st().mix_blocks.clear();
     st().mix_jobs.clear();
     st().memory = SIZE_MAX;
     st().last = hipSuccess;
@@ -96,7 +98,7 @@ hipError_t hipMalloc(void **p, size_t n) {
 }
 hipError_t hipFree(void *p) {
     std::lock_guard<std::recursive_mutex> lock(fake::st().mu);
-    fake::note("hipFree");
+    (void)fake::note("hipFree");
     auto it = fake::st().live.find(p);
     if (it == fake::st().live.end()) return p ? hipErrorInvalidValue : hipSuccess;
     fake::st().used -= it->second;
@@ -192,11 +194,12 @@ int launch_run(const JobDesc &, int, bool, const TraceDesc *, int, int, size_t, 
 size_t wave_lds_bytes(int, int, int, int, int, int64_t w) { return (size_t)w; }
 int launch_wave(const JobDesc &, int, int, int, size_t, void *s) { return launched("wave", s); }
 int launch_mix(const JobDesc *jobs, const BatchItem *items, int, int, int blocks, size_t, void *s) {
-    std::vector<JobDesc> ran;
-    for (int q = 0; q < blocks; ++q) ran.push_back(jobs[items[q].job]);
     {
         std::lock_guard<std::recursive_mutex> lock(fake::st().mu);
-        fake::st().mix_jobs.push_back(std::move(ran));
+        fake::st().mix_blocks.push_back(blocks);
+        for (int q = 0; q < blocks; ++q)
+            if (q == 0 || items[q].job != items[q - 1].job)
+                fake::st().mix_jobs.push_back(jobs[items[q].job]);
     }
     return launched("mix", s);
 }

@@ -90,9 +90,75 @@ static void batch_error() {
     CHECK(b.run() == DA_OK);
 }
 
+// Jobs of the wave kernels and of the table-driven kernel in one batch: launched
+// side by side, without a wait on the host between, and joined to one stream.
+static void batch_overlap() {
+    Batch b;
+    b.add(create(40));
+    b.add(create(41, true, 1, 2));
+    b.add(create(60, false, 1, DA_STORE_SPARSE));
+    b.add(create(42, false, 1 << 16, 2));      // its factor is past 16 bits
+    fake::reset();
+    CHECK(b.run() == DA_OK);
+    CHECK(fake::count("mix") == 2 && fake::count("hipGraphLaunch") == 1);
+    const auto &log = fake::st().log;
+    std::vector<size_t> at;
+    for (size_t q = 0; q < log.size(); ++q)
+        if (is_launch(log[q])) at.push_back(q);
+    for (size_t q = at.front(); q < at.back(); ++q)
+        CHECK(log[q].name != "hipStreamSynchronize" && log[q].name != "hipDeviceSynchronize");
+    const void *s = nullptr;   // the caller's stream: the outputs leave on it
+    size_t out = log.size();
+    for (size_t q = 0; q < log.size(); ++q)
+        if (log[q].name == "outputs" && out == log.size()) s = log[out = q].stream;
+    for (size_t q : at) {
+        for (size_t r : at) CHECK(q == r || log[q].stream != log[r].stream);
+        if (log[q].stream == s) continue;
+        const void *ev = nullptr;   // recorded behind the launch, waited for on s
+        for (size_t w = q + 1; w < out && !ev; ++w)
+            if (log[w].name == "hipEventRecord" && log[w].stream == log[q].stream) ev = log[w].event;
+        bool joined = false;
+        for (size_t w = q + 1; w < out; ++w)
+            joined = joined || (log[w].name == "hipStreamWaitEvent" && log[w].stream == s &&
+                                log[w].event == ev);
+        CHECK(ev && joined);
+    }
+}
+
+// More items than the tables hold: chunk by chunk, each after the one before.
+static void batch_chunks() {
+    Batch b;
+    const int32_t R = 1200000;
+    b.add(create(1), R);
+    b.add(create(1, false, 1, DA_STORE_SPARSE), R);
+    fake::reset();
+    CHECK(b.run() == DA_OK);
+    const size_t per_item = 4;   // replicas of N = 1 per item of the mixed launches
+    size_t items = 0;
+    for (int n : fake::st().mix_blocks) {
+        CHECK(n <= BatchRunner::kCapItems);
+        items += (size_t)n;
+    }
+    CHECK(items == (R + per_item - 1) / per_item);
+    // (16 replicas per item of the persistent launches)
+    CHECK(fake::count("hipGraphLaunch") ==
+          (R / 16 + BatchRunner::kCapItems - 1) / BatchRunner::kCapItems);
+    const auto &log = fake::st().log;
+    for (size_t q = 0; q < log.size(); ++q) {
+        if (!is_launch(log[q])) continue;
+        bool waited = false;   // before a table is written again
+        for (size_t w = q + 1; w < log.size(); ++w) {
+            waited = waited || log[w].name == "hipStreamSynchronize";
+            CHECK(waited || log[w].name != "hipMemcpyAsync");
+        }
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
+        {"batch_overlap", batch_overlap},
+        {"batch_chunks", batch_chunks},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;
