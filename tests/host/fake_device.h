@@ -138,7 +138,9 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int) {
     return hipSuccess;
 }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
+    std::memset(p, 0, sizeof *p);
     std::strcpy(p->gcnArchName, "gfx950");
+    p->sharedMemPerBlock = 163840;
     return hipSuccess;
 }
 hipError_t hipGetLastError(void) {
