@@ -485,6 +485,7 @@ int BatchRunner::run(const std::vector<JobDesc> &jobs, hipStream_t s, std::strin
     rc = plan_mixed(P, err);
     if (rc) return rc;
     plan_rest(P);
+    note_shapes(P);
     const size_t items = std::max(P.mixed.size(), P.rest.size());
     if (items == 0) return DA_OK;
     std::memcpy(h_jobs, P.jobs.data(), P.jobs.size() * sizeof(JobDesc));
@@ -566,6 +567,29 @@ void BatchRunner::plan_rest(BatchPlan &P) {
         const JobDesc &a = P.jobs[(size_t)p.job], &b = P.jobs[(size_t)q.job];
         return (a.s1 - a.s0) * a.NW > (b.s1 - b.s0) * b.NW;
     });
+}
+
+// What each job runs in, as da_last_kernel_stats reports it: its class's launch of
+// 512 threads a workgroup, or the persistent launch.
+void BatchRunner::note_shapes(const BatchPlan &P) {
+    int class_blocks[9] = {};
+    for (const BatchPlan::Mixed &m : P.mixed) ++class_blocks[m.cls];
+    std::vector<int> cls(P.jobs.size(), -1);
+    for (const BatchPlan::Mixed &m : P.mixed) cls[(size_t)m.it.job] = m.cls;
+    shapes.assign(P.jobs.size(), LaunchShape());
+    for (size_t j = 0; j < P.jobs.size(); ++j) {
+        const JobDesc &J = P.jobs[j];
+        LaunchShape &sh = shapes[j];
+        sh.wave = J.F > 0;
+        sh.F = sh.wave ? J.F : 8;
+        sh.NW = J.NW;
+        sh.NH = J.NH;
+        sh.RPW = J.RPW;
+        sh.w_lds = J.w_lds;
+        sh.gen = sh.wave || (J.gth && !P.dynamic) ? 1 : 0;
+        sh.threads = sh.wave ? 512 : 1024;
+        sh.blocks = J.s1 <= J.s0 ? 0 : sh.wave ? class_blocks[cls[j]] : blocks;
+    }
 }
 
 // Items off .. off + kCapItems of both tables: the persistent launch (its idle
@@ -1585,7 +1609,6 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
         if (const char *why = job_range_error(jobs[(size_t)a])) return fail(ctx, DA_EINVAL, why);
         rc = init_state(ctx, jobs[(size_t)a], it.schedule.init, s);
         if (rc) return rc;
-        record_stats(ctx, sh, 1, sh.wave ? 1 : 0);
     }
     da_ctx *c0 = items[0].ctx;
     // process-lifetime runner (never destroyed: no device frees at exit)
@@ -1601,6 +1624,8 @@ int da_anneal_batch(const da_batch_item *items, int32_t count, void *stream) {
         rc = runner.run(jobs, s, err);
         if (rc) fail(c0, rc, err);
     }
+    for (int32_t a = 0; a < count && !rc; ++a)
+        record_stats(items[a].ctx, runner.shapes[(size_t)a], 1, runner.shapes[(size_t)a].gen);
     if (!rc) rc = check_hip(c0, hipEventRecord(be1, s), "event record");
     for (int32_t a = 0; a < count && !rc; ++a)
         rc = extract_outputs(items[a].ctx, jobs[(size_t)a], items[a].replicas, &items[a].out_dev, s);

@@ -141,11 +141,13 @@ struct BatchRunner {
     // [0]: plain DA step kernel; [1]: the variant reading per-job features
     hipGraph_t graph[2] = {nullptr, nullptr};
     hipGraphExec_t exec[2] = {nullptr, nullptr};
+    std::vector<LaunchShape> shapes;   // of the last run's jobs, as launched
     int prepare(std::string &err);
     // Enqueues the batch on `s` (jobs must already have initialised state).
     int run(const std::vector<JobDesc> &jobs, hipStream_t s, std::string &err);
     int plan_mixed(BatchPlan &P, std::string &err);
     void plan_rest(BatchPlan &P);
+    void note_shapes(const BatchPlan &P);
     hipError_t enqueue(const BatchPlan &P, size_t off, hipStream_t s);
     void settle(hipStream_t s);
     void release();

@@ -154,11 +154,46 @@ static void batch_chunks() {
     }
 }
 
+// da_last_kernel_stats after a batch states the launch each job went in: that of
+// its descriptor, in a batch that fits the chip and in one that fills it.
+static void batch_stats() {
+    for (int32_t many : {3, 40000}) {
+        Batch b;
+        b.add(create(40), many);
+        b.add(create(100, true, 1, 2));
+        b.add(create(700), 5);
+        b.add(create(3000), 2);
+        b.add(create(60, false, 1, DA_STORE_SPARSE));
+        for (auto &it : b.items)   // (a batch is timed on its first context only)
+            CHECK(da_anneal_async(it.ctx, &it.schedule, 0, 1, 10, 1, nullptr, nullptr, nullptr) ==
+                  DA_OK);
+        fake::reset();
+        CHECK(b.run() == DA_OK);
+        for (auto &it : b.items) {
+            da_kernel_stats st{};
+            CHECK(da_last_kernel_stats(it.ctx, &st) == DA_OK);
+            bool found = false;
+            size_t launch = 0;
+            for (const JobDesc &J : fake::st().mix_jobs) {
+                if (J.seed != it.seed) continue;
+                found = true;
+                CHECK(st.flips_per_lane == J.F && st.rng_waves == J.NH && st.w_in_lds == J.w_lds);
+                CHECK(st.replicas_per_block == J.RPW && st.threads == 512 && st.draw_estimates == 1);
+                for (int n : fake::st().mix_blocks) launch += st.blocks == n ? 1 : 0;
+                CHECK(launch > 0 && st.blocks >= (it.replicas + J.RPW - 1) / J.RPW);
+            }
+            if (!found) CHECK(st.flips_per_lane == 8 && st.threads == 1024 && st.blocks == 256);
+            CHECK(found == (it.ctx->ell_D == 0));
+        }
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
         {"batch_overlap", batch_overlap},
         {"batch_chunks", batch_chunks},
+        {"batch_stats", batch_stats},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;
