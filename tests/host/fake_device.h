@@ -106,6 +106,14 @@ hipError_t hipFree(void *p) {
     std::free(p);
     return hipSuccess;
 }
+hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) { return hipMalloc(p, n); }
+hipError_t hipFreeAsync(void *p, hipStream_t s) {
+    std::lock_guard<std::recursive_mutex> lock(fake::st().mu);
+    const hipError_t e = hipFree(p);
+    fake::st().log.back().name = "hipFreeAsync";
+    fake::st().log.back().stream = s;
+    return e;
+}
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
     const hipError_t e = fake::note("hipHostMalloc", nullptr, nullptr, hipErrorOutOfMemory);
     if (e == hipSuccess) *p = std::malloc(n);

@@ -188,12 +188,25 @@ static void batch_stats() {
     }
 }
 
+// da_create waits for its own work only: no call that waits for the device.
+static void create_waits() {
+    for (int N : {100, 300}) {
+        fake::reset();
+        da_ctx *c = create(N);
+        CHECK(fake::count("hipFree") == 0 && fake::count("hipDeviceSynchronize") == 0);
+        const size_t held = fake::st().used;
+        da_destroy(c);
+        CHECK(held >= (size_t)N * N && held < 2 * (size_t)N * N + 65536 && fake::st().used == 0);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
         {"batch_overlap", batch_overlap},
         {"batch_chunks", batch_chunks},
         {"batch_stats", batch_stats},
+        {"create_waits", create_waits},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;

@@ -68,3 +68,22 @@ def test_refused(api, N):
     with pytest.raises(api.DaError) as e:
         api.da_create(Q, 1)
     assert "requested type" in str(e.value)
+
+
+def test_beside_a_running_anneal(api):
+    """An instance made while another context's anneal runs does not wait for it."""
+    import torch
+    Q = _q("g1", 300)
+    api.da_create(Q)
+    big = api.da_create(_q("g1", 1024))
+    sch = api.schedule(300.0, 3.0, "geometric", 16, 1)
+    out, stream, done = api.device_outputs(8, 1024), torch.cuda.Stream(), torch.cuda.Event()
+    api.da_anneal_async(big, sch, 0, 8, 1000, 1, None, out, stream)
+    torch.cuda.synchronize()
+    api.da_anneal_async(big, sch, 0, 8, 1_000_000, 1, None, out, stream)   # about half a second
+    done.record(stream)
+    ctx = api.da_create(Q)
+    assert not done.query()
+    torch.cuda.synchronize()
+    x = np.ones((1, 300), np.uint8)
+    assert api.da_energy(ctx, x)[0] == Q.astype(np.int64).sum()
