@@ -193,6 +193,8 @@ typedef struct da_info {
  * takes out the greatest common divisor of W as wscale, stores W/wscale in
  * dtype_hint (or the smallest exact type for DA_DTYPE_AUTO) and uploads W and
  * b to the current HIP device; with DA_STORE_SPARSE also the sparse row lists.
+ * While it runs it uses 4 N^2 bytes of device memory more where they are free
+ * (the host does that work otherwise).
  * Errors: DA_EINVAL (null, N < 1, N > DA_MAX_N, bad hint), DA_ERANGE
  * (max_i |b_i| + sum_j |W_ij| > 2^30, W/wscale does not fit the forced type,
  * or a sparse list out of range), DA_ENOMEM, DA_EDEVICE (no gfx950 device). */

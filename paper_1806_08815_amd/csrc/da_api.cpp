@@ -1338,7 +1338,7 @@ int da_create(const int32_t *Q, int32_t N, int32_t dtype_hint, da_ctx **out) {
 
     // Small instances on the host: the device's answer takes a round trip (N = 64:
     // 98 us against 141, N = 512: 976 against 194, N = 8192: 382 ms against 10)
-    if (N <= 128) {
+    auto on_host = [&]() -> int {
         HostMatrix hm;
         int32_t dtype = 0, wscale = 1;
         int rc = derive_storage(Q, N, dtype_hint, dtype, wscale, err);
@@ -1348,17 +1348,20 @@ int da_create(const int32_t *Q, int32_t N, int32_t dtype_hint, da_ctx **out) {
         }
         if (!rc) rc = create_ctx(hm, nullptr, out, err);
         return rc ? fail(nullptr, rc, err) : DA_OK;
-    }
+    };
+    if (N <= 128) return on_host();
     // Q and the derivation's scratch, on the device for the length of this call.
-    // Ordered on the stream (and given back when it is next waited for): hipFree
-    // waits for everything that runs on the device, other contexts' anneals too
-    // (N = 512 beside an anneal of 414 ms: 414 ms with it)
+    // Ordered on the stream and given back when that is waited for: hipFree waits
+    // for everything that runs on the device, other contexts' anneals too (N = 512
+    // beside an anneal of 414 ms: 414 ms with it).  Where it does not fit beside the
+    // image, the host derives
     const size_t q_bytes = (size_t)N * (size_t)N * 4;
     const size_t q_pad = (q_bytes + 255) & ~(size_t)255;
     char *d = nullptr;
-    int rc = check_hip(nullptr, hipMallocAsync((void **)&d, q_pad + derive_scratch_bytes(N), nullptr),
-                       "instance upload buffer");
-    if (rc) return rc;
+    if (hipMallocAsync((void **)&d, q_pad + derive_scratch_bytes(N), nullptr) != hipSuccess) {
+        (void)hipGetLastError();   // (or the next launch reports it)
+        return on_host();
+    }
     const int32_t *d_Q = reinterpret_cast<const int32_t *>(d);
     uint64_t *res = nullptr, host[3] = {0, 0, 0};
     hipError_t e = hipMemcpyAsync(d, Q, q_bytes, hipMemcpyHostToDevice, nullptr);
@@ -1366,7 +1369,7 @@ int da_create(const int32_t *Q, int32_t N, int32_t dtype_hint, da_ctx **out) {
         e = (hipError_t)launch_derive(d_Q, N, reinterpret_cast<uint64_t *>(d + q_pad), &res, nullptr);
     if (e == hipSuccess) e = hipMemcpyAsync(host, res, sizeof host, hipMemcpyDeviceToHost, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    rc = check_hip(nullptr, e, "instance derivation");
+    int rc = check_hip(nullptr, e, "instance derivation");
     HostMatrix hm;
     hm.N = N;
     hm.ld = (N + 63) / 64 * 64;
@@ -1378,9 +1381,11 @@ int da_create(const int32_t *Q, int32_t N, int32_t dtype_hint, da_ctx **out) {
         if (!rc) rc = create_ctx(hm, nullptr, out, err, d_Q);
         if (rc) fail(nullptr, rc, err);
     }
-    e = hipFreeAsync(d, nullptr);
-    if (!rc) rc = check_hip(nullptr, e, "instance upload buffer");
-    return rc;
+    (void)hipFreeAsync(d, nullptr);
+    (void)hipStreamSynchronize(nullptr);
+    if (rc != DA_ENOMEM) return rc;
+    (void)hipGetLastError();
+    return on_host();
 }
 
 void da_destroy(da_ctx *ctx) {

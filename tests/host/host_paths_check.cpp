@@ -200,6 +200,40 @@ static void create_waits() {
     }
 }
 
+// da_create where the image fits but not the upload buffer, alone or beside it:
+// the same instance, and no error left for the next call's launches.
+static void create_memory() {
+    const int N = 300, ld = 320;
+    const std::vector<int32_t> Q = instance(N, true);
+    const size_t image = (size_t)ld * ld * 2 + ld * 4;
+    for (size_t room : {image, (size_t)N * N * 4 + derive_scratch_bytes(N) + 60000}) {
+        fake::reset();
+        fake::st().memory = fake::st().used + room;
+        da_ctx *c = nullptr;
+        CHECK(da_create(Q.data(), N, 0, &c) == DA_OK);
+        fake::st().memory = SIZE_MAX;
+        if (!c) continue;
+        CHECK(c->dtype == 2 && c->wscale == 1);
+        const int16_t *W = static_cast<const int16_t *>(c->d_W);
+        for (int i = 0; i < ld; ++i)
+            for (int j = 0; j < ld; ++j) {
+                const int32_t w = i < N && j < N && i != j
+                                      ? Q[(size_t)i * N + j] + Q[(size_t)j * N + i] : 0;
+                CHECK(W[(size_t)i * ld + j] == w);
+            }
+        for (int i = 0; i < N; ++i) CHECK(c->d_b[i] == Q[(size_t)i * N + i]);
+        const da_schedule s = schedule();
+        CHECK(da_anneal_async(c, &s, 0, 1, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+        da_destroy(c);
+    }
+    // not even the image fits
+    fake::reset();
+    fake::st().memory = fake::st().used + image / 2;
+    da_ctx *c = nullptr;
+    CHECK(da_create(Q.data(), N, 0, &c) == DA_ENOMEM && c == nullptr);
+    fake::st().memory = SIZE_MAX;
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -207,6 +241,7 @@ int main(int argc, char **argv) {
         {"batch_chunks", batch_chunks},
         {"batch_stats", batch_stats},
         {"create_waits", create_waits},
+        {"create_memory", create_memory},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;

@@ -39,6 +39,7 @@ def program(tmp_path_factory):
     "batch_chunks",    # more items than the tables hold
     "batch_stats",     # the launch shapes reported after a batch
     "create_waits",    # an instance made beside running anneals
+    "create_memory",   # and with little device memory left
 ])
 def test_host_path(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
