@@ -1125,18 +1125,16 @@ PinnedBlocks &pinned_blocks() {
     return *p;
 }
 
-// Outputs to the caller's memory.  A kernel writes them densely, up to 1 MiB
-// into a pinned block itself (one launch and one wait), more into a device
-// buffer of the context that contiguous copies leave from: strided copies to
-// pageable memory go row by row (2048 rows of 1024 bytes took 26 ms).
 }  // namespace
 
 // Outputs to the caller's memory.  A kernel writes them densely, up to 1 MiB
-// into a pinned block itself (one launch and one wait), more into a device
-// buffer of the context that contiguous copies leave from: strided copies to
-// pageable memory go row by row (2048 rows of 1024 bytes took 26 ms).
+// into a pinned block itself (one launch and one wait), more into device memory
+// that contiguous copies leave from: strided copies to pageable memory go row by
+// row (2048 rows of 1024 bytes took 26 ms).  That device memory is `scratch`, where
+// the caller has enough to spare, or allocated in stream order for this call; where
+// there is none, the rows are copied one by one.
 int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o,
-                         hipStream_t s) {
+                         hipStream_t s, void *scratch, size_t scratch_bytes) {
     const size_t nE = (size_t)R * 8, nx = (size_t)R * (size_t)J.N;
     const size_t bytes = 3 * nE + 2 * nx;
     JobDesc K = J;
@@ -1152,16 +1150,31 @@ int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_resu
         return d;
     };
     void *pin = bytes <= PinnedBlocks::kBytes ? pinned_blocks().take() : nullptr;
-    if (!pin && bytes > ctx->out_cap) {
-        if (ctx->d_out) (void)hipFree(ctx->d_out);
-        ctx->d_out = nullptr;
-        ctx->out_cap = 0;
-        const int rc = check_hip(ctx, hipMalloc(&ctx->d_out, bytes), "output buffer allocation");
-        if (rc) return rc;
-        ctx->out_cap = bytes;
+    void *at = pin ? pin : bytes <= scratch_bytes ? scratch : nullptr, *own = nullptr;
+    if (!at) {
+        if (hipMallocAsync(&own, bytes, s) == hipSuccess) at = own;
+        else (void)hipGetLastError();   // (or the next launch reports it)
     }
-    const da_result d = parts(pin ? pin : ctx->d_out);
-    hipError_t e = (hipError_t)launch_outputs(K, d, s);
+    hipError_t e = hipSuccess;
+    if (!at) {
+        auto rows = [&](uint8_t *dst, const uint8_t *src) {
+            if (dst && e == hipSuccess)
+                e = hipMemcpy2DAsync(dst, (size_t)J.N, src, (size_t)J.ld, (size_t)J.N, (size_t)R,
+                                     hipMemcpyDeviceToHost, s);
+        };
+        auto words = [&](int64_t *dst, const int64_t *src) {
+            if (dst && e == hipSuccess) e = hipMemcpyAsync(dst, src, nE, hipMemcpyDeviceToHost, s);
+        };
+        rows(o->best_x, J.bx);
+        rows(o->final_x, J.x);
+        words(o->best_E, J.bE);
+        words(o->final_E, J.E);
+        words(o->n_accept, J.nacc);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        return check_hip(ctx, e, "copy of outputs to host");
+    }
+    const da_result d = parts(at);
+    e = (hipError_t)launch_outputs(K, d, s);
     if (pin && e == hipSuccess) e = hipStreamSynchronize(s);
     auto copy = [&](void *dst, const void *src, size_t n) {
         if (!dst || e != hipSuccess) return;
@@ -1173,6 +1186,7 @@ int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_resu
     copy(o->n_accept, d.n_accept, nE);
     copy(o->best_x, d.best_x, nx);
     copy(o->final_x, d.final_x, nx);
+    if (own) (void)hipFreeAsync(own, s);
     if (pin) pinned_blocks().give(pin);
     else if (e == hipSuccess) e = hipStreamSynchronize(s);
     return check_hip(ctx, e, "copy of outputs to host");
@@ -1396,7 +1410,6 @@ void da_destroy(da_ctx *ctx) {
     if (ctx->d_W) (void)hipFree(ctx->d_W);
     if (ctx->d_b) (void)hipFree(ctx->d_b);
     if (ctx->d_ell) (void)hipFree(ctx->d_ell);
-    if (ctx->d_out) (void)hipFree(ctx->d_out);
     for (void *p : {(void *)ctx->pt_slot2rep, (void *)ctx->pt_lvl, (void *)ctx->pt_swaps,
                     (void *)ctx->pt_pair, (void *)ctx->pt_round, (void *)ctx->pt_dbeta})
         if (p) (void)hipFree(p);
@@ -1806,7 +1819,8 @@ int pt_run(da_ctx *ctx, const double *temps, int32_t M, int32_t chains, int64_t 
 
     if (out) {
         da_result o{out->best_x, out->best_E, out->final_x, out->final_E, out->n_accept};
-        rc = copy_outputs_to_host(ctx, J, R, &o, s);
+        // (a round's fields serve nothing once it is over)
+        rc = copy_outputs_to_host(ctx, J, R, &o, s, J.h, (size_t)R * (size_t)J.ld * 4);
         hipError_t e = hipSuccess;
         if (!rc && out->slot) e = hipMemcpy(out->slot, ctx->pt_lvl, (size_t)R * 4, hipMemcpyDeviceToHost);
         if (e == hipSuccess && !rc && out->n_swaps)

@@ -226,8 +226,6 @@ struct da_ctx {
     std::shared_ptr<dapt::LevelTables> keep_tables;
     std::shared_ptr<dapt::StepTables> keep_steps;
     std::shared_ptr<dapt::TempList> keep_temps;
-    int64_t *d_out = nullptr;    // outputs on their way to the host, dense
-    size_t out_cap = 0;          // its bytes
     // what the replica state in `st` holds: replicas st_base .. st_base+st_R-1
     // after st_step steps (st_step < 0: nothing resumable)
     int64_t st_step = -1;
@@ -273,8 +271,9 @@ struct JobTables {
 int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err);
 void attach_tables(JobDesc &J, const da_schedule &sch, const JobTables &jt);
 // Outputs of a run (dense, null: not wanted) into the caller's memory; waits.
+// scratch: device memory of the caller's that may be overwritten.
 int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_result *o,
-                         hipStream_t s);
+                         hipStream_t s, void *scratch = nullptr, size_t scratch_bytes = 0);
 // Event pair for the next timed call (from the context's pool).
 int next_events(da_ctx *ctx, hipEvent_t &e0, hipEvent_t &e1);
 std::vector<double> schedule_temps(const da_schedule &s);

@@ -337,7 +337,9 @@ void da_server::retire(std::unique_ptr<Job> &jp) {
         j.n_accept.resize(R);
         const da_result o{j.best_x.data(), j.best_E.data(), j.final_x.data(), j.final_E.data(),
                           j.n_accept.data()};
-        const int rc = copy_outputs_to_host(j.ctx, j.J, (int32_t)R, &o, stream);
+        // (through the fields' memory: the job is over, and its budget used up)
+        const int rc = copy_outputs_to_host(j.ctx, j.J, (int32_t)R, &o, stream, j.J.h,
+                                            R * (size_t)j.J.ld * 4);
         if (rc) {
             j.status = rc;
             j.err = j.ctx->err;

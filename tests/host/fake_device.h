@@ -202,7 +202,18 @@ int launch_run(const JobDesc &, int, bool, const TraceDesc *, int, int, size_t, 
     return launched("run", s);
 }
 size_t wave_lds_bytes(int, int, int, int, int, int64_t w) { return (size_t)w; }
-int launch_wave(const JobDesc &, int, int, int, size_t, void *s) { return launched("wave", s); }
+int launch_wave(const JobDesc &J, int, int, int, size_t, void *s) {
+    for (int32_t r = 0; r < J.R; ++r) {   // some state
+        J.E[r] = 3 * r;
+        J.bE[r] = -r;
+        J.nacc[r] = 7 * r;
+        for (int32_t i = 0; i < J.N; ++i) {
+            J.x[(size_t)r * J.ld + i] = (uint8_t)((r + i) % 3);
+            J.bx[(size_t)r * J.ld + i] = (uint8_t)((r ^ i) % 5);
+        }
+    }
+    return launched("wave", s);
+}
 int launch_mix(const JobDesc *jobs, const BatchItem *items, int, int, int blocks, size_t, void *s) {
     {
         std::lock_guard<std::recursive_mutex> lock(fake::st().mu);

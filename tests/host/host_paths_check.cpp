@@ -234,6 +234,62 @@ static void create_memory() {
     fake::st().memory = SIZE_MAX;
 }
 
+// Outputs of an anneal or of tempering on their way to the host, more than a
+// pinned block holds: whole, with and without device memory to spare, and with no
+// device memory kept that da_get_info leaves out, nor a wait for the device.
+static void outputs_memory() {
+    const int N = 300, R = 3000;
+    std::vector<uint8_t> bx((size_t)R * N), x((size_t)R * N);
+    std::vector<int64_t> bE(R), E(R), n(R);
+    const da_result all{bx.data(), bE.data(), x.data(), E.data(), n.data()};
+    da_ctx *c = create(N);
+    const da_schedule s = schedule();
+    auto no_outputs = [&] {
+        return da_anneal_async(c, &s, 0, R, 10, 1, nullptr, nullptr, nullptr);
+    };
+    CHECK(no_outputs() == DA_OK);   // state and tables are there
+    const double T[2] = {1.0, 2.0};
+    auto whole = [&] {
+        for (int r = 0; r < R; ++r) {
+            CHECK(E[r] == 3 * r && bE[r] == -r && n[r] == 7 * r);
+            for (int i = 0; i < N; ++i)
+                if (x[(size_t)r * N + i] != (r + i) % 3 || bx[(size_t)r * N + i] != (r ^ i) % 5)
+                    ++g_bad;
+        }
+    };
+    auto held = [&] {
+        da_info info{};
+        CHECK(da_get_info(c, &info) == DA_OK);
+        return fake::st().used - (size_t)info.device_bytes;
+    };
+    const size_t before = held();
+    for (bool room : {false, true}) {
+        fake::reset();
+        if (!room) fake::st().memory = fake::st().used;
+        CHECK(da_anneal(c, &s, R, 10, 1, const_cast<da_result *>(&all)) == DA_OK);
+        whole();
+        CHECK(held() == before);
+        CHECK(fake::count("hipFree") == 0 && fake::count("hipDeviceSynchronize") == 0);
+        CHECK((fake::count("hipMemcpy2DAsync") == 0) == room);
+        CHECK(no_outputs() == DA_OK);   // no error left behind
+    }
+    da_pt_result pt{};
+    pt.best_x = bx.data();
+    pt.best_E = bE.data();
+    pt.final_x = x.data();
+    pt.final_E = E.data();
+    pt.n_accept = n.data();
+    fake::reset();
+    CHECK(da_pt(c, T, 2, R / 2, 2, 5, 0, 1, &pt) == DA_OK);
+    whole();
+    fake::st().memory = fake::st().used;   // the buffers of tempering are there
+    CHECK(da_pt(c, T, 2, R / 2, 2, 5, 0, 1, &pt) == DA_OK);
+    whole();
+    CHECK(fake::count("hipMemcpy2DAsync") == 0);
+    da_destroy(c);
+    fake::st().memory = SIZE_MAX;
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -242,6 +298,7 @@ int main(int argc, char **argv) {
         {"batch_stats", batch_stats},
         {"create_waits", create_waits},
         {"create_memory", create_memory},
+        {"outputs_memory", outputs_memory},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;
