@@ -1105,8 +1105,11 @@ class PinnedBlocks {
             return p;
         }
         void *p = nullptr;
-        if (made_ == kBlocks || hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess)
+        if (made_ == kBlocks) return nullptr;
+        if (hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();   // (or the next launch reports it)
             return nullptr;
+        }
         ++made_;
         return p;
     }
@@ -1187,8 +1190,9 @@ int copy_outputs_to_host(da_ctx *ctx, const JobDesc &J, int32_t R, const da_resu
     copy(o->best_x, d.best_x, nx);
     copy(o->final_x, d.final_x, nx);
     if (own) (void)hipFreeAsync(own, s);
-    if (pin) pinned_blocks().give(pin);
-    else if (e == hipSuccess) e = hipStreamSynchronize(s);
+    // (after a failed wait the kernel may still write to the block: left out of use)
+    if (pin && e == hipSuccess) pinned_blocks().give(pin);
+    if (!pin && e == hipSuccess) e = hipStreamSynchronize(s);
     return check_hip(ctx, e, "copy of outputs to host");
 }
 

@@ -290,6 +290,32 @@ static void outputs_memory() {
     fake::st().memory = SIZE_MAX;
 }
 
+// Small outputs where pinned memory cannot be had, and where the wait for the
+// kernel that writes it fails (it may still write then).
+static void outputs_pinned() {
+    const int N = 70, R = 5;
+    std::vector<uint8_t> bx(N * R), x(N * R);
+    std::vector<int64_t> bE(R), E(R), n(R);
+    da_result all{bx.data(), bE.data(), x.data(), E.data(), n.data()};
+    da_ctx *c = create(N);
+    const da_schedule s = schedule();
+    CHECK(da_anneal_async(c, &s, 0, R, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+    fake::reset();
+    fake::st().fail_from["hipHostMalloc"] = 0;
+    CHECK(da_anneal(c, &s, R, 10, 1, &all) == DA_OK);
+    CHECK(E[R - 1] == 3 * (R - 1) && x[N + 1] == 2 && bx[N + 1] == 0);
+    fake::reset();
+    CHECK(da_anneal(c, &s, R, 10, 1, &all) == DA_OK);
+    CHECK(fake::count("hipHostMalloc") == 1);
+    fake::reset();
+    fake::st().fail_from["hipStreamSynchronize"] = 0;
+    CHECK(da_anneal(c, &s, R, 10, 1, &all) == DA_EDEVICE);
+    fake::reset();
+    CHECK(da_anneal(c, &s, R, 10, 1, &all) == DA_OK);
+    CHECK(fake::count("hipHostMalloc") == 1);   // another block
+    da_destroy(c);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -299,6 +325,7 @@ int main(int argc, char **argv) {
         {"create_waits", create_waits},
         {"create_memory", create_memory},
         {"outputs_memory", outputs_memory},
+        {"outputs_pinned", outputs_pinned},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;

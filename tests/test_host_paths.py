@@ -41,6 +41,7 @@ def program(tmp_path_factory):
     "create_waits",    # an instance made beside running anneals
     "create_memory",   # and with little device memory left
     "outputs_memory",  # large outputs to the host: device memory they take
+    "outputs_pinned",  # small ones: without pinned memory, and a failed wait
 ])
 def test_host_path(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
