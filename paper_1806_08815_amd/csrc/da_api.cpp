@@ -40,6 +40,8 @@ void set_thread_error(const std::string &msg) { t_err = msg; }
 int fail(da_ctx *ctx, int code, const std::string &msg) {
     if (ctx) ctx->err = msg;
     t_err = msg;
+    // reported here: the thread's next launch is not to find it again
+    if (code == DA_ENOMEM || code == DA_EDEVICE) (void)hipGetLastError();
     return code;
 }
 

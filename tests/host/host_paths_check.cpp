@@ -316,6 +316,27 @@ static void outputs_pinned() {
     da_destroy(c);
 }
 
+// A call fails for want of memory, with that error; the next one succeeds.
+static void error_once() {
+    const std::vector<int32_t> Q = instance(70);
+    da_ctx *c = create(70);
+    const da_schedule s = schedule();
+    for (int R : {40, 80}) {   // the tables' memory, then more state
+        fake::reset();
+        fake::st().fail_from["hipMalloc"] = 0;
+        CHECK(da_anneal_async(c, &s, 0, R, 10, 1, nullptr, nullptr, nullptr) == DA_ENOMEM);
+        fake::st().fail_from.clear();
+        CHECK(da_anneal_async(c, &s, 0, R, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+    }
+    da_ctx *d = nullptr;
+    fake::reset();
+    fake::st().fail_from["hipMalloc"] = 0;
+    CHECK(da_create(Q.data(), 70, 0, &d) == DA_ENOMEM);
+    fake::st().fail_from.clear();
+    CHECK(da_anneal_async(c, &s, 0, 4, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+    da_destroy(c);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -326,6 +347,7 @@ int main(int argc, char **argv) {
         {"create_memory", create_memory},
         {"outputs_memory", outputs_memory},
         {"outputs_pinned", outputs_pinned},
+        {"error_once", error_once},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;
