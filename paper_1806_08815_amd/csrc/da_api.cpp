@@ -253,12 +253,12 @@ JobDesc make_job(const da_ctx *ctx, const LevelTables *lt, int32_t R, uint32_t r
     return J;
 }
 
-bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh) {
-    if (ctx->ell_D > 0) return false;
-    const int64_t ws = std::abs((int64_t)ctx->wscale), hb = ctx->hbound + 1;
+bool wave_takes(int32_t dtype, int64_t hbound, int32_t wscale, double T_min, double T_max,
+                LaunchShape &sh) {
+    const int64_t ws = std::abs((int64_t)wscale), hb = hbound + 1;
     // the field update's factor: 16 bits for 16-bit couplings, else 24
-    sh.w24 = ctx->dtype < 4 || (ctx->hbound / ws < (1 << 23) && ws < (1 << 23)) ? 1 : 0;
-    const int64_t wlim = ctx->dtype == 2 ? (1 << 15) : (sh.w24 ? (1 << 23) : INT64_MAX);
+    sh.w24 = dtype < 4 || (hbound / ws < (1 << 23) && ws < (1 << 23)) ? 1 : 0;
+    const int64_t wlim = dtype == 2 ? (1 << 15) : (sh.w24 ? (1 << 23) : INT64_MAX);
     if (ws >= wlim) return false;
     // the test's sum |h| + E_off + L(u) stays below 2^31: E_off is cut off at
     // max |h| + 1, L(u) <= 11.79 T, and T 2^q < 2^17 wherever q > 0
@@ -273,6 +273,12 @@ bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, Launch
     sh.wclamp = T_max >= 262144.0 || T_min * (double)(1 << q) < 16384.0 ? 1 : 0;
     sh.ecap = (int)hb;
     sh.wave = true;
+    return true;
+}
+
+bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh) {
+    if (ctx->ell_D > 0 || !wave_takes(ctx->dtype, ctx->hbound, ctx->wscale, T_min, T_max, sh))
+        return false;
     // Up to 512 variables one wave.  Beyond, with few replicas on a compute unit,
     // a team of 8 flips per lane whose random-number waves keep the draws off the
     // step's chain; they draw two blocks a lane while that leaves them off it, one
@@ -1054,7 +1060,8 @@ int next_events(da_ctx *ctx, hipEvent_t &e0, hipEvent_t &e1) {
     return DA_OK;
 }
 
-int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err) {
+int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err,
+               const HostTables *pre) {
     if (sch.n_levels == 0 && steps > kMaxPerStepSteps) {
         err = "per-step schedules take at most 2^24 steps";
         return DA_EINVAL;
@@ -1073,7 +1080,7 @@ int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, 
         if (!device_bound_error(jt.gerr, err)) return DA_ENOMEM;
     } else {
         jt.levels = get_level_tables(
-            sch.n_levels > 0 ? schedule_temps(sch) : std::vector<double>{0.0}, err);
+            sch.n_levels > 0 ? schedule_temps(sch) : std::vector<double>{0.0}, err, pre);
         if (!jt.levels) return DA_ENOMEM;
     }
     if (wave || perstep) {

@@ -74,8 +74,10 @@ struct HostTables {
 };
 void build_host_tables(const std::vector<double> &temps, HostTables &ht);
 // Tables for a temperature list (cached per device); nullptr on failure with
-// `err` set.
-std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err);
+// `err` set.  `pre`, when given, is the host image of these temperatures' tables
+// (of others: not used), uploaded where they have to be made.
+std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err,
+                                              const HostTables *pre = nullptr);
 // Device bytes of the tables of L levels with `buckets` brackets in total.
 int64_t level_table_bytes(int32_t L, int64_t buckets);
 
@@ -243,6 +245,11 @@ int validate_schedule(const da_schedule *s, std::string &err);
 // direct: the schedule's tables include direct tables (staged when they fit)
 LaunchShape choose_shape(const da_ctx *ctx, int32_t R, const da_launch *launch,
                          bool anneal_mode, bool direct = false);
+// Whether the wave and team kernels take dense instances of this coupling type,
+// field bound and common factor at temperatures between T_min and T_max; if so,
+// their fixed point is set in sh.
+bool wave_takes(int32_t dtype, int64_t hbound, int32_t wscale, double T_min, double T_max,
+                LaunchShape &sh);
 // Shape of the wave and team kernels for replicas of this instance at temperatures
 // between T_min and T_max; false when they do not take them.
 bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, LaunchShape &sh);
@@ -268,7 +275,8 @@ struct JobTables {
     const double *G = nullptr;
     float gerr = 0.0f;
 };
-int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err);
+int job_tables(const da_schedule &sch, int64_t steps, bool wave, JobTables &jt, std::string &err,
+               const HostTables *pre = nullptr);
 void attach_tables(JobDesc &J, const da_schedule &sch, const JobTables &jt);
 // Outputs of a run (dense, null: not wanted) into the caller's memory; waits.
 // scratch: device memory of the caller's that may be overwritten.

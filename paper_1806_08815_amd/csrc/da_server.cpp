@@ -50,6 +50,7 @@ struct Job {
     int32_t dtype = 0, wscale = 1;
     int64_t footprint = 0;
     HostMatrix hm;                    // prepared, until uploaded
+    std::unique_ptr<HostTables> ht;   // likewise, of a job for the table-driven kernel
     da_ctx *ctx = nullptr;
     JobTables tables;
     JobDesc J{};
@@ -155,6 +156,13 @@ void da_server::prep_loop() {
         Job &j = *jp;
         prepare_matrix(j.Q.data(), j.spec.N, j.dtype, j.wscale, j.hm);
         std::vector<int32_t>().swap(j.Q);
+        const da_schedule &sch = j.spec.schedule;
+        LaunchShape sh;
+        if (!wave_takes(j.dtype, j.hm.hbound, j.wscale, std::min(sch.T_hi, sch.T_lo),
+                        std::max(sch.T_hi, sch.T_lo), sh)) {
+            j.ht.reset(new HostTables());
+            build_host_tables(schedule_temps(sch), *j.ht);
+        }
         {
             std::lock_guard<std::mutex> lock(mu);
             preparing.erase(j.ticket);
@@ -181,7 +189,9 @@ int da_server::start_job(Job &j) {
     if (rc) return rc;
     j.ctx = ctx;
     const LaunchShape sh = batch_shape(ctx, j.spec.replicas, j.spec.schedule);
-    rc = job_tables(j.spec.schedule, j.spec.steps, sh.wave, j.tables, j.err);
+    // (a re-admitted job's tables come from the cache, or are built again)
+    rc = job_tables(j.spec.schedule, j.spec.steps, sh.wave, j.tables, j.err, j.ht.get());
+    j.ht.reset();
     if (rc) return rc;
     ctx->keep_tables = j.tables.levels;
     if (!ctx->st.ensure(j.spec.replicas, ctx->ld, j.err)) return DA_ENOMEM;

@@ -163,7 +163,8 @@ void build_host_tables(const std::vector<double> &temps, HostTables &ht) {
     if (ht.brk.empty()) ht.brk.push_back(0);
 }
 
-std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err) {
+std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, std::string &err,
+                                              const HostTables *pre) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         err = "hipGetDevice failed";
@@ -176,8 +177,12 @@ std::shared_ptr<LevelTables> get_level_tables(const std::vector<double> &temps, 
     if (it != g_cache.end()) {
         if (auto sp = it->second.lock()) return sp;
     }
-    HostTables ht;
-    build_host_tables(temps, ht);
+    HostTables own;
+    if (!pre || pre->temps != temps) {
+        build_host_tables(temps, own);
+        pre = &own;
+    }
+    const HostTables &ht = *pre;
     auto lt = std::make_shared<LevelTables>();
     lt->temps = temps;
     lt->L = (int32_t)temps.size();

@@ -6,6 +6,16 @@
 // the code under test, with its file-scope state in reach
 #include "da_api.cpp"
 
+namespace dapt {
+void logged_build(const std::vector<double> &temps, HostTables &ht) {
+    (void)fake::note("build_host_tables");
+    build_host_tables(temps, ht);
+}
+}  // namespace dapt
+#define build_host_tables logged_build
+#include "da_server.cpp"
+#undef build_host_tables
+
 #include <cstdio>
 
 static long g_bad = 0;
@@ -337,6 +347,49 @@ static void error_once() {
     da_destroy(c);
 }
 
+// The server builds the level tables of the jobs that need them on its preparation
+// threads, not on the device worker, and hands them on; the others' not at all.
+static void server_tables() {
+    for (bool wide : {false, true}) {   // (wide: a factor past the wave kernels' range)
+        const int N = 60, R = 4;
+        const std::vector<int32_t> Q = instance(N, false, wide ? 1 << 16 : 1);
+        fake::reset();
+        da_server *srv = nullptr;
+        CHECK(da_server_create(size_t(1) << 30, nullptr, &srv) == DA_OK);
+        da_job job{};
+        job.Q = Q.data();
+        job.N = N;
+        job.dtype_hint = 2;
+        job.schedule = schedule(wide ? 4e6 : 30.0, wide ? 1e5 : 1.0);
+        job.replicas = R;
+        job.steps = 1000;
+        job.seed = 1;
+        uint64_t ticket = 0;
+        CHECK(da_submit(srv, &job, &ticket) == DA_OK);
+        da_job_stats st{};
+        CHECK(da_wait(srv, ticket, nullptr, &st) == DA_OK);
+        da_server_destroy(srv);
+        std::thread::id built, launched;
+        for (const auto &c : fake::st().log) {
+            if (c.name == "build_host_tables") built = c.thread;
+            if (is_launch(c)) launched = c.thread;
+        }
+        CHECK(fake::count("hipGraphLaunch") == (wide ? 1 : 0) && fake::count("mix") == (wide ? 0 : 1));
+        CHECK(fake::count("build_host_tables") == (wide ? 1 : 0));
+        CHECK(built != launched && launched != std::thread::id());
+    }
+    // tables made before are taken as they are, and only for their temperatures
+    const std::vector<double> temps = {5.0, 2.5};
+    HostTables ht;
+    build_host_tables(temps, ht);
+    ht.thr[7] += 1;
+    std::string err;
+    auto lt = get_level_tables(temps, err, &ht);
+    CHECK(lt && lt->d_thr[7] == ht.thr[7] && lt->L == 2);
+    auto other = get_level_tables({5.0, 2.25}, err, &ht);
+    CHECK(other && other->d_thr[7] == ht.thr[7] - 1);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -348,6 +401,7 @@ int main(int argc, char **argv) {
         {"outputs_memory", outputs_memory},
         {"outputs_pinned", outputs_pinned},
         {"error_once", error_once},
+        {"server_tables", server_tables},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;
