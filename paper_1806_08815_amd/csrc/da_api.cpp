@@ -873,6 +873,9 @@ std::shared_ptr<TempList> get_temp_list(const std::vector<double> &temps, std::s
         err = "temperature list allocation or upload failed";
         return nullptr;
     }
+    // (lists that no context holds any more leave the cache here)
+    for (auto q = g_temps.begin(); q != g_temps.end();)
+        q = q->second.expired() ? g_temps.erase(q) : std::next(q);
     g_temps[key] = tl;
     return tl;
 }

@@ -390,6 +390,23 @@ static void server_tables() {
     CHECK(other && other->d_thr[7] == ht.thr[7] - 1);
 }
 
+// Temperature lists leave the cache with the contexts that held them.
+static void temps_bounded() {
+    da_ctx *c = create(40), *d = create(41);
+    const da_schedule keep = schedule(20.0, 1.5);
+    CHECK(da_anneal_async(d, &keep, 0, 1, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+    for (int q = 0; q < 300; ++q) {
+        const da_schedule s = schedule(30.0 + q, 1.0, 4 + q % 9);
+        CHECK(da_anneal_async(c, &s, 0, 1, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+        CHECK(g_temps.size() <= 3);
+    }
+    const int lists = fake::count("hipMalloc");
+    CHECK(da_anneal_async(c, &keep, 0, 1, 10, 1, nullptr, nullptr, nullptr) == DA_OK);
+    CHECK(fake::count("hipMalloc") == lists);   // d's list is still there
+    da_destroy(c);
+    da_destroy(d);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -402,6 +419,7 @@ int main(int argc, char **argv) {
         {"outputs_pinned", outputs_pinned},
         {"error_once", error_once},
         {"server_tables", server_tables},
+        {"temps_bounded", temps_bounded},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;

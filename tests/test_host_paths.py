@@ -44,6 +44,7 @@ def program(tmp_path_factory):
     "outputs_pinned",  # small ones: without pinned memory, and a failed wait
     "error_once",      # a failed call's error does not reach the next call
     "server_tables",   # where a served job's tables are built
+    "temps_bounded",   # the cache of temperature lists
 ])
 def test_host_path(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
