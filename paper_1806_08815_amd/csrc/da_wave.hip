@@ -249,9 +249,8 @@ template <int F>
 __host__ __device__ constexpr int team_rec_bytes(int NW) {
     return (NW < 4 ? 4 : NW) * 64 * (F > 8 ? 8 : 4) + 16;
 }
-// Bounds of one step: of every Philox block the first four draws' and, shifted
-// by half the banks, the last four's, so that lanes of 4 and of 8 flips read
-// them without a bank conflict.
+// Bounds of one step: of every Philox block the first four draws' and, in the other
+// half, the last four's, so that neighbouring lanes read neighbouring 16 bytes.
 __host__ __device__ constexpr int team_half_bytes(int N) { return (N + 1023) / 1024 * 128 * 16 + 128; }
 
 // The random-number waves of a team: during step s they write the bounds of step
@@ -445,8 +444,8 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     auto denergy = [&](int o) { return reinterpret_cast<int *>(lds + o + RB - 16); };
     uint4 *ring = reinterpret_cast<uint4 *>(lds);
     constexpr int NB = F >= 8 ? F / 8 : 1;   // Philox blocks per lane and step (F >= 8)
-    constexpr int P = F >= 8 || HELP ? 1 : 8 / F;   // steps drawn at once
-    static_assert(!TEAM || HELP || F >= 8, "a team's lanes draw whole blocks");
+    constexpr int P = F >= 8 ? 1 : 8 / F;   // steps drawn at once
+    static_assert(!TEAM || F >= 8, "a team's lanes draw whole blocks");
     constexpr int RW = F >= 2 ? F / 2 : 1;   // 32-bit words of a lane's draws
     constexpr int NX = (F + 3) / 4;
     typedef typename VecOf<WT, F>::type RowV;
@@ -570,11 +569,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     };
     // this lane's draws of step t: flip f is half f & 1 of word f >> 1
     auto fetch = [&](uint32_t t, uint32_t (&r)[RW]) {
-        if constexpr (F == 4 && P == 1) {
-            const uint4 v = db[0].draw(t, r0, k0, k1);
-            r[0] = (i0 & 4) ? v.z : v.x;
-            r[RW - 1] = (i0 & 4) ? v.w : v.y;
-        } else if constexpr (F >= 8) {
+        if constexpr (F >= 8) {
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
                 const uint4 v = db[q].draw(t, r0, k0, k1);
@@ -622,8 +617,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     // HELP: this lane's bounds of step t from the ring (lanes past the last
     // block: some block's)
     const int half = HELP ? team_half_bytes(J.N) : 0;
-    const uint8_t *hring = lds + 2 * RB + min(i0 >> 3, (J.N - 1) >> 3) * 16 +
-                           (F == 4 && (i0 & 4) ? half : 0);
+    const uint8_t *hring = lds + 2 * RB + min(i0 >> 3, (J.N - 1) >> 3) * 16;
     auto handed = [&](uint32_t t, int (&o)[F]) {
         const uint8_t *p = hring + (t & 1u) * (2 * half);
 #pragma unroll
@@ -1070,20 +1064,21 @@ __global__ __launch_bounds__(512) void k_mix(const JobDesc *__restrict__ jobs,
 // (defined here, compiled for one coupling type and team size per part of this file)
 template <typename WT>
 int launch_wave_w(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
+    // (the forms that wave_shape chooses: W in LDS wherever it fits there, which it
+    // does up to 128 variables, and past 256 for int8 alone)
     if (J.w_lds) {
-        // (a row of 16 flips per lane is past what fits LDS)
+        if constexpr (sizeof(WT) == 1)
+            if (F == 8) DAPT_LAUNCH(k_wave, WT, 8, true);
         switch (F) {
             case 1: DAPT_LAUNCH(k_wave, WT, 1, true);
             case 2: DAPT_LAUNCH(k_wave, WT, 2, true);
             case 4: DAPT_LAUNCH(k_wave, WT, 4, true);
-            case 8: DAPT_LAUNCH(k_wave, WT, 8, true);
             default: return (int)hipErrorInvalidValue;
         }
     }
+    if constexpr (sizeof(WT) == 4)
+        if (F == 4) DAPT_LAUNCH(k_wave, WT, 4, false);
     switch (F) {
-        case 1: DAPT_LAUNCH(k_wave, WT, 1, false);
-        case 2: DAPT_LAUNCH(k_wave, WT, 2, false);
-        case 4: DAPT_LAUNCH(k_wave, WT, 4, false);
         case 8: DAPT_LAUNCH(k_wave, WT, 8, false);
         case 16: DAPT_LAUNCH(k_wave, WT, 16, false);
         default: return (int)hipErrorInvalidValue;
@@ -1094,20 +1089,13 @@ template <typename WT>
 int launch_team_w(const JobDesc &J, int F, int blocks, int threads, size_t lds, void *stream) {
     const int key = F * 1000 + (J.NW <= 2 ? 2 : J.NW <= 4 ? 4 : 16) * 10 +
                     (J.NH == 0 ? 0 : J.NH * 512 >= J.N ? 1 : 2);
-    switch (key) {
-        case 4041: DAPT_LAUNCH(k_team, WT, 4, 4, 1);
-        case 4042: DAPT_LAUNCH(k_team, WT, 4, 4, 2);
-        case 8020: DAPT_LAUNCH(k_team, WT, 8, 2, 0);
+    switch (key) {   // (those that wave_shape chooses)
         case 8021: DAPT_LAUNCH(k_team, WT, 8, 2, 1);
         case 8022: DAPT_LAUNCH(k_team, WT, 8, 2, 2);
-        case 8040: DAPT_LAUNCH(k_team, WT, 8, 4, 0);
         case 8041: DAPT_LAUNCH(k_team, WT, 8, 4, 1);
         case 8042: DAPT_LAUNCH(k_team, WT, 8, 4, 2);
-        case 8160: DAPT_LAUNCH(k_team, WT, 8, 16, 0);
-        case 8161: DAPT_LAUNCH(k_team, WT, 8, 16, 1);
         case 8162: DAPT_LAUNCH(k_team, WT, 8, 16, 2);
         case 16040: DAPT_LAUNCH(k_team, WT, 16, 4, 0);
-        case 16041: DAPT_LAUNCH(k_team, WT, 16, 4, 1);
         case 16042: DAPT_LAUNCH(k_team, WT, 16, 4, 2);
         case 16160: DAPT_LAUNCH(k_team, WT, 16, 16, 0);
         case 16162: DAPT_LAUNCH(k_team, WT, 16, 16, 2);

@@ -37,6 +37,7 @@ struct State {
     hipError_t last = hipSuccess;            // as hipGetLastError keeps it
     std::vector<int> mix_blocks;             // workgroups of each mixed launch
     std::vector<dapt::JobDesc> mix_jobs;     // the jobs they ran
+    std::vector<dapt::JobDesc> runs;         // launches of the table-driven step kernel
     uintptr_t handles = 0x1000;
 };
 inline State &st() {
@@ -73,6 +74,7 @@ inline void reset() {
     st().fail_from.clear();
     st().mix_blocks.clear();
     st().mix_jobs.clear();
+    st().runs.clear();
     st().memory = SIZE_MAX;
     st().last = hipSuccess;
 }
@@ -198,7 +200,11 @@ int launch_energy(const JobDesc &, int, const uint8_t *, int32_t, int64_t *, int
     return launched("energy", s);
 }
 int launch_finish_start(const JobDesc &, void *s) { return launched("finish_start", s); }
-int launch_run(const JobDesc &, int, bool, const TraceDesc *, int, int, size_t, void *s) {
+int launch_run(const JobDesc &J, int, bool, const TraceDesc *, int, int, size_t, void *s) {
+    {
+        std::lock_guard<std::recursive_mutex> lock(fake::st().mu);
+        fake::st().runs.push_back(J);
+    }
     return launched("run", s);
 }
 size_t wave_lds_bytes(int, int, int, int, int, int64_t w) { return (size_t)w; }

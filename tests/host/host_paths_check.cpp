@@ -407,6 +407,37 @@ static void temps_bounded() {
     da_destroy(d);
 }
 
+// Not a check: the step kernels that wave_shape chooses over sizes, couplings and
+// replicas, one a line: type, flips per lane, then W in LDS, or waves and Philox
+// blocks of a team as the launcher tells its variants apart.
+static void list_shapes() {
+    std::map<std::string, int> seen;
+    std::vector<int> sizes;
+    for (int N = 1; N <= 8192; N += N < 700 ? 1 : N < 4200 ? 13 : 61) sizes.push_back(N);
+    for (int N : {1024, 1025, 2048, 2049, 4096, 4097, 8192}) sizes.push_back(N);
+    for (int N : sizes)
+        for (int dtype : {1, 2, 4})
+            for (int per_cu : {1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 17, 40}) {
+                da_ctx c;
+                c.N = N;
+                c.ld = (N + 63) / 64 * 64;
+                c.dtype = dtype;
+                c.hbound = 1000;
+                LaunchShape sh;
+                CHECK(wave_shape(&c, 256 * per_cu, 1.0, 30.0, sh));
+                char line[80];
+                const char type = dtype == 1 ? 'a' : dtype == 2 ? 's' : 'i';
+                if (sh.NW > 1)
+                    std::snprintf(line, sizeof line, "team %c %d %d %d", type, sh.F,
+                                  sh.NW <= 2 ? 2 : sh.NW <= 4 ? 4 : 16,
+                                  sh.NH == 0 ? 0 : sh.NH * 512 >= N ? 1 : 2);
+                else
+                    std::snprintf(line, sizeof line, "wave %c %d %d", type, sh.F, sh.w_lds);
+                seen[line] = 1;
+            }
+    for (auto &s : seen) std::printf("%s\n", s.first.c_str());
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"batch_error", batch_error},
@@ -420,6 +451,7 @@ int main(int argc, char **argv) {
         {"error_once", error_once},
         {"server_tables", server_tables},
         {"temps_bounded", temps_bounded},
+        {"list_shapes", list_shapes},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
     if (it == checks.end()) return 2;

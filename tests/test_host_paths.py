@@ -7,10 +7,13 @@ launches, waits and copies, and what happens when one of them fails, are checked
 on the CPU.
 """
 import os
+import re
 import shutil
 import subprocess
 
 import pytest
+
+from paper_1806_08815_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIP_INCLUDE = "/opt/rocm/include"
@@ -50,3 +53,21 @@ def test_host_path(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-4000:] + r.stderr[-2000:]
     assert "failures 0" in r.stdout
+
+
+def test_compiled_step_kernels_are_those_chosen(program):
+    """Every variant of the wave and team kernels that the library holds is one that
+    a launch shape asks for, and the other way round."""
+    r = subprocess.run([program, "list_shapes"], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:]
+    chosen = {l for l in r.stdout.splitlines() if l.startswith(("wave", "team"))}
+    if not os.path.exists(build.LIB):
+        build.build_library()
+    with open(build.LIB, "rb") as f:
+        names = f.read()
+    built = set()
+    for m in re.finditer(rb"6k_waveI([asi])Li(\d+)ELb([01])ELb[01]ELb[01]E", names):
+        built.add("wave %s %s %s" % tuple(g.decode() for g in m.groups()))
+    for m in re.finditer(rb"6k_teamI([asi])Li(\d+)ELi(\d+)ELi(\d+)ELb[01]ELb[01]E", names):
+        built.add("team %s %s %s %s" % tuple(g.decode() for g in m.groups()))
+    assert chosen == built, (sorted(built - chosen), sorted(chosen - built))
