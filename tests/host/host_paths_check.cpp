@@ -407,6 +407,32 @@ static void temps_bounded() {
     da_destroy(d);
 }
 
+// Launch shapes of the table-driven kernel are timed, also for short schedules, on
+// windows that stay inside the schedule, once for a size and replica count.
+static void tuner_windows() {
+    for (int N : {71, 93, 111, 133})
+        for (bool sparse : {true, false}) {
+            da_ctx *c = sparse ? create(N, true, 1, DA_STORE_SPARSE) : create(N + 1, false, 1 << 15, 2);
+            int32_t R = 1;   // (a new bucket of replica counts each time)
+            for (int64_t S : {65, 100, 575, 2000}) {
+                R *= 2;
+                const da_schedule s = schedule(2e5, 1e4, 128);
+                fake::reset();
+                CHECK(da_anneal_async(c, &s, 0, R, S, 1, nullptr, nullptr, nullptr) == DA_OK);
+                const auto &runs = fake::st().runs;
+                CHECK(runs.size() > 1 && fake::count("wave") == 0);
+                for (const JobDesc &J : runs)
+                    CHECK(J.s0 >= 0 && J.s0 <= J.s1 && J.s1 <= J.S && J.S == S);
+                CHECK(runs.back().s0 == 0 && runs.back().s1 == S);
+                const size_t timed = runs.size();
+                fake::reset();
+                CHECK(da_anneal_async(c, &s, 0, R, S, 1, nullptr, nullptr, nullptr) == DA_OK);
+                CHECK(fake::st().runs.size() == 1 && timed > 2);
+            }
+            da_destroy(c);
+        }
+}
+
 // Not a check: the step kernels that wave_shape chooses over sizes, couplings and
 // replicas, one a line: type, flips per lane, then W in LDS, or waves and Philox
 // blocks of a team as the launcher tells its variants apart.
@@ -451,6 +477,7 @@ int main(int argc, char **argv) {
         {"error_once", error_once},
         {"server_tables", server_tables},
         {"temps_bounded", temps_bounded},
+        {"tuner_windows", tuner_windows},
         {"list_shapes", list_shapes},
     };
     auto it = argc > 1 ? checks.find(argv[1]) : checks.end();

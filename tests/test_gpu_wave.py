@@ -186,3 +186,48 @@ def test_tempering_sweeps(api, N, M, chains, rounds, K):
     ref = oracle.pt(Q, temps, chains=chains, rounds=rounds, steps_per_round=K, eoff_inc=1, seed=5)
     for k in KEYS + ("slot", "n_swaps", "pair_swaps"):
         assert np.array_equal(np.asarray(gpu[k]).reshape(-1), np.asarray(ref[k]).reshape(-1)[:np.asarray(gpu[k]).size]), k
+
+
+# one wave of 16 flips per lane with four replicas in a workgroup: four replicas
+# per compute unit, and from six on (256 units), ragged N and last workgroups
+@pytest.mark.parametrize("kind", ["sk", "gauss", "q100000"])
+@pytest.mark.parametrize("N,R", [(1000, 1000), (999, 1500), (513, 1021), (1024, 1793)])
+def test_one_wave_of_sixteen(api, kind, N, R):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    ctx = _check(api, Q, 0, R, 150, 7, T_hi, T_lo, inc, init="random")
+    st = api.da_last_kernel_stats(ctx)
+    assert (st["flips_per_lane"], st["rng_waves"], st["replicas_per_block"]) == (16, 0, 4)
+
+
+@pytest.mark.parametrize("dtype", [1, 2, 4])
+def test_one_wave_of_sixteen_types(api, dtype):
+    Q, T_hi, T_lo, inc = _instance("sk", 830)
+    ctx = _check(api, Q, dtype, 1022, 200, 6, T_hi, T_lo, inc)
+    assert api.da_last_kernel_stats(ctx)["flips_per_lane"] == 16
+
+
+@pytest.mark.parametrize("N,R", [(700, 1000), (700, 1500)])
+@pytest.mark.parametrize("kind,L,S,extra", [
+    ("sk", 150, 100, {}), ("cold", 4, 150, {}), ("sk", 0, 150, dict(kind="linear_beta")),
+    ("gauss", 0, 70, {}), ("q100", 3, 150, dict(trial="single")), ("sk", 3, 0, {}), ("sk", 0, 1, {}),
+])
+def test_one_wave_of_sixteen_schedules(api, N, R, kind, L, S, extra):
+    Q, T_hi, T_lo, inc = _instance(kind, N)
+    ctx = _check(api, Q, 0, R, S, L, T_hi, T_lo, inc, **extra)
+    st = api.da_last_kernel_stats(ctx)
+    assert (st["flips_per_lane"], st["rng_waves"]) == (16, 0)
+
+
+# the shapes of teams by replicas per compute unit (256 units)
+@pytest.mark.parametrize("N,R,F,NH", [
+    (513, 3, 8, 1), (1024, 512, 8, 1), (999, 600, 8, 2), (1000, 1100, 8, 2), (1000, 1280, 8, 2),
+    (1025, 2, 8, 2), (2048, 300, 8, 4), (1300, 1024, 8, 3), (1300, 1100, 16, 0),
+    (2049, 2, 8, 3), (4096, 256, 8, 4), (2100, 300, 16, 3), (2100, 600, 16, 0),
+    (4097, 2, 16, 5), (5000, 300, 16, 0)])
+def test_team_shapes(api, N, R, F, NH):
+    Q, T_hi, T_lo, inc = _instance("sk", N)
+    ctx = _check(api, Q, 0, R, 20, 3, T_hi, T_lo, inc)
+    st = api.da_last_kernel_stats(ctx)
+    waves = -(-N // (64 * F))
+    assert (st["flips_per_lane"], st["rng_waves"]) == (F, NH)
+    assert (st["threads"], st["blocks"]) == (64 * (waves + NH), R)

@@ -48,6 +48,7 @@ def program(tmp_path_factory):
     "error_once",      # a failed call's error does not reach the next call
     "server_tables",   # where a served job's tables are built
     "temps_bounded",   # the cache of temperature lists
+    "tuner_windows",   # the launches that time the table-driven kernel's shapes
 ])
 def test_host_path(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
