@@ -284,19 +284,28 @@ bool wave_shape(const da_ctx *ctx, int32_t R, double T_min, double T_max, Launch
     // step's chain; they draw two blocks a lane while that leaves them off it, one
     // where replicas share the unit, and are left out where it is full; 16 flips
     // per lane, the fewest instructions per step, where it is, or past 16 waves.
-    // ns per step measured at N = 1024 and 1, 2, 3, 4 replicas per unit: two
-    // blocks 500, 575, 701, 780, one block 517, 582, 595, 663, one wave of 16
-    // flips 637, 661, -, 646; N = 2048: two blocks 649, 956, 1281, 1630, one block
-    // 668, 772, 1016, 1451, none 721, 937, 1182, 1433; N = 4096: 8 flips and two
-    // blocks 830, 1367, 2042, 16 flips and two blocks 870, 1295, 1968, none 1050,
-    // 1466, 1939; N = 8192: 16 flips and two blocks 1226, 2311, none 1447, 2302.
+    // ns per step measured (Gaussian int16, levels of 100 steps and more) at N = 1024
+    // and 1, 2, 3, 4 replicas per unit: two blocks 524, 552, 679, 725, one block 521,
+    // 557, 550, 596, one wave of 16 flips 663, 680, 670, 673; N = 2048: two blocks
+    // 608, 846, 1202, 1509, one block 641, 713, 887, 1333, one team of two waves of
+    // 16 flips 804, 1149, 1543, 1561; N = 4096 and 1, 2, 3 per unit: 8 flips and two
+    // blocks 798, 1183, 1761, 16 flips and two blocks 770, 1047, 1639, none 917,
+    // 1306, 1725; N = 8192 and 1, 2: 16 flips and two blocks 1164, 2077, none 1322,
+    // 2093.
+    // Past three replicas per unit at N <= 1024 a call alone and calls that share
+    // the chip differ: two anneals at once take what one of twice the replicas
+    // takes.  Teams of one block (alone; one of two at once) against one wave at
+    // 4 per unit 596; 619 against 673; 508, at 5: 730; 748 against 1000; 703 (the
+    // fifth wave shares a SIMD, and the step takes as long as with eight), at 6:
+    // 837; 830 against 997; 706, at 9: 1332; 1162 against 1400; 1100, from 7 on
+    // otherwise slower both ways (7: 1117 against 1000).  So teams up to three, and
+    // at five, where they gain 27 % alone and lose 6 % beside another.
     const int N = ctx->N;
     const int per_cu = (R + ctx->cus - 1) / ctx->cus;
     int HB = 0;   // Philox blocks per lane of a random-number wave
     if (N <= 512) {
         sh.F = N <= 64 ? 1 : N <= 128 ? 2 : N <= 256 ? 4 : 8;
     } else if (N <= 1024) {
-        // (the fifth wave of 16 flips shares a SIMD: 1057 against 779 with teams)
         const bool team = per_cu <= 3 || per_cu == 5;
         sh.F = team ? 8 : 16;
         HB = !team ? 0 : per_cu <= 2 ? 2 : 1;
