@@ -1375,8 +1375,9 @@ int da_create(const int32_t *Q, int32_t N, int32_t dtype_hint, da_ctx **out) {
     std::string err;
     if (!device_is_gfx950(err)) return fail(nullptr, DA_EDEVICE, err);
 
-    // Small instances on the host: the device's answer takes a round trip (N = 64:
-    // 98 us against 141, N = 512: 976 against 194, N = 8192: 382 ms against 10)
+    // Small instances on the host: the device's answer takes a round trip and an
+    // upload buffer (us, host and device: N = 64 73 and 141, 129 102 and 178, 200 142
+    // and 179, 256 236 and 186, 512 800 and 220, 8192 315 ms and 10.6)
     auto on_host = [&]() -> int {
         HostMatrix hm;
         int32_t dtype = 0, wscale = 1;
@@ -1388,7 +1389,7 @@ int da_create(const int32_t *Q, int32_t N, int32_t dtype_hint, da_ctx **out) {
         if (!rc) rc = create_ctx(hm, nullptr, out, err);
         return rc ? fail(nullptr, rc, err) : DA_OK;
     };
-    if (N <= 128) return on_host();
+    if (N <= 224) return on_host();
     // Q and the derivation's scratch, on the device for the length of this call.
     // Ordered on the stream and given back when that is waited for: hipFree waits
     // for everything that runs on the device, other contexts' anneals too (N = 512

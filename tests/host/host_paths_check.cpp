@@ -210,6 +210,15 @@ static void create_waits() {
     }
 }
 
+// Where da_create derives an instance: up to 224 variables the host is faster.
+static void create_sizes() {
+    for (int N : {1, 129, 200, 224, 225, 256, 700}) {
+        fake::reset();
+        da_destroy(create(N));
+        CHECK(fake::count("derive") == (N > 224 ? 1 : 0));
+    }
+}
+
 // da_create where the image fits but not the upload buffer, alone or beside it:
 // the same instance, and no error left for the next call's launches.
 static void create_memory() {
@@ -471,6 +480,7 @@ int main(int argc, char **argv) {
         {"batch_chunks", batch_chunks},
         {"batch_stats", batch_stats},
         {"create_waits", create_waits},
+        {"create_sizes", create_sizes},
         {"create_memory", create_memory},
         {"outputs_memory", outputs_memory},
         {"outputs_pinned", outputs_pinned},

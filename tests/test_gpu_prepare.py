@@ -1,4 +1,4 @@
-"""Instances made on the device (N > 128) and on the host against numpy: storage
+"""Instances made on the device (N > 224) and on the host against numpy: storage
 type and common factor, energies, at the edges of the 64 x 64 tiles, couplings
 of the largest size, none at all, and what is refused.  Whole numbers: exact."""
 import numpy as np
@@ -87,3 +87,10 @@ def test_beside_a_running_anneal(api):
     torch.cuda.synchronize()
     x = np.ones((1, 300), np.uint8)
     assert api.da_energy(ctx, x)[0] == Q.astype(np.int64).sum()
+
+
+@pytest.mark.parametrize("kind", ["g1", "g6", "g2^20", "wide", "diag", "one", "cancel"])
+@pytest.mark.parametrize("N", [224, 225, 255, 256, 257, 449])
+def test_storage_and_energies_past_the_host_sizes(api, kind, N):
+    """Up to 224 variables the host derives the instance, past them the device."""
+    test_storage_and_energies(api, kind, N)

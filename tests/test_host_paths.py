@@ -43,6 +43,7 @@ def program(tmp_path_factory):
     "batch_stats",     # the launch shapes reported after a batch
     "create_waits",    # an instance made beside running anneals
     "create_memory",   # and with little device memory left
+    "create_sizes",    # small ones are derived on the host
     "outputs_memory",  # large outputs to the host: device memory they take
     "outputs_pinned",  # small ones: without pinned memory, and a failed wait
     "error_once",      # a failed call's error does not reach the next call
