@@ -495,8 +495,10 @@ int da_poll(da_server *srv, uint64_t ticket, da_result *out, da_job_stats *stats
 /* As da_poll, but waits for the job. */
 int da_wait(da_server *srv, uint64_t ticket, da_result *out, da_job_stats *stats);
 
-/* Device bytes a job would hold while resident (coupling matrix, fields,
- * tables, state).  Host-only; the admission policy uses exactly this. */
+/* Device bytes reserved for a job while it is resident (coupling matrix, fields,
+ * state, outputs and the level tables): an upper bound, since only jobs of the
+ * table-driven kernel hold the tables (others 8 bytes a level).  Host-only; the
+ * admission policy uses exactly this. */
 int64_t da_job_footprint(int32_t N, int32_t dtype_bytes, int32_t replicas, int32_t n_levels);
 
 /* Drains running jobs, then frees everything; NULL is a no-op. */

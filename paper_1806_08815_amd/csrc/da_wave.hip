@@ -24,18 +24,18 @@
 //     the xors of the later ones are three-input.
 //   * Energy, offset and counts are wave-uniform scalars.
 // ns per step, before (compute and random-number waves on tables, da_kernels.hip)
-// and now: N = 64, 16 replicas 668 -> 194; N = 512 Gaussian, 64 replicas ~600 -> 428;
-// N = 1024 Gaussian, 1024 replicas 690 -> 657 alone (VALU instructions per
-// replica-step 359 -> 230; two anneals at once 690 -> 465 each), 2048 replicas
-// 1440 -> 1001, +-1 2190 -> 1109.
+// and now: N = 64, 16 replicas 668 -> 200; N = 512 Gaussian, 64 replicas ~600 -> 430;
+// N = 1024 Gaussian, 1024 replicas 690 -> 660 (VALU instructions per replica-step
+// 359 -> 230; two such anneals at once 690 -> 465 each), 2048 replicas 1440 -> 1016,
+// +-1 2190 -> 1108.
 //
 // Beyond 512 variables with few replicas the chain of one wave is too long, and a
 // team shares it (wave_run, team_draws): one barrier a step, the lanes' records and
 // the bounds of random-number waves through LDS.  What bounds it then is the chain
 // row fetch (231 ns from L2), test, scan, exchange, search: N = 1024, 128 replicas
-// 543 (direct tables, +-1), 533 (Gaussian), 718 (+-1, short levels) -> 485 .. 511;
-// dense int32 N = 999 890 -> 543; a new temperature every step 1030 -> 550; N = 8192,
-// 64 replicas 2700 -> 1110.
+// 543 (direct tables, +-1), 533 (Gaussian), 718 (+-1, short levels) -> 492 .. 529;
+// dense int32 N = 999 890 -> 552; a new temperature every step 1030 -> 570; N = 8192,
+// 64 replicas 2700 -> 1120.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,13 +55,52 @@ namespace {
 
 constexpr double kLn2 = 0.69314718055994530942;
 
-// a ^ b ^ k, k wave-uniform.  (The builtin, not inline asm: round keys that were
-// spilled come back by v_readlane, after which a vector instruction may read the
-// scalar only two wait states later.  The compiler keeps these for its own
-// instructions and cannot for text.)
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k) {
-    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)k, 0x96);
-}
+// Round keys of the draws and the xor that takes them, a ^ b ^ key.
+//   From scalar registers by the builtin, not inline asm: keys that were spilled come
+// back by v_readlane, after which a vector instruction may read the scalar only two
+// wait states later.  The compiler keeps these for its own instructions and cannot
+// for text.
+//   In vector registers (VEC) inline asm has no such rule to break, and the compiler
+// then spreads the field update among the draws: one wave of 16 flips per lane,
+// 16-bit couplings, 1024 replicas of N = 1024: 67.9 ms an anneal with the builtin, 66.4
+// so, for 14 registers.  Where those spill (32-bit couplings) or the waves share the
+// update's wait (teams, batches: 8.4 against 9.3 ms) it is the slower.
+template <bool VEC>
+struct DrawKeys {
+    uint32_t k0, k1;
+    __device__ __forceinline__ DrawKeys(uint32_t a, uint32_t b) : k0(a), k1(b) {}
+    __device__ __forceinline__ uint32_t xor_k0(uint32_t a, uint32_t b, int r) const {
+        return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b,
+                                                     (int)(k0 + (uint32_t)r * kPhiloxW0), 0x96);
+    }
+    __device__ __forceinline__ uint32_t xor_k1(uint32_t a, uint32_t b, int r) const {
+        return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b,
+                                                     (int)(k1 + (uint32_t)r * kPhiloxW1), 0x96);
+    }
+};
+template <>
+struct DrawKeys<true> {
+    uint32_t a[10], b[10];   // of rounds 3 .. 9
+    __device__ __forceinline__ DrawKeys(uint32_t k0, uint32_t k1) {
+#pragma unroll
+        for (int r = 3; r < 10; ++r) {
+            a[r] = k0 + (uint32_t)r * kPhiloxW0;
+            b[r] = k1 + (uint32_t)r * kPhiloxW1;
+            asm("" : "+v"(a[r]), "+v"(b[r]));   // (held, not made again at each use)
+        }
+    }
+    static __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k) {
+        uint32_t r;
+        asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(k));
+        return r;
+    }
+    __device__ __forceinline__ uint32_t xor_k0(uint32_t x, uint32_t y, int r) const {
+        return xor3(x, y, a[r]);
+    }
+    __device__ __forceinline__ uint32_t xor_k1(uint32_t x, uint32_t y, int r) const {
+        return xor3(x, y, b[r]);
+    }
+};
 
 // The Metropolis draws of one Philox block (counter (block, step, rid, 0)) over
 // many steps.  Of the ten rounds, what does not depend on the step is kept: the
@@ -80,8 +119,9 @@ struct DrawBlock {
         f3 = (uint32_t)q0 ^ (k1 + 3u * kPhiloxW1);
     }
     // r0: hi(M1 rid) ^ k0, wave-uniform
-    __device__ __forceinline__ uint4 draw(uint32_t step, uint32_t r0, uint32_t k0,
-                                          uint32_t k1) const {
+    template <bool VEC>
+    __device__ __forceinline__ uint4 draw(uint32_t step, uint32_t r0,
+                                          const DrawKeys<VEC> &keys) const {
         const uint64_t s1 = (uint64_t)kPhiloxM0 * (r0 ^ step);      // round 1
         uint32_t c2 = (uint32_t)(s1 >> 32) ^ b1;
         uint64_t p1 = (uint64_t)kPhiloxM1 * c2;                     // round 2
@@ -90,7 +130,7 @@ struct DrawBlock {
         c2 = (uint32_t)s1 ^ e2;
         uint64_t p0 = (uint64_t)kPhiloxM0 * c0;                     // round 3
         p1 = (uint64_t)kPhiloxM1 * c2;
-        c0 = xor3((uint32_t)(p1 >> 32), c1, k0 + 3u * kPhiloxW0);
+        c0 = keys.xor_k0((uint32_t)(p1 >> 32), c1, 3);
         c1 = (uint32_t)p1;
         c2 = (uint32_t)(p0 >> 32) ^ f3;
         uint32_t c3 = (uint32_t)p0;
@@ -98,9 +138,9 @@ struct DrawBlock {
         for (int r = 4; r < 10; ++r) {
             p0 = (uint64_t)kPhiloxM0 * c0;
             p1 = (uint64_t)kPhiloxM1 * c2;
-            c0 = xor3((uint32_t)(p1 >> 32), c1, k0 + (uint32_t)r * kPhiloxW0);
+            c0 = keys.xor_k0((uint32_t)(p1 >> 32), c1, r);
             c1 = (uint32_t)p1;
-            c2 = xor3((uint32_t)(p0 >> 32), c3, k1 + (uint32_t)r * kPhiloxW1);
+            c2 = keys.xor_k1((uint32_t)(p0 >> 32), c3, r);
             c3 = (uint32_t)p0;
         }
         return make_uint4(c0, c1, c2, c3);
@@ -298,6 +338,7 @@ __device__ __forceinline__ void team_draws(const JobDesc &J, int rr, uint8_t *ri
         }
     };
     level_of_step(s0);
+    const DrawKeys<false> keys(k0, k1);
     DrawBlock db[HB];
 #pragma unroll
     for (int q = 0; q < HB; ++q)
@@ -310,7 +351,7 @@ __device__ __forceinline__ void team_draws(const JobDesc &J, int rr, uint8_t *ri
         uint8_t *slot = ring + (t & 1u) * (2 * half) + (hw * HB * 64 + lane) * 16;
 #pragma unroll
         for (int q = 0; q < HB; ++q) {
-            const uint4 r = db[q].draw(t, r0, k0, k1);
+            const uint4 r = db[q].draw(t, r0, keys);
             int4 e0, e1;
             e0.x = draw_bound<CLAMP>(r.x & 0xFFFFu, ga, gb);
             e0.y = draw_bound<CLAMP>(r.x >> 16, ga, gb);
@@ -421,15 +462,16 @@ __device__ __forceinline__ void pt_sweep(const JobDesc &J, int rr, uint32_t t) {
 // Runs steps [s0, s1) of replica rr by the J.NW <= NWC waves of a team (NWC = 1:
 // this wave alone; NWC = 16: any number).  wl: W in LDS (WLDS); lds: this wave's
 // Philox blocks [2][64] (alone, F < 8), or a team's records and bounds (HELP: from
-// its random-number waves; else every wave draws its own, F >= 8).  FEAT: per-step schedules and single-trial proposals; without it
-// neither leaves code in the loop.
+// its random-number waves; else every wave draws its own, F >= 8).  FEAT: per-step
+// schedules and single-trial proposals; without it neither leaves code in the loop.
+// VK: round keys in vector registers (DrawKeys).
 //
 // A team meets at one barrier a step.  Before it every wave leaves its lanes'
 // records in LDS; after it every wave finds the chosen flip from them (up to
 // four waves: from all records of its own lane number, read at once), reads row
 // k of W for its own fields, and the wave that holds the flip leaves its energy
 // change for the others to add a step later.
-template <typename WT, int F, int NWC, bool HELP, bool WLDS, bool CLAMP, bool FEAT>
+template <typename WT, int F, int NWC, bool HELP, bool WLDS, bool CLAMP, bool FEAT, bool VK = false>
 __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t *wl, uint8_t *lds,
                                          int wr) {
     constexpr bool TEAM = NWC > 1;
@@ -554,6 +596,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     level_consts();
 
     // --- draws ---------------------------------------------------------------
+    const DrawKeys<VK> keys(k0, k1);
     DrawBlock db[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q)
@@ -562,7 +605,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
     // into the half of the ring that the group before it does not hold
     auto produce = [&](uint32_t t) {
         const uint32_t sub = (uint32_t)lane / (8u * F);
-        ring[(t & P) / P * 64 + lane] = db[0].draw(t + sub, r0, k0, k1);
+        ring[(t & P) / P * 64 + lane] = db[0].draw(t + sub, r0, keys);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -572,7 +615,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
         if constexpr (F >= 8) {
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
-                const uint4 v = db[q].draw(t, r0, k0, k1);
+                const uint4 v = db[q].draw(t, r0, keys);
                 r[4 * q] = v.x;
                 r[4 * q + 1] = v.y;
                 r[4 * q + 2] = v.z;
@@ -963,7 +1006,7 @@ __device__ __forceinline__ void wave_run(const JobDesc &J, int rr, const uint8_t
 
 // One wave per replica, the J.RPW replicas from rr0 per workgroup (they share W in
 // LDS and nothing else).  LDS: [W][2][64] Philox blocks per wave (F < 8).
-template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
+template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT, bool VK = false>
 __device__ __forceinline__ void wave_block(const JobDesc &J, int rr0, uint8_t *smem) {
     int w_bytes = 0;
     if constexpr (WLDS) {
@@ -976,8 +1019,8 @@ __device__ __forceinline__ void wave_block(const JobDesc &J, int rr0, uint8_t *s
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (wave >= J.RPW || rr0 + wave >= J.R) return;
-    wave_run<WT, F, 1, false, WLDS, CLAMP, FEAT>(J, rr0 + wave, smem,
-                                                 smem + w_bytes + (F < 8 ? wave * 2048 : 0), 0);
+    wave_run<WT, F, 1, false, WLDS, CLAMP, FEAT, VK>(J, rr0 + wave, smem,
+                                                     smem + w_bytes + (F < 8 ? wave * 2048 : 0), 0);
 }
 
 // A team of J.NW waves and J.NH random-number waves for replica rr; HB: Philox
@@ -997,7 +1040,7 @@ __device__ __forceinline__ void team_block(const JobDesc &J, int rr, uint8_t *sm
 template <typename WT, int F, bool WLDS, bool CLAMP, bool FEAT>
 __global__ __launch_bounds__(1024) void k_wave(JobDesc J) {
     extern __shared__ __align__(16) uint8_t smem[];
-    wave_block<WT, F, WLDS, CLAMP, FEAT>(J, blockIdx.x * J.RPW, smem);
+    wave_block<WT, F, WLDS, CLAMP, FEAT, F == 16 && sizeof(WT) == 2>(J, blockIdx.x * J.RPW, smem);
 }
 
 template <typename WT, int F, int NWC, int HB, bool CLAMP, bool FEAT>
