@@ -112,3 +112,27 @@ def test_timed_short_schedules(api, N, S, L, form):
                         steps=S, seed=9)
     for k in KEYS:
         assert np.array_equal(gpu[k], ref[k]), k
+
+
+def test_served_jobs(api):
+    """Jobs of both kernels in one server, epochs that cut levels and steps."""
+    f = 2**15
+    g = np.random.default_rng(8)
+    jobs = []
+    for N, R, S in ((90, 5, 1000), (300, 3, 700)):
+        Q = np.triu(g.integers(-2, 3, size=(N, N)), 1).astype(np.int32) * f
+        jobs.append((Q, api.schedule(3e5, 1e4, "geometric", 6, eoff_inc=f), R, S, N, 2))
+    Q = instances.ising_to_qubo(instances.sk_bimodal(70, 2))[0]
+    jobs.append((Q, api.schedule(30.0, 1.0, "geometric", 6, eoff_inc=1), 9, 900, 1, 0))
+    want = [api.da_anneal(api.da_create(Q, hint), sch, R, S, seed)
+            for Q, sch, R, S, seed, hint in jobs]
+    srv = api.da_server_create(1 << 30, epoch_steps=151)
+    tickets = [api.da_submit(srv, Q, sch, R, S, seed, hint) for Q, sch, R, S, seed, hint in jobs]
+    got = [api.da_wait(srv, t) for t in tickets]
+    srv.close()
+    for a, (Q, sch, R, S, seed, hint) in enumerate(jobs):
+        ref = oracle.anneal(Q, T_hi=sch.T_hi, T_lo=sch.T_lo, n_levels=6, eoff_inc=sch.eoff_inc,
+                            replica_base=R - 1, replicas=1, steps=S, seed=seed)
+        for k in KEYS:
+            assert np.array_equal(got[a][k], want[a][k]), (a, k)
+            assert np.array_equal(got[a][k][R - 1], ref[k][0]), (a, k)
